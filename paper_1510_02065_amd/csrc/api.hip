@@ -280,22 +280,16 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
         if (hipDeviceGetAttribute(&lim, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess && lim > 0)
             h->num_cu = lim;
     }
-    // Packed layout of all instances, and the steps 1-3 kernel: one
-    // workgroup per facility triple when the largest instance's triple fits
-    // in LDS, else location cubes; k_sweep when every block is stored.
+    // Packed layout of all instances.
     const long long align_elems = 128 / (long long)h->elem;
     for (int k = 0; k < count; ++k) h->Nmax = std::max(h->Nmax, (int)Ns[k]);
-    if (h->dmode == qap::kAllBlocks)
-        h->sweep_kind = 0;
-    else
-        h->sweep_kind = QAP_OPS(h->precision, sweep_lds(h->Nmax)) <= h->lds_limit ? 2 : 1;
     h->inst.resize(count);
     for (int k = 0; k < count; ++k) {
         const int N = Ns[k], n1 = N - 1, n2 = N - 2;
         qap::Inst& I = h->inst[k];
         I.N = N;
         I.ntri = N * (N - 1) * (N - 2) / 6;
-        I.wpt = h->sweep_kind == 0 ? (N * n1 * n2 + 255) / 256 : h->sweep_kind == 1 ? qap::kSweepParts : 1;
+        I.wpt = (N * n1 * n2 + 255) / 256;
         I.pad_ = 0;
         I.offB = h->totalB;
         I.offC = h->totalC;
@@ -323,27 +317,26 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
             else   // pair-major, one block per pair, unpadded; instances start 128-byte aligned
                 h->totalD += ((nC / 2) * n2 * n2 + align_elems - 1) / align_elems * align_elems;
         }
-        h->totalWG += h->sweep_kind == 2 ? (long long)I.ntri : 8LL * ((I.ntri + 7) / 8) * I.wpt;
+        h->totalWG += 8LL * ((I.ntri + 7) / 8) * I.wpt;
     }
-    // One sweep launch per instance size when a batch mixes sizes.
-    if (h->sweep_kind == 2 && h->level == 2) {
-        h->sweep_nt = QAP_OPS(h->precision, triple_threads(h->Nmax));
+    // One sweep launch per instance size, the largest first.
+    if (h->dmode == qap::kHalfStore && h->level == 2) {
         std::vector<int> sizes(Ns, Ns + count);
         std::sort(sizes.begin(), sizes.end(), std::greater<int>());
         sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
-        if (sizes.size() > 1) {
-            for (int N : sizes) {
-                qap::SweepClass c;
-                c.N = N;
-                c.nt = QAP_OPS(h->precision, triple_threads(N));
-                for (int k = 0; k < count; ++k)
-                    if ((int)Ns[k] == N) {
-                        c.ids.push_back(k);
-                        c.pre.push_back(c.ntri);
-                        c.ntri += h->inst[k].ntri;
-                    }
-                h->sweep_cls.push_back(std::move(c));
-            }
+        for (int N : sizes) {
+            qap::SweepClass c;
+            c.N = N;
+            c.nt = QAP_OPS(h->precision, sweep_threads(N, h->lds_limit));
+            const long long tiles = QAP_OPS(h->precision, sweep_tiles(N));
+            for (int k = 0; k < count; ++k)
+                if ((int)Ns[k] == N) {
+                    const long long ntri = h->inst[k].ntri;
+                    c.ids.push_back(k);
+                    c.pre.push_back(c.nwg);
+                    c.nwg += c.nt == qap::kSweepBox ? 8 * ((ntri + 7) / 8) * tiles * tiles : ntri;
+                }
+            h->sweep_cls.push_back(std::move(c));
         }
     }
     // Segment-size classes of the three families.

@@ -89,15 +89,16 @@ struct ClassHost {
     FamilyClass dev() const { return FamilyClass{d_ids, d_pre, (int)ids.size(), total}; }
 };
 
-// Instances of one size in a batch: the per-triple cost sweep of steps 1-3
-// runs one launch per size, with the workgroup width and LDS for that size,
-// so a CU holds as many of the small instances' workgroups as fit.
+// Instances of one size: steps 1-3 run one launch per size, with the kernel,
+// the workgroup width and the LDS for that size, so a CU holds as many of the
+// small instances' workgroups as fit.
+constexpr int kSweepBox = -1;
 struct SweepClass {
     int N = 0;
     std::vector<int> ids;          // instances of this size
-    std::vector<long long> pre;    // first workgroup (triple) of each, within the launch
-    long long ntri = 0;            // triples of the launch
-    int nt = 0;                    // threads of a per-triple workgroup (0: persistent kernel)
+    std::vector<long long> pre;    // first workgroup of each, within the launch (kSweepBox), or first triple
+    long long nwg = 0;             // workgroups (kSweepBox) or triples of the launch
+    int nt = 0;                    // threads of a per-triple workgroup, 0: persistent kernel, kSweepBox: k_sweep_box
     int* d_ids = nullptr;
     long long* d_pre = nullptr;
 };
@@ -118,7 +119,6 @@ struct qap_rlt2 {
     long long pending = 0;   // iterations of qap_rlt2_step whose trace entries are still on the device
     int dmode = qap::kHalfStore;   // D storage and enumeration (kAllBlocks or kHalfStore)
     int Nmax = 0;                  // largest instance
-    int sweep_kind = 0;            // steps 1-3: 0 k_sweep, 1 k_sweep_cube, 2 k_sweep_triple
     bool tuned = false;
     size_t lds_limit = 65536;   // dynamic LDS a workgroup may request
     int num_cu = 256;           // compute units of the device
@@ -129,8 +129,7 @@ struct qap_rlt2 {
     long long totalB = 0, totalC = 0, totalD = 0, totalWG = 0;
     std::vector<long long> preB, preC, preWG;
     qap::ClassHost fam[3][4];   // [D, C, B][segment class]
-    std::vector<qap::SweepClass> sweep_cls;   // empty: one sweep launch over every instance
-    int sweep_nt = 0;                         // that launch: threads of a per-triple workgroup (0: persistent)
+    std::vector<qap::SweepClass> sweep_cls;   // kHalfStore: one sweep launch per instance size, largest first
     // Overlapped steps 1-4 of a batch of mixed sizes (qap_rlt2_ascend): the
     // sweep of each size runs on `stream`, and the D->C concentration of that
     // size on `stream2` as soon as its sweep is done, so one size's
@@ -182,10 +181,10 @@ struct Ops {
     static hipError_t certify(qap_rlt2* h);
     // Initial dual of instance k from device copies of F, D and B0 (nullable).
     static hipError_t init_instance(qap_rlt2* h, int k, const double* dF, const double* dDm, const double* dB0);
-    // Threads of a per-triple sweep workgroup at size N (0: persistent kernel).
-    static int triple_threads(int N);
-    // LDS of a per-triple sweep workgroup at size N ((size_t)-1: does not fit).
-    static size_t sweep_lds(int N);
+    // Kernel of steps 1-3 at size N (SweepClass::nt).
+    static int sweep_threads(int N, size_t lds_limit);
+    // Location tiles per axis of k_sweep_box at size N.
+    static int sweep_tiles(int N);
     // Batched assignment problems (qap_lap_solve) with `seg` lanes per
     // problem: slot s < count (count = *dcount if dcount is not null, the
     // grid sized for `count`) solves problem idx[s] (s if idx is null), by

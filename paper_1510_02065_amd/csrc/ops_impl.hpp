@@ -137,37 +137,65 @@ int triple_per_cu(int N)
     return nb;
 }
 
-// Steps 1-3 over `ntri` triples of the instances ids[0..K) (all instances
-// when ids is null), whose triples start at workgroups pre[0..K), laid out in
-// LDS for size N.  When a CU holds only one triple's workgroup, one persistent
+template <int PM, int BS>
+hipError_t launch_box(qap_rlt2* h, const SweepClass& c)
+{
+    using T = StoreT<PM>;
+    using Shape = BoxShape<BS>;
+    constexpr size_t lds = Shape::template lds<T>();
+    if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((k_sweep_box<PM, BS>), dim3((unsigned)c.nwg), dim3(Shape::NT), lds, h->stream,
+                       static_cast<T*>(h->dD), static_cast<const T*>(h->dCC), static_cast<T*>(h->dB), h->dTri, h->dInst,
+                       c.d_pre, c.d_ids, (int)c.ids.size(), h->dAct);
+    return hipGetLastError();
+}
+
+// Steps 1-3 over the instances of one size.  kSweepBox: one workgroup per
+// (j, n) tile pair of a triple.  Otherwise everything of a triple goes
+// through LDS: when a CU holds only one triple's workgroup, one persistent
 // workgroup per CU walks the triples and overlaps each triple's start with the
 // previous one's tiles; when it holds two or more (nt > 0), one workgroup of
 // nt threads per triple lets the hardware overlap them.  The workgroup that
 // takes an instance's first triple clears its B.
 template <int PM>
-hipError_t launch_triple(qap_rlt2* h, const long long* pre, const int* ids, int K, long long ntri, int N, int nt)
+hipError_t launch_sweep(qap_rlt2* h, const SweepClass& c)
 {
     using T = StoreT<PM>;
     T* B = static_cast<T*>(h->dB);
     T* D = static_cast<T*>(h->dD);
     const T* CC = static_cast<const T*>(h->dCC);
-    if (nt > 0) {
-        if (nt == kTripleThreadsSmall) {
-            const size_t lds = sweep_triple_lds<T, kTripleThreadsSmall>(N);
-            if (lds == (size_t)-1) return hipErrorInvalidConfiguration;
-            hipLaunchKernelGGL((k_sweep_triple<PM, kTripleThreadsSmall>), dim3((unsigned)ntri),
-                               dim3(kTripleThreadsSmall), lds, h->stream, D, CC, B, h->dTri, h->dInst, pre, ids, K,
-                               h->dAct);
-        } else {
-            const size_t lds = sweep_triple_lds<T>(N);
-            hipLaunchKernelGGL((k_sweep_triple<PM, kTripleThreads>), dim3((unsigned)ntri), dim3(kTripleThreads), lds,
-                               h->stream, D, CC, B, h->dTri, h->dInst, pre, ids, K, h->dAct);
+    const int K = (int)c.ids.size();
+    if (c.nt == kSweepBox) {
+        switch (box_edge<T>(c.N)) {
+#define QAP_BOX(BS) \
+    case BS: return launch_box<PM, BS>(h, c);
+            QAP_BOX(15) QAP_BOX(16)
+            default:
+                if constexpr (PM == kPrecF64) {
+                    switch (box_edge<T>(c.N)) { QAP_BOX(11) QAP_BOX(12) QAP_BOX(13) QAP_BOX(14) }
+                } else {
+                    switch (box_edge<T>(c.N)) {
+                        QAP_BOX(17) QAP_BOX(18) QAP_BOX(19) QAP_BOX(20) QAP_BOX(21) QAP_BOX(22)
+                    }
+                }
+#undef QAP_BOX
         }
+        return hipErrorInvalidConfiguration;
+    }
+    if (c.nt == kTripleThreadsSmall) {
+        const size_t lds = sweep_triple_lds<T, kTripleThreadsSmall>(c.N);
+        if (lds == (size_t)-1) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((k_sweep_triple<PM, kTripleThreadsSmall>), dim3((unsigned)c.nwg), dim3(kTripleThreadsSmall),
+                           lds, h->stream, D, CC, B, h->dTri, h->dInst, c.d_pre, c.d_ids, K, h->dAct);
+    } else if (c.nt == kTripleThreads) {
+        const size_t lds = sweep_triple_lds<T>(c.N);
+        hipLaunchKernelGGL((k_sweep_triple<PM, kTripleThreads>), dim3((unsigned)c.nwg), dim3(kTripleThreads), lds,
+                           h->stream, D, CC, B, h->dTri, h->dInst, c.d_pre, c.d_ids, K, h->dAct);
     } else {
-        const size_t lds = sweep_triple_lds<T>(N);
-        const long long grid = std::min<long long>(ntri, h->num_cu);
+        const size_t lds = sweep_triple_lds<T>(c.N);
+        const long long grid = std::min<long long>(c.nwg, h->num_cu);
         hipLaunchKernelGGL((k_sweep_triple_p<PM>), dim3((unsigned)grid), dim3(kTripleThreads), lds, h->stream, D, CC,
-                           B, h->dTri, h->dInst, pre, ids, K, ntri, N, h->dAct);
+                           B, h->dTri, h->dInst, c.d_pre, c.d_ids, K, c.nwg, c.N, h->dAct);
     }
     return hipGetLastError();
 }
@@ -175,8 +203,10 @@ hipError_t launch_triple(qap_rlt2* h, const long long* pre, const int* ids, int 
 }  // namespace
 
 template <int PM>
-int Ops<PM>::triple_threads(int N)
+int Ops<PM>::sweep_threads(int N, size_t lds_limit)
 {
+    using T = StoreT<PM>;
+    if (sweep_triple_lds<T>(N) > lds_limit) return kSweepBox;
     // The smaller workgroup when a CU holds two or more of them, else the larger
     // one when a CU holds two or more, else 0 (persistent).  Smaller
     // workgroups keep more triples in flight per CU, each waiting at its own
@@ -189,9 +219,9 @@ int Ops<PM>::triple_threads(int N)
 }
 
 template <int PM>
-size_t Ops<PM>::sweep_lds(int N)
+int Ops<PM>::sweep_tiles(int N)
 {
-    return sweep_triple_lds<StoreT<PM>>(N);
+    return box_tiles<StoreT<PM>>(N);
 }
 
 template <int PM>
@@ -224,23 +254,11 @@ hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
                                h->dInst, h->dPreWG, h->K, h->dAct);
             return hipGetLastError();
         }
-        if (h->sweep_kind == 2) {
-            if (h->sweep_cls.empty())
-                return launch_triple<PM>(h, h->dPreWG, nullptr, h->K, h->totalWG, h->Nmax, h->sweep_nt);
-            for (const SweepClass& c : h->sweep_cls) {
-                e = launch_triple<PM>(h, c.d_pre, c.d_ids, (int)c.ids.size(), c.ntri, c.N, c.nt);
-                if (e != hipSuccess) return e;
-            }
-            return hipSuccess;
+        for (const SweepClass& c : h->sweep_cls) {
+            e = launch_sweep<PM>(h, c);
+            if (e != hipSuccess) return e;
         }
-        const size_t lds = (size_t)6 * h->Nmax * h->Nmax * sizeof(T);
-        if (lds <= h->lds_limit)
-            hipLaunchKernelGGL((k_sweep_cube<PM, true>), dim3((unsigned)h->totalWG), dim3(256), lds, st, D, CC, B,
-                               h->dTri, h->dInst, h->dPreWG, h->K, h->Nmax, h->dAct);
-        else
-            hipLaunchKernelGGL((k_sweep_cube<PM, false>), dim3((unsigned)h->totalWG), dim3(256), 0, st, D, CC, B,
-                               h->dTri, h->dInst, h->dPreWG, h->K, h->Nmax, h->dAct);
-        return hipGetLastError();
+        return hipSuccess;
     }
     case 4:
         if (h->level == 1) return hipSuccess;
@@ -272,7 +290,7 @@ hipError_t Ops<PM>::enqueue_sweep_concentrate_overlapped(qap_rlt2* h)
     if ((e = hipStreamWaitEvent(Bs, h->ev_fork, 0)) != hipSuccess) return e;
     for (size_t i = 0; i < h->sweep_cls.size() && e == hipSuccess; ++i) {
         const SweepClass& c = h->sweep_cls[i];
-        e = launch_triple<PM>(h, c.d_pre, c.d_ids, (int)c.ids.size(), c.ntri, c.N, c.nt);
+        e = launch_sweep<PM>(h, c);
         if (e == hipSuccess) e = hipEventRecord(h->ev_size[i], A);
         if (e == hipSuccess) e = hipStreamWaitEvent(Bs, h->ev_size[i], 0);
         if (e != hipSuccess) break;

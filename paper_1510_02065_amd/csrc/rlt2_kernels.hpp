@@ -286,13 +286,13 @@ __device__ __forceinline__ int entry_of(int N, int a, int la, int b, int lb, int
 struct Inst {
     int N;
     int ntri;          // N(N-1)(N-2)/6 facility triples
-    int wpt;           // sweep workgroups per facility triple
+    int wpt;           // k_sweep workgroups per facility triple
     int pad_;
     long long offB;    // first entry of the instance in the packed B array
     long long offC;    // first entry in the packed C (and CC) arrays
     long long offD;    // first entry in the packed D array
     long long ldD;     // block stride of D (>= (N-2)^2, 128-byte multiple)
-    long long wg0;     // first sweep workgroup (a multiple of 8)
+    long long wg0;     // first k_sweep workgroup (a multiple of 8)
     long long tri0;    // first int of the instance's facility-triple table
 };
 
@@ -430,7 +430,7 @@ __device__ __forceinline__ void clear_inst_B(T* __restrict__ B, const Inst& I, i
 // triple's six sub-arrays (6 N(N-1)(N-2) entries) together and the partially
 // used cache lines of the four strided members meet in its L2.
 // The first totalB threads of the grid also clear B.  Used when every block
-// is stored; see k_sweep_cube for one block per complementary pair.
+// is stored; see k_sweep_box for one block per complementary pair.
 template <int PM>
 __global__ __launch_bounds__(256) void k_sweep(StoreT<PM>* __restrict__ Dd, const StoreT<PM>* __restrict__ CC,
                                                StoreT<PM>* __restrict__ B, const int* __restrict__ tri,
@@ -508,27 +508,63 @@ __global__ __launch_bounds__(256) void k_sweep(StoreT<PM>* __restrict__ Dd, cons
     Dk[a5] = mean;
 }
 
-// Steps 1-3 with one stored block per complementary pair (pair_row).  As
+// ---- steps 1-3 in boxes of location triples -----------------------------------
+// One stored block per complementary pair (pair_row), for instances whose
+// facility triple does not fit in LDS whole (see k_sweep_triple).  As
 // i < k < p, members (P1 P2 P3) and (P2 P1 P3) share one stored entry A,
-// (P1 P3 P2) and (P3 P1 P2) share B, and (P2 P3 P1) and (P3 P2 P1) share C;
-// each member still gets its own block's spread share, in k_sweep's order,
-// so the sum has the same bits as with every block stored.
-//
-// Workgroups: kSweepParts per facility triple, on one XCD (ids congruent to
-// the triple mod 8, as in k_sweep, so lines shared between them meet in that
-// XCD's L2).  A workgroup first stages the six N x N tables of spread shares
-// of its triple in LDS (X[m][a][b] = CC of block (f1, a, f2, b) for the six
-// ordered facility pairs), so the groups read them from LDS instead of
-// making scattered L2 requests.  Each wave then takes 4 x 4 x 4 cubes of
-// location triples (j, n, q), two at a time:
+// (P1 P3 P2) and (P3 P1 P2) share B, and (P2 P3 P1) and (P3 P2 P1) share C:
 //   A = D_{(i,j),(k,n)}[p][q]  (contiguous over q),
 //   B = D_{(i,j),(p,q)}[k][n]  (contiguous over n),
 //   C = D_{(k,n),(p,q)}[i][j]  (contiguous over j),
-// each in the triple's own run of the pair-major layout, so each member's 64
-// lanes fall on 16 runs of 4 consecutive entries.  Groups with a repeated
-// location and cube cells past N are masked off.  STAGE = false (tables too
-// large for LDS, N > 58 in FP64) reads the spread shares from global memory.
-constexpr int kSweepParts = 8;
+// each in the triple's own run of the pair-major layout; each member still
+// gets its own block's spread share, in k_sweep's order, so the sum has the
+// same bits as with every block stored.
+//
+// A workgroup takes the boxes of BS x BS x BS locations (j, n, q) of one
+// (j, n) tile pair of one triple, q tile by q tile.  Threads are pairs of
+// tile coordinates and loop over the third one, a different pair for each
+// member, so that neighbouring lanes run along the member's contiguous axis:
+// (n, q) for A and for the means, (n, q) with n fastest for B, (j, q) with j
+// fastest for C.  B and C are turned through LDS (rows of RS and planes of PS
+// entries, both odd, so that either direction touches distinct banks); the
+// means go back through B's tile.  The next box's entries are requested before
+// the current box is computed.  Buffer loads and stores take a per-lane byte
+// offset and drop lanes whose offset lies past the run, which is how cells
+// with a repeated location or past N are masked without a branch.
+// Bound by HBM: the runs of BS entries start at any 8 (4) byte boundary and
+// the lines they share with the neighbouring boxes leave the L2 before those
+// are read, so a run moves about one 64-byte sector more on reads and half of
+// one more on writes than it holds (N = 40 FP64: 38.6 GB for 28.2 GB of
+// entries, at 4.9 TB/s).  Longer edges therefore move less but hold fewer
+// workgroups per CU.  Measured (ms, one sweep): FP64 N = 31 1.55 with edge 16
+// and 1.91 with 11, N = 40 8.1 with 14 and 10.0 with 20 (one workgroup per
+// CU); FP32 nearest N = 40 5.05 with 20 and 5.86 with 14, N = 48 15.2 with 16
+// and 23.6 with 24 (spills).  4 x 4 x 4 cubes per wave, 32-byte runs, took
+// 2.10 ms at N = 31 and 10.98 at N = 40 in FP64 and 8.39 at N = 40 in
+// certified FP32 (now 5.5).
+// The box edge: as few tiles as edges of at most kBoxMax entries allow, and
+// then the smallest edge that covers N with them.
+template <typename T>
+constexpr int kBoxMax = sizeof(T) == 8 ? 16 : 22;
+template <typename T>
+constexpr int kBoxMin = sizeof(T) == 8 ? 11 : 15;   // the edges of N = 26 .. 64 (FP32: 33 .. 64) are not smaller
+
+template <typename T>
+__host__ __device__ inline int box_tiles(int N) { return (N + kBoxMax<T> - 1) / kBoxMax<T>; }
+template <typename T>
+inline int box_edge(int N)
+{
+    const int e = (N + box_tiles<T>(N) - 1) / box_tiles<T>(N);
+    return e < kBoxMin<T> ? kBoxMin<T> : e;
+}
+template <int BS>
+struct BoxShape {
+    static constexpr int NT = (BS * BS + 63) / 64 * 64;   // threads
+    static constexpr int RS = BS | 1;                     // row stride of a turned tile
+    static constexpr int PS = (BS * RS) | 1;              // plane stride
+    template <typename T>
+    static constexpr size_t lds() { return (size_t)(2 * BS * PS + 4 * BS * BS) * sizeof(T); }
+};
 
 template <int PM, typename T = StoreT<PM>>
 __device__ __forceinline__ T six_way_mean(T A0, T B0, T C0, T x0, T x1, T x2, T x3, T x4, T x5)
@@ -555,98 +591,160 @@ __device__ __forceinline__ T six_way_mean(T A0, T B0, T C0, T x0, T x1, T x2, T 
     }
 }
 
-template <int PM, bool STAGE>
-__global__ __launch_bounds__(256) void k_sweep_cube(StoreT<PM>* __restrict__ Dd, const StoreT<PM>* __restrict__ CC,
-                                                    StoreT<PM>* __restrict__ B, const int* __restrict__ tri,
-                                                    const Inst* __restrict__ inst,
-                                                    const long long* __restrict__ preWG, int K, int Nmax,
-                                                    const int* __restrict__ act)
+// Buffer access to a run of T: the lane's byte offset is checked against the
+// run's size by the hardware (a load past it gives 0, a store is dropped).
+template <typename T>
+struct RunBuf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ RunBuf(T* base, int entries)
+        : r(__builtin_amdgcn_make_buffer_rsrc(base, (short)0, entries * (int)sizeof(T), 0x00020000)) {}
+    __device__ __forceinline__ T load(unsigned off) const {
+        if constexpr (sizeof(T) == 8) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+            return __hiloint2double((int)w[1], (int)w[0]);
+        } else {
+            return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+        }
+    }
+    __device__ __forceinline__ void store(T x, unsigned off) const {
+        if constexpr (sizeof(T) == 8) {
+            typedef unsigned u2 __attribute__((ext_vector_type(2)));
+            u2 w;
+            w[0] = (unsigned)__double2loint(x);
+            w[1] = (unsigned)__double2hiint(x);
+            __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)off, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)off, 0, 0);
+        }
+    }
+};
+
+// Workgroups: those of a triple have ids congruent to the triple mod 8 and
+// consecutive among that XCD's ids (as in k_sweep), so the lines its boxes
+// share meet in that XCD's L2.  pre/ids as in k_sweep_triple, with
+// 8 ceil(ntri / 8) box_tiles^2 workgroups per instance.
+template <int PM, int BS>
+__global__ __launch_bounds__(BoxShape<BS>::NT, 2) void k_sweep_box(
+    StoreT<PM>* __restrict__ Dd, const StoreT<PM>* __restrict__ CC, StoreT<PM>* __restrict__ B,
+    const int* __restrict__ tri, const Inst* __restrict__ inst, const long long* __restrict__ pre,
+    const int* __restrict__ ids, int K, const int* __restrict__ act)
 {
     using T = StoreT<PM>;
+    constexpr int NT = BoxShape<BS>::NT, RS = BoxShape<BS>::RS, PS = BoxShape<BS>::PS;
+    constexpr unsigned OUT = ~0u;   // past every run
     extern __shared__ __align__(16) unsigned char smem[];
-    T* __restrict__ X = reinterpret_cast<T*>(smem);   // [6][Nmax][Nmax]
-    const int kk = find_seg(preWG, K, (long long)blockIdx.x);
-    if (!act[kk]) return;   // whole workgroup
-    const Inst I = inst[kk];
-    const int lbk = (int)((long long)blockIdx.x - I.wg0);
-    if (lbk == 0) clear_inst_B(B, I, threadIdx.x, 256);
-    const int xcd = lbk & 7;
-    const int local = lbk >> 3;
-    const int t = (local / kSweepParts) * 8 + xcd;
-    if (t >= I.ntri) return;   // whole workgroup
-    const int part = local % kSweepParts;
+    T* __restrict__ Bt = reinterpret_cast<T*>(smem);   // [j][n][q], then the means
+    T* __restrict__ Ct = Bt + BS * PS;                 // [j][n][q]
+    T* __restrict__ X0 = Ct + BS * PS;                 // spread shares [j][n], [j][q], [j][n] (of n, j), [j][q] (of q, j)
+    T* __restrict__ X1 = X0 + BS * BS;
+    T* __restrict__ X2 = X1 + BS * BS;
+    T* __restrict__ X4 = X2 + BS * BS;
+    const int s = find_seg(pre, K, (long long)blockIdx.x);
+    const int id = ids[s];
+    if (!act[id]) return;   // whole workgroup
+    const Inst I = inst[id];
     const int N = I.N, n1 = N - 1, n2 = N - 2;
+    const int nt = box_tiles<T>(N);
+    const int lbk = (int)((long long)blockIdx.x - pre[s]);
+    const int local = lbk >> 3;
+    const int t = (local / (nt * nt)) * 8 + (lbk & 7);
+    const int tid = threadIdx.x;
+    if (lbk == 0) clear_inst_B(B, I, tid, NT);
+    if (t >= I.ntri) return;   // whole workgroup
+    const int w = local % (nt * nt);
+    const int j0 = (w / nt) * BS, nn0 = (w % nt) * BS;
     const int* tr = tri + I.tri0 + 3 * t;
     const int i = tr[0], k = tr[1], p = tr[2];
+    const int run = N * n1 * n2;
     T* __restrict__ Dk = Dd + I.offD;
     const T* __restrict__ CCk = CC + I.offC;
-
-    // Spread shares of the triple: X[m][a][b] = CC of block (f1_m, a, f2_m, b),
-    // (f1, f2) = (i,k), (i,p), (k,i), (k,p), (p,i), (p,k).
-    const int NN = Nmax * Nmax;
-    if constexpr (STAGE) {
-        for (int x = threadIdx.x; x < 6 * N * N; x += 256) {
-            const int m = x / (N * N), r = x - m * N * N;
-            const int a = r / N, b = r - a * N;
-            if (a == b) continue;
-            const int f1 = m < 2 ? i : m < 4 ? k : p;
-            const int f2 = (m == 0 || m == 5) ? k : (m == 1 || m == 3) ? p : i;
-            X[m * NN + a * Nmax + b] = CCk[beta_of(N, f1, a, f2, b)];
-        }
-        __syncthreads();
-    }
-    auto share = [&](int m, int a, int b) -> T {
-        if constexpr (STAGE) {
-            return X[m * NN + a * Nmax + b];
-        } else {
-            const int f1 = m < 2 ? i : m < 4 ? k : p;
-            const int f2 = (m == 0 || m == 5) ? k : (m == 1 || m == 3) ? p : i;
-            return CCk[beta_of(N, f1, a, f2, b)];
-        }
+    const RunBuf<T> gA(Dk + (pair_index(N, i, k) * n2 + (p - 2)) * run, run);
+    const RunBuf<T> gB(Dk + (pair_index(N, i, p) * n2 + (k - 1)) * run, run);
+    const RunBuf<T> gC(Dk + (pair_index(N, k, p) * n2 + i) * run, run);
+    // This thread's pair of tile coordinates; threads past the last pair lie
+    // outside every tile.
+    const bool on = tid < BS * BS;
+    const int hi = on ? tid / BS : 0, lo = tid - hi * BS;
+    const int far = on ? 0 : N;   // added to a location: outside
+    // Byte offsets in the three runs of group (j, n, q), OUT when it is not one.
+    auto valid = [&](int j, int n, int q) { return j < N && n < N && q < N && j != n && j != q && n != q; };
+    auto row = [&](int a, int b) { return (int)__umul24(__umul24(a, n1) + b - (b > a), n2); };
+    auto offset = [&](int a, int b, int c, bool ok) -> unsigned {
+        return ok ? (unsigned)(row(a, b) + c - (c > a) - (c > b)) * (unsigned)sizeof(T) : OUT;
     };
-
-    const long long NL = (long long)N * n1;
-    const long long rA = (pair_index(N, i, k) * n2 + (p - 2)) * NL * n2;
-    const long long rB = (pair_index(N, i, p) * n2 + (k - 1)) * NL * n2;
-    const long long rC = (pair_index(N, k, p) * n2 + i) * NL * n2;
-    const int nt = (N + 3) >> 2;   // cube tiles per axis
-    const int ncube = nt * nt * nt;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int stride = kSweepParts * 4;
-    for (int c0 = part * 4 + wave; c0 < ncube; c0 += 2 * stride) {
-        int j[2], n[2], q[2];
-        bool ok[2];
-        int64_t aA[2], aB[2], aC[2];
-        T A0[2], B0[2], C0[2];
-        for (int u = 0; u < 2; ++u) {
-            const int cube = c0 + u * stride;
-            const int tq = cube % nt, tn = (cube / nt) % nt, tj = cube / (nt * nt);
-            j[u] = tj * 4 + (lane >> 4);
-            n[u] = tn * 4 + ((lane >> 2) & 3);
-            q[u] = tq * 4 + (lane & 3);
-            ok[u] = cube < ncube && j[u] < N && n[u] < N && q[u] < N && j[u] != n[u] && j[u] != q[u] &&
-                    n[u] != q[u];
-            const int jj = j[u], nn = n[u], qq = q[u];
-            const int jn = nn - (nn > jj), jq = qq - (qq > jj), nj = jj - (jj > nn), nq = qq - (qq > nn);
-            aA[u] = rA + ((jj * n1 + jn) * n2 + (jq - (qq > nn)));
-            aB[u] = rB + ((jj * n1 + jq) * n2 + (jn - (nn > qq)));
-            aC[u] = rC + ((nn * n1 + nq) * n2 + (nj - (jj > qq)));
-            if (ok[u]) {
-                A0[u] = Dk[aA[u]];
-                B0[u] = Dk[aB[u]];
-                C0[u] = Dk[aC[u]];
+    auto offA = [&](int j, int n, int q) { return offset(j, n, q, valid(j, n, q)); };
+    auto offB = [&](int j, int n, int q) { return offset(j, q, n, valid(j, n, q)); };
+    auto offC = [&](int j, int n, int q) { return offset(n, q, j, valid(j, n, q)); };
+    // CC of block (f1, a, f2, b); entries that no group reads load CCk[0].
+    auto share = [&](int f1, int a, int f2, int b) -> T {
+        return CCk[(a == b || a >= N || b >= N) ? 0 : beta_of(N, f1, a, f2, b)];
+    };
+    T ra[BS], rb[BS], rc[BS], na[BS];
+    T x1, x4, x3, x5;
+    auto fetch = [&](T (&a)[BS], int q0) {
+        int q = q0 + lo + far, n = nn0 + hi;      // A and the means
+        int qb = q0 + hi + far, nb = nn0 + lo;    // B (and q of C)
+        int jc = j0 + lo;                         // C
+        // The locations pass through an empty asm so that what the offsets of
+        // every u share is not kept in registers across the boxes.
+        asm volatile("" : "+v"(q), "+v"(n), "+v"(qb), "+v"(nb), "+v"(jc));
+#pragma unroll
+        for (int u = 0; u < BS; ++u) {
+            a[u] = gA.load(offA(j0 + u, n, q));
+            rb[u] = gB.load(offB(j0 + u, nb, qb));
+            rc[u] = gC.load(offC(jc, nn0 + u, qb));
+            if (u & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        x1 = share(i, j0 + hi, p, q);
+        x4 = share(p, q, i, j0 + hi);
+        x3 = share(k, n, p, q);
+        x5 = share(p, q, k, n);
+    };
+    fetch(ra, 0);
+    if (on) {
+        X0[tid] = share(i, j0 + hi, k, nn0 + lo);
+        X2[tid] = share(k, nn0 + lo, i, j0 + hi);
+    }
+    const int own = hi * RS + lo;   // (n, q) of this thread in a plane
+    for (int tq = 0; tq < nt; ++tq) {
+        const int q0 = tq * BS;
+        // The box into LDS.
+        if (on) {
+#pragma unroll
+            for (int u = 0; u < BS; ++u) {
+                Bt[u * PS + lo * RS + hi] = rb[u];
+                Ct[lo * PS + u * RS + hi] = rc[u];
+            }
+            X1[tid] = x1;
+            X4[tid] = x4;
+        }
+        const T y3 = x3, y5 = x5;
+        __syncthreads();
+        if (tq + 1 < nt) fetch(na, q0 + BS);
+        if (on) {
+#pragma unroll
+            for (int u = 0; u < BS; ++u) {
+                const T mean = six_way_mean<PM>(ra[u], Bt[u * PS + own], Ct[u * PS + own], X0[u * BS + hi],
+                                                X1[u * BS + lo], X2[u * BS + hi], y3, X4[u * BS + lo], y5);
+                ra[u] = mean;
+                Bt[u * PS + own] = mean;
+                if ((u & 1)) __builtin_amdgcn_sched_barrier(0);
             }
         }
-        for (int u = 0; u < 2; ++u) {
-            if (!ok[u]) continue;
-            const int jj = j[u], nn = n[u], qq = q[u];
-            const T mean = six_way_mean<PM>(A0[u], B0[u], C0[u], share(0, jj, nn), share(1, jj, qq), share(2, nn, jj),
-                                           share(3, nn, qq), share(4, qq, jj), share(5, qq, nn));
-            Dk[aA[u]] = mean;
-            Dk[aB[u]] = mean;
-            Dk[aC[u]] = mean;
+        __syncthreads();
+        int q = q0 + lo + far, n = nn0 + hi;
+        int qb = q0 + hi + far, nb = nn0 + lo, jc = j0 + lo;
+        asm volatile("" : "+v"(q), "+v"(n), "+v"(qb), "+v"(nb), "+v"(jc));
+#pragma unroll
+        for (int u = 0; u < BS; ++u) {
+            gA.store(ra[u], offA(j0 + u, n, q));
+            gB.store(on ? Bt[u * PS + lo * RS + hi] : (T)0, offB(j0 + u, nb, qb));
+            gC.store(on ? Bt[lo * PS + u * RS + hi] : (T)0, offC(jc, nn0 + u, qb));
+            if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        __syncthreads();   // the means have been read
+#pragma unroll
+        for (int u = 0; u < BS; ++u) ra[u] = na[u];
     }
 }
 
@@ -669,7 +767,7 @@ __device__ __forceinline__ T& at32(T* base, unsigned idx)
 // reads the C run whole and the triple's six tables of spread shares, then
 // for each tile of JT locations j reads the A and B rows of those j (one
 // contiguous stretch each), forms the means of the tile's groups (j, n, q) as
-// k_sweep_cube does, and writes the rows back; finally it writes the C run
+// k_sweep_box does, and writes the rows back; finally it writes the C run
 // back.  Every HBM access is a run of consecutive entries.
 //
 // Every global load and store is issued unconditionally in straight-line code,
@@ -743,8 +841,8 @@ __device__ __forceinline__ void tile_group(T* __restrict__ As, T* __restrict__ B
     c = mean;
 }
 
-// Workgroup b takes triple b - pre[s] of instance ids[s] (of instance s when
-// ids is null), s the last of the K prefix entries with pre[s] <= b.  The
+// Workgroup b takes triple b - pre[s] of instance ids[s], s the last of the K
+// prefix entries with pre[s] <= b.  The
 // FP32 variants are compiled for eight waves per SIMD (64 VGPRs, two
 // 1024-thread workgroups per CU); the FP64 one would spill there.
 template <int PM, int NT>
@@ -756,7 +854,7 @@ __global__ __launch_bounds__(NT, PM == kPrecF64 ? 1 : 8) void k_sweep_triple(
     using T = StoreT<PM>;
     extern __shared__ __align__(16) unsigned char smem[];
     const int s = find_seg(pre, K, (long long)blockIdx.x);
-    const int id = ids ? ids[s] : s;
+    const int id = ids[s];
     if (!act[id]) return;   // whole workgroup
     const Inst I = inst[id];
     const int t = (int)((long long)blockIdx.x - pre[s]);
@@ -907,7 +1005,7 @@ __device__ __forceinline__ TripleRef<T> triple_ref(T* Dd, const T* CC, const int
                                                    const int* __restrict__ act)
 {
     const int s = find_seg(pre, K, Tg);
-    const int id = ids ? ids[s] : s;
+    const int id = ids[s];
     const Inst I = inst[id];
     const int t = (int)(Tg - pre[s]);
     TripleRef<T> r;

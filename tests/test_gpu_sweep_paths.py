@@ -27,3 +27,28 @@ def test_stored_half_matches_every_block(N, precision):
     np.testing.assert_array_equal(ta, tb)
     for x, y in zip(va, vb):
         np.testing.assert_array_equal(x, y)
+
+
+# Box edges of k_sweep_box: FP64 16 (two tiles, the last one short), 12 (three
+# tiles, the last one short), 13 (whole); FP32 18, 22 (the largest), 15 (three tiles).
+@pytest.mark.parametrize("N,precision", [(31, "fp64"), (34, "fp64"), (39, "fp64"), (36, "fp32n"), (44, "fp32"),
+                                         (45, "fp32n")])
+def test_box_sweep_matches_every_block(N, precision):
+    test_stored_half_matches_every_block(N, precision)
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_batch_across_sweep_kernels_equals_individual_handles(overlap):
+    # 27: boxes; 23: persistent per-triple; 16, 8: a workgroup per triple.
+    cases = [qapgen.clustered(27, 1), qapgen.small(8, 1), qapgen.clustered(23, 1), qapgen.uniform(16, 1)]
+    print("batch N =", [F.shape[0] for F, _ in cases], "overlap", overlap, flush=True)
+    g = Rlt2.batch([F for F, _ in cases], [D for _, D in cases], trace_level=2, overlap=overlap)
+    g.ascend(3)
+    for k, (F, D) in enumerate(cases):
+        h = Rlt2(F, D, trace_level=2)
+        h.ascend(3)
+        np.testing.assert_array_equal(h.trace()[0], g.trace_k(k)[0])
+        for x, y in zip(h.lap_values(), g.lap_values_k(k)):
+            np.testing.assert_array_equal(x, y)
+        h.close()
+    g.close()
