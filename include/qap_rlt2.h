@@ -99,17 +99,10 @@ typedef struct {
                          most recent iteration (qap_rlt2_lap_values)           */
     int use_graph;    /* 1 (default): qap_rlt2_ascend replays one captured HIP
                          graph per iteration; 0: plain launches                */
-    int autotune;     /* 1 (default): during the first qap_rlt2_ascend, time the
-                         concentration kernels of every family and size class
-                         over the lanes per problem (8, 16, 32 or 64, with as
-                         many columns per lane as the size needs) on a
-                         restored copy of the live data, and keep the fastest;
-                         the algorithm's decisions do not depend on the
-                         choice, only the rounding of its final sums.  0: the
-                         configuration with the most problems per wave that
-                         fits in LDS                                          */
-    const char* tune_cache; /* nullable path of a text file that stores the
-                         tuned choices and is read back by later handles     */
+    int autotune;     /* accepted and not used: the concentration kernels'
+                         launch shape follows from the problem size (every
+                         shape gives the same results)                       */
+    const char* tune_cache; /* likewise: no file is read or written          */
     int complementary; /* 1 (default): store one block of each pair of
                          complementary D blocks D_ijkn, D_knij (Section 6) and
                          concentrate it once, S going to both c_ijkn and
@@ -137,7 +130,7 @@ typedef struct {
 typedef struct qap_rlt2 qap_rlt2;
 
 /* Fill *opts with the defaults (FP64, current device, own stream,
- * trace_level 1, use_graph 1, autotune 1, no tune cache, complementary 1,
+ * trace_level 1, use_graph 1, complementary 1,
  * no stop rule, level 2). */
 qap_status qap_rlt2_default_opts(qap_rlt2_opts* opts);
 
@@ -358,8 +351,7 @@ qap_status qap_rlt2_load_state(qap_rlt2* h, int k, const double* lb, const doubl
                                const double* D);
 
 /* Snapshot of the whole handle (every instance's LB, B, C, D, stop flags,
- * iteration counts, traces and tuned kernel choices) into host memory, for
- * checkpointing a long run (Section 7).  *size receives the bytes needed;
+ * iteration counts and traces) into host memory, for checkpointing a long run (Section 7).  *size receives the bytes needed;
  * with buf NULL or capacity < *size nothing else is written (and QAP_OK is
  * returned when buf is NULL, QAP_EINVAL otherwise). */
 qap_status qap_rlt2_snapshot(qap_rlt2* h, void* buf, uint64_t capacity, uint64_t* size);

@@ -12,7 +12,6 @@
 #include <cstring>
 #include <functional>
 #include <limits>
-#include <map>
 #include <new>
 #include <string>
 #include <vector>
@@ -31,65 +30,6 @@ using qap::fail;
 
 namespace {
 
-// ---- autotuner cache ---------------------------------------------------------
-
-std::string tune_key(const qap_rlt2* h, int famk, const qap::ClassHost& c)
-{
-    char buf[128];
-    snprintf(buf, sizeof(buf), "gfx950 prec=%d fam=%d seg=%d nmax=%d", h->precision, famk, c.seg, c.nmax);
-    return buf;
-}
-
-std::map<std::string, std::pair<int, int>> read_tune_file(const std::string& path)
-{
-    std::map<std::string, std::pair<int, int>> m;
-    FILE* f = fopen(path.c_str(), "r");
-    if (!f) return m;
-    char line[256];
-    while (fgets(line, sizeof(line), f)) {
-        char* bar = strchr(line, '|');
-        if (!bar) continue;
-        *bar = 0;
-        int seg = 0, k = 0;
-        if (sscanf(bar + 1, "%d %d", &seg, &k) == 2) m[line] = {seg, k};
-    }
-    fclose(f);
-    return m;
-}
-
-void load_tune_cache(qap_rlt2* h)
-{
-    if (h->tune_cache.empty()) return;
-    const auto m = read_tune_file(h->tune_cache);
-    int hits = 0, need = 0;
-    for (int famk = 0; famk < 2; ++famk)
-        for (qap::ClassHost& c : h->fam[famk]) {
-            if (c.total <= 0) continue;
-            ++need;
-            auto it = m.find(tune_key(h, famk, c));
-            if (it != m.end() && qap::slot_cfg_allowed(it->second.first, it->second.second) &&
-                it->second.first * it->second.second >= c.nmax) {
-                c.seg_run = it->second.first;
-                c.k_run = it->second.second;
-                ++hits;
-            }
-        }
-    if (need > 0 && hits == need) h->tuned = true;
-}
-
-void save_tune_cache(const qap_rlt2* h)
-{
-    if (h->tune_cache.empty()) return;
-    auto m = read_tune_file(h->tune_cache);
-    for (int famk = 0; famk < 2; ++famk)
-        for (const qap::ClassHost& c : h->fam[famk])
-            if (c.total > 0) m[tune_key(h, famk, c)] = {c.seg_run, c.k_run};
-    if (FILE* f = fopen(h->tune_cache.c_str(), "w")) {
-        for (auto& kv : m) fprintf(f, "%s|%d %d\n", kv.first.c_str(), kv.second.first, kv.second.second);
-        fclose(f);
-    }
-}
-
 // ---- iteration schedule ------------------------------------------------------
 
 hipError_t enqueue_step_any(qap_rlt2* h, int step) { return QAP_OPS(h->precision, enqueue_step(h, step)); }
@@ -106,27 +46,6 @@ hipError_t enqueue_iteration(qap_rlt2* h)
         hipError_t e = enqueue_step_any(h, s);
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
-}
-
-// First iteration of a handle with autotuning: run the steps one by one and
-// tune each concentration family on its live data just before it runs.
-hipError_t tuned_first_iteration(qap_rlt2* h)
-{
-    hipError_t e;
-    if (h->lap_solver == QAP_LAP_SOLVER_AUCTION) {   // one column per lane: nothing to tune
-        h->tuned = true;
-        return enqueue_iteration(h);
-    }
-    if ((e = enqueue_step_any(h, 3)) != hipSuccess) return e;
-    if (h->level == 2 && (e = QAP_OPS(h->precision, tune_family(h, qap::kFamD))) != hipSuccess) return e;
-    if ((e = enqueue_step_any(h, 4)) != hipSuccess) return e;
-    if ((e = enqueue_step_any(h, 5)) != hipSuccess) return e;
-    if ((e = QAP_OPS(h->precision, tune_family(h, qap::kFamC))) != hipSuccess) return e;
-    if ((e = enqueue_step_any(h, 6)) != hipSuccess) return e;
-    if ((e = enqueue_step_any(h, 7)) != hipSuccess) return e;
-    h->tuned = true;
-    save_tune_cache(h);
     return hipSuccess;
 }
 
@@ -237,9 +156,7 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
     h->level = o.level;
     h->trace_level = std::max(0, std::min(2, o.trace_level));
     h->use_graph = o.use_graph ? 1 : 0;
-    h->autotune = o.autotune ? 1 : 0;
     h->lap_solver = o.lap_solver;
-    if (o.tune_cache) h->tune_cache = o.tune_cache;
     h->dmode = o.complementary ? qap::kHalfStore : qap::kAllBlocks;
     h->elem = o.precision == QAP_FP64 ? sizeof(double) : sizeof(float);
     h->stopK = o.K;
@@ -356,31 +273,6 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
             c.total += (f == 0) ? (h->dmode == qap::kAllBlocks ? nblk : nblk / 2) : (f == 1) ? (long long)N * N : 1;
         }
     }
-    // Default configuration of every class: the most problems per wave that
-    // fit (families D and C).  The B family (one problem per instance) is
-    // latency-bound: one column per lane, the smallest segment that holds it.
-    for (qap::ClassHost& c : h->fam[2]) {
-        if (c.total <= 0) continue;
-        const int seg = qap::seg_for(c.nmax);
-        if (qap::slot_lds_prec(h->precision, seg, 1, c.nmax) <= h->lds_limit) {
-            c.seg_run = seg;
-            c.k_run = 1;
-        }
-    }
-    for (auto& f : h->fam)
-        for (qap::ClassHost& c : f) {
-            if (c.total <= 0 || c.seg_run != 0) continue;
-            for (int seg : {8, 16, 32, 64}) {
-                const int k = (c.nmax + seg - 1) / seg;
-                if (!qap::slot_cfg_allowed(seg, k)) continue;
-                if (qap::slot_lds_prec(h->precision, seg, k, c.nmax) > h->lds_limit) continue;
-                c.seg_run = seg;
-                c.k_run = k;
-                break;
-            }
-            if (c.seg_run == 0) return bail(fail(QAP_EINVAL, "problem size needs more LDS than a workgroup has"));
-        }
-
     // The overlapped schedule: the D family split by instance size, in the
     // sweep classes' order, a second stream and the events between them.
     if (o.overlap && h->level == 2 && h->dmode == qap::kHalfStore && h->sweep_cls.size() > 1) {
@@ -448,7 +340,6 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
         CK(upload(&c.d_ids, c.ids, h->stream));
         CK(upload(&c.d_pre, c.pre, h->stream));
     }
-    if (h->autotune) load_tune_cache(h);
     const std::vector<int> ones(count, 1);
     const double stop[2] = {h->stopK, h->stopUB};
     CK(hipMemcpyAsync(h->dAct, ones.data(), count * sizeof(int), hipMemcpyHostToDevice, h->stream));
@@ -686,18 +577,6 @@ qap_status qap_rlt2_ascend(qap_rlt2* h, int iters, double* bound)
             if (e != hipSuccess) return mark_broken(h, e, "reading the stop flags");
             left = 0;
         }
-    }
-    if (left > 0 && h->autotune && !h->tuned) {
-        hipError_t e = tuned_first_iteration(h);
-        if (e != hipSuccess) return mark_broken(h, e, "autotuned first iteration");
-        e = hipStreamSynchronize(h->stream);
-        if (e != hipSuccess) return mark_broken(h, e, "hipStreamSynchronize");
-        st = drain_trace(h);
-        if (st != QAP_OK) {
-            h->broken = true;
-            return st;
-        }
-        --left;
     }
     while (left > 0) {
         // With the stop rule on, iterations go in small chunks so that the
@@ -1033,13 +912,15 @@ qap_status qap_rlt2_snapshot(qap_rlt2* h, void* buf, uint64_t capacity, uint64_t
     std::vector<char> v = snap_header(h);
     size_t need = v.size();
     for (const SnapPart& p : snap_parts(h)) need += p.bytes;
-    // host part: tuned choices, iteration counts and traces
+    // host part: kernel configurations (a fixed part of the format: a flag,
+    // then lanes per problem and columns per lane of every class), iteration
+    // counts and traces
     std::vector<char> tail;
-    put(tail, (int32_t)h->tuned);
+    put(tail, (int32_t)1);
     for (auto& f : h->fam)
         for (auto& c : f) {
-            put(tail, (int32_t)c.seg_run);
-            put(tail, (int32_t)c.k_run);
+            put(tail, (int32_t)c.seg);
+            put(tail, (int32_t)(c.seg ? 1 : 0));
         }
     for (int k = 0; k < h->K; ++k) {
         put(tail, (int64_t)h->itk[k]);
@@ -1082,13 +963,10 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
     if ((size_t)(end - p) < dev_bytes) return fail(QAP_EINVAL, "truncated snapshot");
     // Parse the host part before touching the device.
     const char* q = p + dev_bytes;
-    int32_t tuned = 0;
-    if (!get(q, end, tuned)) return fail(QAP_EINVAL, "truncated snapshot");
-    int32_t cfg[3][4][2];
-    for (int f = 0; f < 3; ++f)
-        for (int c = 0; c < 4; ++c)
-            if (!get(q, end, cfg[f][c][0]) || !get(q, end, cfg[f][c][1]))
-                return fail(QAP_EINVAL, "truncated snapshot");
+    // The kernel configurations do not depend on the snapshot.
+    int32_t cfg = 0;
+    for (int x = 0; x < 1 + 3 * 4 * 2; ++x)
+        if (!get(q, end, cfg)) return fail(QAP_EINVAL, "truncated snapshot");
     std::vector<int64_t> itk(h->K);
     std::vector<std::vector<double>> tl(h->K), tp(h->K);
     for (int k = 0; k < h->K; ++k) {
@@ -1102,15 +980,6 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
             get(q, end, tp[k][t]);
         }
     }
-    for (int f = 0; f < 3; ++f)
-        for (int c = 0; c < 4; ++c) {
-            qap::ClassHost& ch = h->fam[f][c];
-            if (ch.total <= 0) continue;
-            const int sg = cfg[f][c][0], kk = cfg[f][c][1];
-            if (!qap::slot_cfg_allowed(sg, kk) || sg * kk < ch.nmax ||
-                qap::slot_lds_prec(h->precision, sg, kk, ch.nmax) > h->lds_limit)
-                return fail(QAP_EINVAL, "snapshot holds a kernel configuration this device cannot run");
-        }
     QAP_HIP(hipStreamSynchronize(h->stream));
     for (const SnapPart& s : parts) {
         if (s.bytes) QAP_HIP(hipMemcpy(s.dev, p, s.bytes, hipMemcpyHostToDevice));
@@ -1118,22 +987,6 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
     }
     QAP_HIP(hipMemsetAsync(h->dCounter, 0, h->K * sizeof(long long), h->stream));
     QAP_HIP(hipStreamSynchronize(h->stream));
-    h->tuned = tuned != 0;
-    bool changed = false;
-    for (int f = 0; f < 3; ++f)
-        for (int c = 0; c < 4; ++c) {
-            qap::ClassHost& ch = h->fam[f][c];
-            if (ch.total <= 0) continue;
-            changed = changed || ch.seg_run != cfg[f][c][0] || ch.k_run != cfg[f][c][1];
-            ch.seg_run = cfg[f][c][0];
-            ch.k_run = cfg[f][c][1];
-        }
-    if (changed && h->graph_exec) {   // the captured launches used the old choices
-        (void)hipGraphExecDestroy(h->graph_exec);
-        (void)hipGraphDestroy(h->graph);
-        h->graph_exec = nullptr;
-        h->graph = nullptr;
-    }
     h->itk = itk;
     h->tLB = tl;
     h->tLBp = tp;
@@ -1177,8 +1030,6 @@ qap_status qap_rlt2_children(qap_rlt2* h, int k, int count, const int32_t* fac, 
     o.stream = h->own_stream ? nullptr : h->stream;
     o.trace_level = h->trace_level;
     o.use_graph = h->use_graph;
-    o.autotune = h->autotune;
-    o.tune_cache = h->tune_cache.empty() ? nullptr : h->tune_cache.c_str();
     o.complementary = h->dmode == qap::kHalfStore ? 1 : 0;
     o.K = h->stopK;
     o.UB = h->stopUB;

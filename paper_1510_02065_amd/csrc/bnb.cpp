@@ -439,7 +439,6 @@ struct Search {
         o.stream = p->stream;
         o.trace_level = 0;
         o.use_graph = 0;   // few iterations per handle: plain launches
-        o.autotune = 0;
         o.K = p->K;
         o.UB = threshold();
         return o;

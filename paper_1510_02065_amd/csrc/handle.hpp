@@ -42,44 +42,13 @@ inline unsigned grid_for(long long work, int threads) { return (unsigned)((work 
 // Per-instance trace entries kept on the device between host reads.
 constexpr long long kTraceCap = 1024;
 
-// (lanes per problem, columns per lane) configurations of the concentration
-// kernels; for a problem size n the candidates are (SEG, ceil(n/SEG)).
-inline bool slot_cfg_allowed(int seg, int k)
-{
-    switch (seg) {
-    case 8: return (k >= 1 && k <= 6) || k == 8;
-    case 16: return k >= 1 && k <= 4;
-    case 32: return k >= 1 && k <= 2;
-    case 64: return k == 1;
-    default: return false;
-    }
-}
-
-template <typename T, int SEG, int K>
-size_t slot_lds(int nmax) { return (size_t)(64 / SEG) * SlotLds<T, SEG, K>::bytes(nmax); }
-
-// LDS of a one-wave workgroup of the (seg, k) configuration at size nmax.
-template <typename T>
-size_t slot_lds_any(int seg, int k, int nmax)
-{
-#define QAP_CFG(SG, KK) \
-    if (seg == SG && k == KK) return slot_lds<T, SG, KK>(nmax);
-    QAP_CFG(8, 1) QAP_CFG(8, 2) QAP_CFG(8, 3) QAP_CFG(8, 4) QAP_CFG(8, 5) QAP_CFG(8, 6) QAP_CFG(8, 8)
-    QAP_CFG(16, 1) QAP_CFG(16, 2) QAP_CFG(16, 3) QAP_CFG(16, 4) QAP_CFG(32, 1) QAP_CFG(32, 2) QAP_CFG(64, 1)
-#undef QAP_CFG
-    return (size_t)-1;
-}
-
-inline size_t slot_lds_prec(int precision, int seg, int k, int nmax)
-{
-    return precision == kPrecF64 ? slot_lds_any<double>(seg, k, nmax) : slot_lds_any<float>(seg, k, nmax);
-}
+// LDS of a one-wave workgroup of the assignment kernels at size nmax.
+template <typename T, int SEG>
+size_t slot_lds(int nmax) { return (size_t)(64 / SEG) * SlotLds<T, SEG, 1>::bytes(nmax); }
 
 // Instances of one family that share a segment size.
 struct ClassHost {
-    int seg = 0;       // size bucket: next power of two >= n (8 at least)
-    int seg_run = 0;   // lanes per problem, chosen by the tuner
-    int k_run = 0;     // columns per lane (seg_run * k_run >= nmax)
+    int seg = 0;       // lanes per problem: next power of two >= n (8 at least)
     int nmax = 0;
     std::vector<int> ids;
     std::vector<long long> pre;
@@ -114,15 +83,12 @@ struct qap_rlt2 {
     bool own_stream = false;
     int trace_level = 1;
     int use_graph = 1;
-    int autotune = 1;
     int lap_solver = QAP_LAP_SOLVER_CANONICAL;   // qap_lap_solver of the concentrations
     long long pending = 0;   // iterations of qap_rlt2_step whose trace entries are still on the device
     int dmode = qap::kHalfStore;   // D storage and enumeration (kAllBlocks or kHalfStore)
     int Nmax = 0;                  // largest instance
-    bool tuned = false;
     size_t lds_limit = 65536;   // dynamic LDS a workgroup may request
     int num_cu = 256;           // compute units of the device
-    std::string tune_cache;
     size_t elem = 8;   // bytes per reduced cost
     double stopK = 0.0, stopUB = 0.0;   // stop rule of Algorithm 1 (UB <= 0: off)
     std::vector<qap::Inst> inst;
@@ -175,8 +141,6 @@ struct Ops {
     // One step of an iteration: 3 (steps 1-3, or step 1 at level 1), 4, 5,
     // 6, 7 (steps 7-8).
     static hipError_t enqueue_step(qap_rlt2* h, int step);
-    // Autotune family famk (kFamD or kFamC) on its live data.
-    static hipError_t tune_family(qap_rlt2* h, int famk);
     // FP64 certification cascade into h->dCert.
     static hipError_t certify(qap_rlt2* h);
     // Initial dual of instance k from device copies of F, D and B0 (nullable).

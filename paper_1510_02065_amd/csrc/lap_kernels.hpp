@@ -25,9 +25,8 @@ enum LapFamily : int { kFamD = 0, kFamC = 1 };
 // How the D family is stored and enumerated (see pair_block).
 enum DStorage : int {
     kAllBlocks = 0,    // every block stored (block-major); problem b is block b, parent c_b
-    kHalfStore = 1,    // one block per complementary pair stored (pair-major);
+    kHalfStore = 1     // one block per complementary pair stored (pair-major);
                        // problem h is stored block h, parents c_beta and c_twin
-    kHalfStoreTune = 2 // as kHalfStore, parent c_beta only (tuning runs)
 };
 
 // Copy an n x n block (row stride ld in global memory) into LDS (row stride
@@ -41,35 +40,29 @@ enum DStorage : int {
 constexpr int kStageRows = 24;
 constexpr int kStageTail = 8;
 
-template <typename T, int SEG, int K>
+template <typename T, int SEG>
 __device__ __forceinline__ void stage_block(T* __restrict__ M, int ldm, const T* __restrict__ blk, long long ld,
-                                            int n, int lane)
+                                            int n, int c)
 {
     const unsigned ldb = (unsigned)ld * (unsigned)sizeof(T);   // row stride in bytes (< 2^24 * 8)
+    if (c >= n) return;
+    const char* __restrict__ col = reinterpret_cast<const char*>(blk + c);
+    auto row_at = [&](int r) -> T {
+        return *reinterpret_cast<const T*>(col + (size_t)(unsigned)__umul24((unsigned)r, ldb));
+    };
+    {
+        T t[kStageRows];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int c = lane + k * SEG;
-        if (c < n) {
-            const char* __restrict__ col = reinterpret_cast<const char*>(blk + c);
-            auto row_at = [&](int r) -> T {
-                return *reinterpret_cast<const T*>(col + (size_t)(unsigned)__umul24((unsigned)r, ldb));
-            };
-            {
-                T t[kStageRows];
+        for (int u = 0; u < kStageRows; ++u) t[u] = row_at(min(u, n - 1));
 #pragma unroll
-                for (int u = 0; u < kStageRows; ++u) t[u] = row_at(min(u, n - 1));
+        for (int u = 0; u < kStageRows; ++u) M[__umul24((unsigned)min(u, n - 1), (unsigned)ldm) + c] = t[u];
+    }
+    for (int r0 = kStageRows; r0 < n; r0 += kStageTail) {
+        T t[kStageTail];
 #pragma unroll
-                for (int u = 0; u < kStageRows; ++u) M[__umul24((unsigned)min(u, n - 1), (unsigned)ldm) + c] = t[u];
-            }
-            for (int r0 = kStageRows; r0 < n; r0 += kStageTail) {
-                T t[kStageTail];
+        for (int u = 0; u < kStageTail; ++u) t[u] = row_at(min(r0 + u, n - 1));
 #pragma unroll
-                for (int u = 0; u < kStageTail; ++u) t[u] = row_at(min(r0 + u, n - 1));
-#pragma unroll
-                for (int u = 0; u < kStageTail; ++u)
-                    M[__umul24((unsigned)min(r0 + u, n - 1), (unsigned)ldm) + c] = t[u];
-            }
-        }
+        for (int u = 0; u < kStageTail; ++u) M[__umul24((unsigned)min(r0 + u, n - 1), (unsigned)ldm) + c] = t[u];
     }
 }
 
@@ -94,36 +87,31 @@ __device__ __forceinline__ long long xcd_major(long long b, long long grid)
 // scalar unit, and with the per-lane size otherwise (a wave across an
 // instance boundary, or with segments past the last problem, whose n is 0).
 // Both compute the same values.
-template <typename T, int SEG, int K, bool AUC, bool DOWN>
+template <typename T, int SEG, bool AUC, bool DOWN>
 __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, int lane, int nmax, int n, T* blk,
                                                   long long ld)
 {
-    const SlotScratch<T, SEG, K> sc(smem + seg * SlotLds<T, SEG, K>::bytes(nmax), n);
-    stage_block<T, SEG, K>(sc.M, sc.ld, blk, ld, n, lane);
+    const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(nmax), n);
+    stage_block<T, SEG>(sc.M, sc.ld, blk, ld, n, lane);
     wave_sync();
-    static_assert(!AUC || K == 1, "the auction solver takes one column per lane");
     if constexpr (AUC)
         return lap_auction_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, nullptr);
-    else if constexpr (K == 1)
-        return lap_concentrate_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, nullptr);
-    else if constexpr (SEG >= 16)
-        return lap_concentrate_flatk<T, SEG, K, DOWN>(sc, n, blk, ld, nullptr, nullptr);
     else
-        return lap_concentrate_slots<T, SEG, K, DOWN>(sc, n, blk, ld, nullptr, nullptr);
+        return lap_concentrate_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, nullptr);
 }
 
 // D -> C (FAM kFamD: blocks D_beta of size N-2, parent c_beta) or C -> B
-// (kFamC: blocks C_ij of size N-1, parent b_ij), K columns per lane, 64/SEG
+// (kFamC: blocks C_ij of size N-1, parent b_ij), one column per lane, 64/SEG
 // problems per wave, one wave per workgroup.  parent += S, the block is
 // replaced by its residual, values[...] = S when values is not null (values
 // are packed like the parents).  `mode` applies to the D family only.  AUC:
-// the auction solver (one column per lane only).  Registers: with one
-// column per lane the FP32 kernels are held to 72 VGPRs (seven waves per
-// SIMD, about what their LDS allows at n = 23) and the FP64 ones of up to 32
-// lanes to 80 (six waves: the LDS of the smaller problems of a batch allows
-// more than the 99 VGPRs they would otherwise take); neither spills.
-template <int PM, int SEG, int K, int FAM, bool AUC = false>
-__global__ __launch_bounds__(64, K > 1 ? 1 : (PM != kPrecF64 ? 7 : (SEG <= 32 ? 6 : 1)))
+// the auction solver.  Registers: the FP32 kernels are held to 72 VGPRs
+// (seven waves per SIMD, about what their LDS allows at n = 23) and the FP64
+// ones of up to 32 lanes to 80 (six waves: the LDS of the smaller problems of
+// a batch allows more than the 99 VGPRs they would otherwise take); neither
+// spills.
+template <int PM, int SEG, int FAM, bool AUC = false>
+__global__ __launch_bounds__(64, PM != kPrecF64 ? 7 : (SEG <= 32 ? 6 : 1))
 void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, StoreT<PM>* __restrict__ B,
                     const Inst* __restrict__ inst, FamilyClass fc, int nmax, double* __restrict__ values, int mode,
                     const int* __restrict__ act)
@@ -157,7 +145,7 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
                 blk = D + I.offD + base;
                 ld = (long long)I.N * (I.N - 1) * n;
                 pidx = I.offC + beta;
-                if (mode == kHalfStore) pidx2 = I.offC + tb;
+                pidx2 = I.offC + tb;
             }
         } else {
             n = I.N - 1;
@@ -169,8 +157,8 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
     const int nu = __builtin_amdgcn_readfirstlane(n);
     T* const bw = active ? blk : nullptr;
     const double S = ballot64(n != nu) == 0
-                         ? stage_and_solve<T, SEG, K, AUC, DOWN>(smem, seg, lane, nmax, nu, bw, ld)
-                         : stage_and_solve<T, SEG, K, AUC, DOWN>(smem, seg, lane, nmax, n, bw, ld);
+                         ? stage_and_solve<T, SEG, AUC, DOWN>(smem, seg, lane, nmax, nu, bw, ld)
+                         : stage_and_solve<T, SEG, AUC, DOWN>(smem, seg, lane, nmax, n, bw, ld);
     if (active && lane == 0) {
         T* parent = (FAM == kFamD) ? C : B;
         parent[pidx] = store_add<PM>(parent[pidx], S);
@@ -183,14 +171,14 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
 }
 
 // B -> LB' and LB += LB' (steps 7-8), one problem of size N per instance of
-// the class, K columns per lane.  lb[2k] = LB, lb[2k+1] = LB' (FP64; in FP32
+// the class.  lb[2k] = LB, lb[2k+1] = LB' (FP64; in FP32
 // certified mode the bound accumulates rounding toward -inf).  The instance's
 // trace gets (LB, LB') at position counter[k]++ when below trace_cap, and
 // sigma (nullable, packed like B) the assignment of the B problem, a
 // permutation of the instance.  Stop rule of Algorithm 1, with stop[0] = K and
 // stop[1] = UB (UB <= 0: none): the instance's act flag is cleared once
 // LB >= UB or LB' / UB < K.
-template <int PM, int SEG, int K, bool AUC = false>
+template <int PM, int SEG, bool AUC = false>
 __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, const Inst* __restrict__ inst,
                                                 FamilyClass fc, int nmax, double* __restrict__ lb,
                                                 double* __restrict__ trace, long long* __restrict__ counter,
@@ -210,20 +198,15 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     const Inst I = inst[k];
     const int n = active ? I.N : 0;
     T* blk = B + I.offB;
-    const SlotScratch<T, SEG, K> sc(smem + seg * SlotLds<T, SEG, K>::bytes(nmax), n);
-    stage_block<T, SEG, K>(sc.M, sc.ld, blk, n, n, lane);
+    const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(nmax), n);
+    stage_block<T, SEG>(sc.M, sc.ld, blk, n, n, lane);
     wave_sync();
     int32_t* sg = (active && sigma) ? sigma + I.offB : nullptr;
     double S;
-    static_assert(!AUC || K == 1, "the auction solver takes one column per lane");
     if constexpr (AUC)
         S = lap_auction_flat<T, SEG, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
-    else if constexpr (K == 1)
-        S = lap_concentrate_flat<T, SEG, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
-    else if constexpr (SEG >= 16)
-        S = lap_concentrate_flatk<T, SEG, K, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
     else
-        S = lap_concentrate_slots<T, SEG, K, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
+        S = lap_concentrate_flat<T, SEG, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
     if (active && lane == 0) {
         const double L = DOWN ? add_down(lb[2 * k], S) : lb[2 * k] + S;
         lb[2 * k] = L;
@@ -278,7 +261,7 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     // k_lap_family_s.
     auto solve = [&](int nn) __attribute__((always_inline)) -> double {
         const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(SEG), nn);
-        stage_block<T, SEG, 1>(sc.M, sc.ld, mat, nn, nn, lane);
+        stage_block<T, SEG>(sc.M, sc.ld, mat, nn, nn, lane);
         wave_sync();
         if constexpr (AUC)
             return lap_auction_flat<T, SEG, PM == kPrecF32Down>(sc, nn, Rw, nn, dw, aw);

@@ -1,6 +1,5 @@
 // Launch code of one precision mode: the kernels of one dual-ascent iteration
-// (Algorithm 1 of arXiv 1510.02065), the autotuner's timed runs, the
-// certification cascade, the initial dual, the batched assignment solve and
+// (Algorithm 1 of arXiv 1510.02065), the certification cascade, the initial dual, the batched assignment solve and
 // the children of a branch-and-bound node.  Included by ops_f64.hip,
 // ops_f32d.hip and ops_f32n.hip, each of which instantiates Ops<PM> for one
 // mode, so the three modes compile in parallel.
@@ -11,97 +10,99 @@ namespace qap {
 
 namespace {
 
-template <int PM, int SEG, int K, bool AUC = false>
-hipError_t launch_family_sk(qap_rlt2* h, int famk, const ClassHost& c, FamilyClass fc, double* values, int mode)
+template <int PM, int SEG, bool AUC>
+hipError_t launch_family_seg(qap_rlt2* h, int famk, const ClassHost& c, double* values)
 {
     using T = StoreT<PM>;
-    if (fc.total <= 0) return hipSuccess;
     constexpr int LPW = 64 / SEG;
-    const size_t lds = slot_lds<T, SEG, K>(c.nmax);
+    const FamilyClass fc = c.dev();
+    const size_t lds = slot_lds<T, SEG>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;   // not launched
     const unsigned grid = (unsigned)((fc.total + LPW - 1) / LPW);
     T* D = static_cast<T*>(h->dD);
     T* C = static_cast<T*>(h->dC);
     T* B = static_cast<T*>(h->dB);
     if (famk == kFamD)
-        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, K, kFamD, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C,
-                           B, h->dInst, fc, c.nmax, values, mode, h->dAct);
+        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamD, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
+                           h->dInst, fc, c.nmax, values, h->dmode, h->dAct);
     else
-        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, K, kFamC, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C,
-                           B, h->dInst, fc, c.nmax, values, kAllBlocks, h->dAct);
+        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamC, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
+                           h->dInst, fc, c.nmax, values, kAllBlocks, h->dAct);
     return hipGetLastError();
 }
 
-template <int PM>
-hipError_t launch_family_class(qap_rlt2* h, int famk, const ClassHost& c, FamilyClass fc, int seg, int k,
-                               double* values, int mode)
+template <int PM, int SEG, bool AUC>
+hipError_t launch_B_seg(qap_rlt2* h, const ClassHost& c)
 {
-#define QAP_CFG(SG, KK) \
-    if (seg == SG && k == KK) return launch_family_sk<PM, SG, KK>(h, famk, c, fc, values, mode);
-    QAP_CFG(8, 1) QAP_CFG(8, 2) QAP_CFG(8, 3) QAP_CFG(8, 4) QAP_CFG(8, 5) QAP_CFG(8, 6) QAP_CFG(8, 8)
-    QAP_CFG(16, 1) QAP_CFG(16, 2) QAP_CFG(16, 3) QAP_CFG(16, 4) QAP_CFG(32, 1) QAP_CFG(32, 2) QAP_CFG(64, 1)
-#undef QAP_CFG
-    return hipErrorInvalidConfiguration;
+    using T = StoreT<PM>;
+    constexpr int LPW = 64 / SEG;
+    const size_t lds = slot_lds<T, SEG>(c.nmax);
+    if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
+    const unsigned grid = (unsigned)((c.total + LPW - 1) / LPW);
+    const bool tr = h->trace_level >= 1;
+    hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
+                       h->dInst, c.dev(), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter, kTraceCap,
+                       h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
+    return hipGetLastError();
 }
 
-// The auction solver's launch for a size class: one column per lane, in the
-// class's own segment width.
-template <int PM>
-hipError_t launch_family_auction(qap_rlt2* h, int famk, const ClassHost& c, double* values, int mode)
-{
-    switch (c.seg) {
-    case 8: return launch_family_sk<PM, 8, 1, true>(h, famk, c, c.dev(), values, mode);
-    case 16: return launch_family_sk<PM, 16, 1, true>(h, famk, c, c.dev(), values, mode);
-    case 32: return launch_family_sk<PM, 32, 1, true>(h, famk, c, c.dev(), values, mode);
-    default: return launch_family_sk<PM, 64, 1, true>(h, famk, c, c.dev(), values, mode);
+// Lanes per problem: the narrowest segment that holds the class's problems
+// (seg_for), one column per lane.  Several columns per lane put more problems
+// in a wave, but the wave runs as many Dijkstra passes as its busiest problem
+// needs and holds more LDS, so a CU holds fewer waves: at n = 23 in FP64,
+// 0.97 ms for 32 lanes x 1 column, 1.29 for 16 x 2 and 2.46 for 8 x 3; at
+// n = 38, 27 ms for 64 x 1 and 41 for 32 x 2.
+#define QAP_BY_SEG(SEGV, CALL)   \
+    switch (SEGV) {              \
+    case 8: return CALL(8);      \
+    case 16: return CALL(16);    \
+    case 32: return CALL(32);    \
+    default: return CALL(64);    \
     }
+
+template <int PM>
+hipError_t launch_family_class(qap_rlt2* h, int famk, const ClassHost& c, double* values)
+{
+    if (c.total <= 0) return hipSuccess;
+    if (h->lap_solver == QAP_LAP_SOLVER_AUCTION) {
+#define QAP_CALL(SG) launch_family_seg<PM, SG, true>(h, famk, c, values)
+        QAP_BY_SEG(c.seg, QAP_CALL)
+#undef QAP_CALL
+    }
+#define QAP_CALL(SG) launch_family_seg<PM, SG, false>(h, famk, c, values)
+    QAP_BY_SEG(c.seg, QAP_CALL)
+#undef QAP_CALL
 }
 
 template <int PM>
 hipError_t launch_family(qap_rlt2* h, int famk, double* values)
 {
     for (const ClassHost& c : h->fam[famk]) {
-        if (c.total <= 0) continue;
-        hipError_t e = h->lap_solver == QAP_LAP_SOLVER_AUCTION
-                           ? launch_family_auction<PM>(h, famk, c, values, h->dmode)
-                           : launch_family_class<PM>(h, famk, c, c.dev(), c.seg_run, c.k_run, values, h->dmode);
+        hipError_t e = launch_family_class<PM>(h, famk, c, values);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <int PM, int SEG, int K, bool AUC = false>
-hipError_t launch_B_sk(qap_rlt2* h, const ClassHost& c)
+template <int PM>
+hipError_t launch_B_class(qap_rlt2* h, const ClassHost& c)
 {
-    using T = StoreT<PM>;
-    constexpr int LPW = 64 / SEG;
-    const size_t lds = slot_lds<T, SEG, K>(c.nmax);
-    if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
-    const unsigned grid = (unsigned)((c.total + LPW - 1) / LPW);
-    const bool tr = h->trace_level >= 1;
-    hipLaunchKernelGGL((k_lap_B_s<PM, SEG, K, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
-                       h->dInst, c.dev(), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter, kTraceCap,
-                       h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
-    return hipGetLastError();
+    if (c.total <= 0) return hipSuccess;
+    if (h->lap_solver == QAP_LAP_SOLVER_AUCTION) {
+#define QAP_CALL(SG) launch_B_seg<PM, SG, true>(h, c)
+        QAP_BY_SEG(c.seg, QAP_CALL)
+#undef QAP_CALL
+    }
+#define QAP_CALL(SG) launch_B_seg<PM, SG, false>(h, c)
+    QAP_BY_SEG(c.seg, QAP_CALL)
+#undef QAP_CALL
 }
 
 template <int PM>
 hipError_t launch_B(qap_rlt2* h)
 {
     for (const ClassHost& c : h->fam[2]) {
-        if (c.total <= 0) continue;
-        hipError_t e = hipErrorInvalidConfiguration;
-#define QAP_CFG(SG, KK) \
-    else if (c.seg_run == SG && c.k_run == KK) e = launch_B_sk<PM, SG, KK>(h, c);
-        if (h->lap_solver == QAP_LAP_SOLVER_AUCTION) {
-            e = c.seg == 8    ? launch_B_sk<PM, 8, 1, true>(h, c)
-                : c.seg == 16 ? launch_B_sk<PM, 16, 1, true>(h, c)
-                : c.seg == 32 ? launch_B_sk<PM, 32, 1, true>(h, c)
-                              : launch_B_sk<PM, 64, 1, true>(h, c);
-        }
-        QAP_CFG(8, 1) QAP_CFG(8, 2) QAP_CFG(8, 3) QAP_CFG(8, 4) QAP_CFG(8, 5) QAP_CFG(8, 6) QAP_CFG(8, 8)
-        QAP_CFG(16, 1) QAP_CFG(16, 2) QAP_CFG(16, 3) QAP_CFG(16, 4) QAP_CFG(32, 1) QAP_CFG(32, 2) QAP_CFG(64, 1)
-#undef QAP_CFG
+        hipError_t e = launch_B_class<PM>(h, c);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -115,7 +116,7 @@ hipError_t launch_batch_seg(hipStream_t st, int count, const int* dcount, const 
     using T = StoreT<PM>;
     if (count <= 0) return hipSuccess;
     constexpr int LPW = 64 / SEG;
-    const size_t lds = LPW * SlotLds<T, SEG, 1>::bytes(SEG);
+    const size_t lds = slot_lds<T, SEG>(SEG);
     const unsigned grid = (unsigned)((count + LPW - 1) / LPW);
     hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, count, dcount, idx, n, mo, vo, cost,
                        value, duals, assign, wr);
@@ -294,15 +295,9 @@ hipError_t Ops<PM>::enqueue_sweep_concentrate_overlapped(qap_rlt2* h)
         if (e == hipSuccess) e = hipEventRecord(h->ev_size[i], A);
         if (e == hipSuccess) e = hipStreamWaitEvent(Bs, h->ev_size[i], 0);
         if (e != hipSuccess) break;
-        // The concentration of this size, on the second stream, with the
-        // configuration tuned for its segment-size class.
-        const ClassHost& d = h->famD_size[i];
-        const ClassHost& bucket = h->fam[kFamD][d.seg == 8 ? 0 : d.seg == 16 ? 1 : d.seg == 32 ? 2 : 3];
-        double* vals = h->trace_level >= 2 ? h->dValD : nullptr;
+        // The concentration of this size, on the second stream.
         h->stream = Bs;
-        e = h->lap_solver == QAP_LAP_SOLVER_AUCTION
-                ? launch_family_auction<PM>(h, kFamD, d, vals, h->dmode)
-                : launch_family_class<PM>(h, kFamD, d, d.dev(), bucket.seg_run, bucket.k_run, vals, h->dmode);
+        e = launch_family_class<PM>(h, kFamD, h->famD_size[i], h->trace_level >= 2 ? h->dValD : nullptr);
         h->stream = A;
     }
     if (e != hipSuccess) return e;
@@ -401,126 +396,6 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src,
                        static_cast<T*>(ch->dD), ch->dInst, K, perD, ch->dmode);
     return hipGetLastError();
-}
-
-// ---- autotuner ----------------------------------------------------------------
-// For each class of a family, time every (lanes per problem, columns per
-// lane) candidate on the first min(total, kTuneItems) problems of the class,
-// each run starting from the same saved copy of the blocks and parents those
-// problems touch, and keep the fastest.  The choice does not change the
-// algorithm's decisions (ties go to the lowest column either way); it changes
-// only the order of the final sums, by rounding.
-constexpr long long kTuneItems = 16384;
-
-template <int PM>
-hipError_t Ops<PM>::tune_family(qap_rlt2* h, int famk)
-{
-    using T = StoreT<PM>;
-    hipError_t e = hipSuccess;
-    for (ClassHost& c : h->fam[famk]) {
-        if (c.total <= 0) continue;
-        const long long X = std::min(c.total, kTuneItems);
-        // Element ranges touched by the first X problems: blocks and parents.
-        int kk = 0;
-        while (kk + 1 < (int)c.pre.size() && c.pre[kk + 1] <= X - 1) ++kk;
-        const Inst& I0 = h->inst[c.ids[0]];
-        const Inst& IL = h->inst[c.ids[kk]];
-        const long long bl = X - 1 - c.pre[kk];
-        long long blk0, blk1, par0, par1;
-        char* blkbase;
-        char* parbase;
-        // Tuning runs on stored half blocks write only the parent c_beta, and
-        // the parents of the first X half blocks lie at or below the last one's.
-        const int mode = h->dmode == kAllBlocks ? kAllBlocks : kHalfStoreTune;
-        if (famk == kFamD) {
-            blk0 = I0.offD;
-            par0 = I0.offC;
-            if (mode == kAllBlocks) {
-                blk1 = IL.offD + (bl + 1) * IL.ldD;
-                par1 = IL.offC + bl + 1;
-            } else {
-                // Stored blocks 0..bl lie in the first bl / (N(N-1)) + 1 facility
-                // pairs of the pair-major layout; their parents c_beta anywhere
-                // below the largest beta among them.
-                const long long NL = (long long)IL.N * (IL.N - 1), n2 = IL.N - 2;
-                blk1 = IL.offD + (bl / NL + 1) * n2 * NL * n2;
-                long long pmax = 0;
-                for (long long hb = 0; hb <= bl; ++hb) {
-                    long long beta = 0, twin = 0, base = 0;
-                    pair_block(IL.N, hb, &beta, &twin, &base);
-                    pmax = std::max(pmax, beta);
-                }
-                par1 = IL.offC + pmax + 1;
-            }
-            blkbase = static_cast<char*>(h->dD);
-            parbase = static_cast<char*>(h->dC);
-        } else {
-            blk0 = I0.offC;
-            blk1 = IL.offC + (bl + 1) * (long long)(IL.N - 1) * (IL.N - 1);
-            par0 = I0.offB;
-            par1 = IL.offB + bl + 1;
-            blkbase = static_cast<char*>(h->dC);
-            parbase = static_cast<char*>(h->dB);
-        }
-        const size_t bbytes = (size_t)(blk1 - blk0) * h->elem, pbytes = (size_t)(par1 - par0) * h->elem;
-        void* sblk = nullptr;
-        void* spar = nullptr;
-        if ((e = hipMalloc(&sblk, bbytes)) != hipSuccess) return e;
-        if ((e = hipMalloc(&spar, pbytes)) != hipSuccess) {
-            (void)hipFree(sblk);
-            return e;
-        }
-        char* b0 = blkbase + blk0 * h->elem;
-        char* p0 = parbase + par0 * h->elem;
-        hipEvent_t ev0 = nullptr, ev1 = nullptr;
-        auto cleanup = [&]() {
-            if (ev0) (void)hipEventDestroy(ev0);
-            if (ev1) (void)hipEventDestroy(ev1);
-            (void)hipFree(sblk);
-            (void)hipFree(spar);
-        };
-        if ((e = hipMemcpyAsync(sblk, b0, bbytes, hipMemcpyDeviceToDevice, h->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(spar, p0, pbytes, hipMemcpyDeviceToDevice, h->stream)) != hipSuccess ||
-            (e = hipEventCreate(&ev0)) != hipSuccess || (e = hipEventCreate(&ev1)) != hipSuccess) {
-            cleanup();
-            return e;
-        }
-        FamilyClass fc = c.dev();
-        fc.total = X;
-        float best = 1e30f;
-        int best_seg = c.seg_run, best_k = c.k_run;
-        for (int seg : {8, 16, 32, 64}) {
-            const int k = (c.nmax + seg - 1) / seg;
-            if (!slot_cfg_allowed(seg, k)) continue;
-            if (slot_lds_any<T>(seg, k, c.nmax) > h->lds_limit) continue;
-            float ms = 0.f;
-            for (int rep = 0; rep < 2; ++rep) {
-                if ((e = hipMemcpyAsync(b0, sblk, bbytes, hipMemcpyDeviceToDevice, h->stream)) != hipSuccess ||
-                    (e = hipMemcpyAsync(p0, spar, pbytes, hipMemcpyDeviceToDevice, h->stream)) != hipSuccess ||
-                    (e = hipEventRecord(ev0, h->stream)) != hipSuccess ||
-                    (e = launch_family_class<PM>(h, famk, c, fc, seg, k, nullptr, mode)) != hipSuccess ||
-                    (e = hipEventRecord(ev1, h->stream)) != hipSuccess ||
-                    (e = hipEventSynchronize(ev1)) != hipSuccess ||
-                    (e = hipEventElapsedTime(&ms, ev0, ev1)) != hipSuccess) {
-                    cleanup();
-                    return e;
-                }
-            }
-            if (ms < best) {
-                best = ms;
-                best_seg = seg;
-                best_k = k;
-            }
-        }
-        c.seg_run = best_seg;
-        c.k_run = best_k;
-        e = hipMemcpyAsync(b0, sblk, bbytes, hipMemcpyDeviceToDevice, h->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(p0, spar, pbytes, hipMemcpyDeviceToDevice, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        cleanup();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 }  // namespace qap
