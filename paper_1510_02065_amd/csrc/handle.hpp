@@ -43,8 +43,8 @@ inline unsigned grid_for(long long work, int threads) { return (unsigned)((work 
 constexpr long long kTraceCap = 1024;
 
 // LDS of a one-wave workgroup of the assignment kernels at size nmax.
-template <typename T, int SEG>
-size_t slot_lds(int nmax) { return (size_t)(64 / SEG) * SlotLds<T, SEG, 1>::bytes(nmax); }
+template <typename T, int SEG, bool AUC>
+size_t slot_lds(int nmax) { return (size_t)(64 / SEG) * LapLds<T, AUC>::bytes(nmax); }
 
 // Instances of one family that share a segment size.
 struct ClassHost {

@@ -24,8 +24,8 @@
 //
 // Layout: a segment of SEG >= n lanes per problem, lane l = person l for the
 // bids and object l for the price and owner arrays in LDS (the problem's
-// SlotScratch: u holds the prices, vb the bid keys, aux the owners, and the
-// two short arrays together the winning person of each object's auction).
+// scratch: prices, bid keys, owners and the winning person of each object's
+// auction).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -55,11 +55,11 @@ struct AuctionEps {
 // feasible duals whatever the assignment state).
 constexpr int kAuctionMaxRounds = 1 << 14;
 
-// Same contract as lap_concentrate_flat (one column per lane, n <= SEG):
+// Same contract as lap_concentrate:
 // solve, write the residual (R, row stride ldr), duals [uc | vc | ur | vr],
 // the assignment, and return S to every lane of the segment.
 template <typename T, int SEG, bool DOWN>
-__device__ __forceinline__ double lap_auction_flat(const SlotScratch<T, SEG, 1>& sc, int n, T* __restrict__ R,
+__device__ __forceinline__ double lap_auction_flat(const LapScratch<T>& sc, int n, T* __restrict__ R,
                                                    long long ldr, T* __restrict__ duals,
                                                    int32_t* __restrict__ assign)
 {
@@ -68,10 +68,10 @@ __device__ __forceinline__ double lap_auction_flat(const SlotScratch<T, SEG, 1>&
     const int ldm = sc.ld;   // row stride of M
     const int l = S::lane();
     const bool ok = l < n;
-    double* __restrict__ price = sc.u;
-    unsigned long long* __restrict__ key = reinterpret_cast<unsigned long long*>(sc.vb);
-    int* __restrict__ owner = sc.aux;
-    int* __restrict__ win = reinterpret_cast<int*>(sc.p);   // p and way: n ints together
+    double* __restrict__ price = sc.template arr<double>(n, 0);
+    unsigned long long* __restrict__ key = sc.template arr<unsigned long long>(n, 1);
+    int* __restrict__ owner = sc.template arr<int>(n, 4);
+    int* __restrict__ win = sc.template arr<int>(n, 5);
 
     // Scale of the problem: the largest |M_rq|.
     double big = 0.0;
@@ -156,10 +156,7 @@ __device__ __forceinline__ double lap_auction_flat(const SlotScratch<T, SEG, 1>&
         vcol = (T)(-price[l]);
     }
     wave_sync();
-    const T vca[1] = {vcol};
-    const T ura[1] = {urow};
-    const int sga[1] = {my};
-    return lap_complete<T, SEG, 1, DOWN>(sc, n, R, ldr, duals, assign, vca, ura, sga);
+    return lap_complete<T, SEG, DOWN>(sc, n, R, ldr, duals, assign, vcol, urow, my);
 }
 
 }  // namespace qap

@@ -87,17 +87,17 @@ __device__ __forceinline__ long long xcd_major(long long b, long long grid)
 // scalar unit, and with the per-lane size otherwise (a wave across an
 // instance boundary, or with segments past the last problem, whose n is 0).
 // Both compute the same values.
-template <typename T, int SEG, bool AUC, bool DOWN>
+template <typename T, int SEG, bool AUC, bool DOWN, bool UNI>
 __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, int lane, int nmax, int n, T* blk,
-                                                  long long ld)
+                                                  long long ld, int32_t* assign = nullptr)
 {
-    const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(nmax), n);
+    const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(nmax), n);
     stage_block<T, SEG>(sc.M, sc.ld, blk, ld, n, lane);
     wave_sync();
     if constexpr (AUC)
-        return lap_auction_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, nullptr);
+        return lap_auction_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, assign);
     else
-        return lap_concentrate_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, nullptr);
+        return lap_concentrate<T, SEG, DOWN, UNI>(sc, n, blk, ld, nullptr, assign);
 }
 
 // D -> C (FAM kFamD: blocks D_beta of size N-2, parent c_beta) or C -> B
@@ -105,11 +105,11 @@ __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, 
 // problems per wave, one wave per workgroup.  parent += S, the block is
 // replaced by its residual, values[...] = S when values is not null (values
 // are packed like the parents).  `mode` applies to the D family only.  AUC:
-// the auction solver.  Registers: the FP32 kernels are held to 72 VGPRs
-// (seven waves per SIMD, about what their LDS allows at n = 23) and the FP64
-// ones of up to 32 lanes to 80 (six waves: the LDS of the smaller problems of
-// a batch allows more than the 99 VGPRs they would otherwise take); neither
-// spills.
+// the auction solver.  Registers: the FP32 kernels are held to 72 VGPRs (seven
+// waves per SIMD; held to 64, eight waves, they spill 11 and N = 25 took 474
+// against 462 us) and the FP64 ones of up to 32 lanes to 80 (six waves; 4
+// spilled; with 96, five waves, N = 20 took 219 against 208 us and N = 25 the
+// same).
 template <int PM, int SEG, int FAM, bool AUC = false>
 __global__ __launch_bounds__(64, PM != kPrecF64 ? 7 : (SEG <= 32 ? 6 : 1))
 void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, StoreT<PM>* __restrict__ B,
@@ -154,15 +154,21 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
             pidx = I.offB + b;
         }
     }
+    // The parents are read now, so that the wave does not wait for them at its end.
+    T* __restrict__ const parent = (FAM == kFamD) ? C : B;
+    T par = 0, par2 = 0;
+    if (active) {
+        par = parent[pidx];
+        par2 = pidx2 >= 0 ? parent[pidx2] : (T)0;
+    }
     const int nu = __builtin_amdgcn_readfirstlane(n);
     T* const bw = active ? blk : nullptr;
     const double S = ballot64(n != nu) == 0
-                         ? stage_and_solve<T, SEG, AUC, DOWN>(smem, seg, lane, nmax, nu, bw, ld)
-                         : stage_and_solve<T, SEG, AUC, DOWN>(smem, seg, lane, nmax, n, bw, ld);
+                         ? stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, nu, bw, ld)
+                         : stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, n, bw, ld);
     if (active && lane == 0) {
-        T* parent = (FAM == kFamD) ? C : B;
-        parent[pidx] = store_add<PM>(parent[pidx], S);
-        if (pidx2 >= 0) parent[pidx2] = store_add<PM>(parent[pidx2], S);
+        parent[pidx] = store_add<PM>(par, S);
+        if (pidx2 >= 0) parent[pidx2] = store_add<PM>(par2, S);
         if (values) {
             values[pidx] = S;
             if (pidx2 >= 0) values[pidx2] = S;
@@ -198,15 +204,12 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     const Inst I = inst[k];
     const int n = active ? I.N : 0;
     T* blk = B + I.offB;
-    const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(nmax), n);
-    stage_block<T, SEG>(sc.M, sc.ld, blk, n, n, lane);
-    wave_sync();
     int32_t* sg = (active && sigma) ? sigma + I.offB : nullptr;
-    double S;
-    if constexpr (AUC)
-        S = lap_auction_flat<T, SEG, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
-    else
-        S = lap_concentrate_flat<T, SEG, DOWN>(sc, n, active ? blk : nullptr, n, nullptr, sg);
+    T* const bw = active ? blk : nullptr;
+    const int nu = __builtin_amdgcn_readfirstlane(n);
+    const double S = ballot64(n != nu) == 0
+                         ? stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, nu, bw, nu, sg)
+                         : stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, n, bw, n, sg);
     if (active && lane == 0) {
         const double L = DOWN ? add_down(lb[2 * k], S) : lb[2 * k] + S;
         lb[2 * k] = L;
@@ -259,17 +262,17 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     int32_t* const aw = (assign && n > 0) ? assign + vo : nullptr;
     // The size as a scalar when every problem of the wave has it, as in
     // k_lap_family_s.
-    auto solve = [&](int nn) __attribute__((always_inline)) -> double {
-        const SlotScratch<T, SEG, 1> sc(smem + seg * SlotLds<T, SEG, 1>::bytes(SEG), nn);
+    auto solve = [&](int nn, auto uni) __attribute__((always_inline)) -> double {
+        const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(SEG), nn);
         stage_block<T, SEG>(sc.M, sc.ld, mat, nn, nn, lane);
         wave_sync();
         if constexpr (AUC)
             return lap_auction_flat<T, SEG, PM == kPrecF32Down>(sc, nn, Rw, nn, dw, aw);
         else
-            return lap_concentrate_flat<T, SEG, PM == kPrecF32Down>(sc, nn, Rw, nn, dw, aw);
+            return lap_concentrate<T, SEG, PM == kPrecF32Down, decltype(uni)::value>(sc, nn, Rw, nn, dw, aw);
     };
     const int nu = __builtin_amdgcn_readfirstlane(n);
-    const double S = ballot64(n != nu) == 0 ? solve(nu) : solve(n);
+    const double S = ballot64(n != nu) == 0 ? solve(nu, std::true_type{}) : solve(n, std::false_type{});
     // A quiet NaN written by bit pattern marks a problem that was not solved.
     if (in && lane == 0) value[b] = bad ? __longlong_as_double(0x7ff8000000000000ll) : S;
 }

@@ -16,7 +16,7 @@ hipError_t launch_family_seg(qap_rlt2* h, int famk, const ClassHost& c, double* 
     using T = StoreT<PM>;
     constexpr int LPW = 64 / SEG;
     const FamilyClass fc = c.dev();
-    const size_t lds = slot_lds<T, SEG>(c.nmax);
+    const size_t lds = slot_lds<T, SEG, AUC>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;   // not launched
     const unsigned grid = (unsigned)((fc.total + LPW - 1) / LPW);
     T* D = static_cast<T*>(h->dD);
@@ -36,7 +36,7 @@ hipError_t launch_B_seg(qap_rlt2* h, const ClassHost& c)
 {
     using T = StoreT<PM>;
     constexpr int LPW = 64 / SEG;
-    const size_t lds = slot_lds<T, SEG>(c.nmax);
+    const size_t lds = slot_lds<T, SEG, AUC>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
     const unsigned grid = (unsigned)((c.total + LPW - 1) / LPW);
     const bool tr = h->trace_level >= 1;
@@ -116,7 +116,7 @@ hipError_t launch_batch_seg(hipStream_t st, int count, const int* dcount, const 
     using T = StoreT<PM>;
     if (count <= 0) return hipSuccess;
     constexpr int LPW = 64 / SEG;
-    const size_t lds = slot_lds<T, SEG>(SEG);
+    const size_t lds = slot_lds<T, SEG, AUC>(SEG);
     const unsigned grid = (unsigned)((count + LPW - 1) / LPW);
     hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, count, dcount, idx, n, mo, vo, cost,
                        value, duals, assign, wr);

@@ -35,6 +35,26 @@ def test_lap_sizes_and_kinds(n):
     _check(mats, out)
 
 
+@pytest.mark.parametrize("n", [2, 7, 8, 9, 15, 16, 17, 23, 32, 33, 64])
+def test_lap_near_ties_and_extreme_scales(n):
+    # The solver's minima run on 32-bit keys and settle equal keys exactly:
+    # entries that differ in the last bits only (equal keys, distinct
+    # values), and entries at both ends of the double range.
+    rng = np.random.default_rng(n)
+    base = rng.integers(0, 4, size=(n, n)).astype(float)
+    mats = [1000.0 + base + rng.integers(0, 8, size=(n, n)) * 2.0 ** -38,
+            base + rng.integers(0, 3, size=(n, n)) * 2.0 ** -45,
+            1.0 + rng.integers(0, 2, size=(n, n)) * 2.0 ** -52,
+            rng.uniform(-1.0, 1.0, size=(n, n)) * 2.0 ** -900,
+            rng.uniform(-1.0, 1.0, size=(n, n)) * 2.0 ** 1005]
+    out = lap_solve(mats, residual=True)
+    scale = np.array([1.0, 1.0, 1.0, 2.0 ** -900, 2.0 ** 1005])
+    for b, c in enumerate(scale):   # compared at scale 1: powers of two are exact
+        one = {"value": out["value"][b:b + 1] / c, "duals": [out["duals"][b] / c], "residual": [out["residual"][b] / c],
+               "assign": [out["assign"][b]]}
+        _check([mats[b] / c], one)
+
+
 def test_lap_mixed_sizes_one_batch():
     rng = np.random.default_rng(0)
     sizes = rng.integers(0, 65, size=300)
