@@ -91,7 +91,8 @@ void release(qap_rlt2* h)
     if (h->graph) (void)hipGraphDestroy(h->graph);
     void* ptrs[] = {h->dB,     h->dC,     h->dD,     h->dCC,   h->dLB,   h->dValD,  h->dValC,  h->dValB,
                     h->dTrace, h->dCounter, h->dTri, h->dAct,  h->dStop, h->dSigma, h->dCt,    h->dBt,
-                    h->dCert,  h->dInst,  h->dPreB,  h->dPreC, h->dPreWG};
+                    h->dCert,  h->dInst,  h->dPreB,  h->dPreC, h->dPreWG,
+                    h->dPreCert};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (auto& f : h->fam)
@@ -230,6 +231,8 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
         h->preB.push_back(h->totalB);
         h->preC.push_back(h->totalC);
         h->preWG.push_back(h->totalWG);
+        h->preCert.push_back(h->totalCert);
+        h->totalCert += (long long)(N * n1 / 2) * qap::cert_stretches(N);
         const long long nC = (long long)N * N * n1 * n1;
         h->totalB += (long long)N * N;
         h->totalC += nC;
@@ -331,6 +334,7 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
     CK(upload(&h->dPreB, h->preB, h->stream));
     CK(upload(&h->dPreC, h->preC, h->stream));
     CK(upload(&h->dPreWG, h->preWG, h->stream));
+    CK(upload(&h->dPreCert, h->preCert, h->stream));
     for (auto& c : h->sweep_cls) {
         CK(upload(&c.d_ids, c.ids, h->stream));
         CK(upload(&c.d_pre, c.pre, h->stream));

@@ -94,6 +94,8 @@ struct qap_rlt2 {
     std::vector<qap::Inst> inst;
     long long totalB = 0, totalC = 0, totalD = 0, totalWG = 0;
     std::vector<long long> preB, preC, preWG;
+    std::vector<long long> preCert;   // first k_cert_pairs workgroup of each instance
+    long long totalCert = 0;
     qap::ClassHost fam[3][4];   // [D, C, B][segment class]
     std::vector<qap::SweepClass> sweep_cls;   // kHalfStore: one sweep launch per instance size, largest first
     // Overlapped steps 1-4 of a batch of mixed sizes (qap_rlt2_ascend): the
@@ -107,7 +109,7 @@ struct qap_rlt2 {
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     std::vector<int> tri;                     // facility triples of every instance
     qap::Inst* dInst = nullptr;
-    long long *dPreB = nullptr, *dPreC = nullptr, *dPreWG = nullptr;
+    long long *dPreB = nullptr, *dPreC = nullptr, *dPreWG = nullptr, *dPreCert = nullptr;
     void* dB = nullptr;
     void* dC = nullptr;
     void* dD = nullptr;

@@ -314,13 +314,13 @@ hipError_t Ops<PM>::certify(qap_rlt2* h)
         hipLaunchKernelGGL((k_cert_noD<T>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st,
                            static_cast<const T*>(h->dC), h->dCt, h->totalC);
     else if (h->dmode == kAllBlocks)
-        hipLaunchKernelGGL((k_cert_D<T, false>), dim3(grid_for(h->totalC, 4)), dim3(256), 0, st,
+        hipLaunchKernelGGL((k_cert_D<T>), dim3(grid_for(h->totalC, 4)), dim3(256), 0, st,
                            static_cast<const T*>(h->dD), static_cast<const T*>(h->dC), h->dCt, h->dInst, h->dPreC,
                            h->K, h->totalC);
     else
-        hipLaunchKernelGGL((k_cert_D<T, true>), dim3(grid_for(h->totalC / 2, 4)), dim3(256), 0, st,
-                           static_cast<const T*>(h->dD), static_cast<const T*>(h->dC), h->dCt, h->dInst, h->dPreC,
-                           h->K, h->totalC);
+        hipLaunchKernelGGL((k_cert_pairs<T>), dim3((unsigned)h->totalCert), dim3(kCertThreads), 0, st,
+                           static_cast<const T*>(h->dD), static_cast<const T*>(h->dC), h->dCt, h->dInst, h->dPreCert,
+                           h->K);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_cert_C<T>), dim3(grid_for(h->totalB, 4)), dim3(256), 0, st, h->dCt,

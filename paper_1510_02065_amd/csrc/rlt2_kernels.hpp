@@ -1230,39 +1230,82 @@ __global__ __launch_bounds__(256) void k_transfer_C(StoreT<PM>* __restrict__ C, 
 // b~ = b + (N-1) min(0, min of C~_ij), and LB + N min(0, min b~) bounds the
 // whole sum from below whatever the signs of the stored entries.
 
-// One wave per stored D block of every instance: ct[beta] = c_beta +
-// (N-2) min(0, min D_beta), for both blocks of the pair when HALF.  The
-// blocks stored (all, or one per pair) number totalC (or totalC / 2; every
-// instance's C count is a multiple of 4, so halving preC gives the prefix of
-// its stored blocks).
-template <typename T, bool HALF>
+// Every stored D block of every instance (all blocks): one wave per block,
+// ct[beta] = c_beta + (N-2) min(0, min D_beta).
+template <typename T>
 __global__ __launch_bounds__(256) void k_cert_D(const T* __restrict__ Dd, const T* __restrict__ C,
                                                 double* __restrict__ ct, const Inst* __restrict__ inst,
                                                 const long long* __restrict__ preC, int K, long long totalC)
 {
     const long long x = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (x >= (HALF ? totalC / 2 : totalC)) return;
-    const Inst I = inst[find_seg(preC, K, HALF ? 2 * x : x)];
-    const int N = I.N, n2 = N - 2, blk = n2 * n2;
-    const long long local = x - (HALF ? I.offC / 2 : I.offC);
-    long long beta = local, twin = -1, base = local * I.ldD, ld = n2;
-    if constexpr (HALF) {
-        pair_block(N, local, &beta, &twin, &base);
-        ld = (long long)N * (N - 1) * n2;
-    }
-    const T* __restrict__ Db = Dd + I.offD + base;
+    if (x >= totalC) return;
+    const Inst I = inst[find_seg(preC, K, x)];
+    const int blk = (I.N - 2) * (I.N - 2);
+    const T* __restrict__ Db = Dd + I.offD + (x - I.offC) * I.ldD;
     double m = 0.0;
-    for (int e = lane; e < blk; e += 64) m = __builtin_fmin(m, (double)Db[(e / n2) * ld + e % n2]);
+    for (int e = lane; e < blk; e += 64) m = __builtin_fmin(m, (double)Db[e]);
     for (int off = 32; off > 0; off >>= 1) m = __builtin_fmin(m, __shfl_xor(m, off, 64));
-    if (lane == 0) {
-        const double md = mul_down((double)(N - 2), m);
-        if constexpr (HALF) {
-            ct[I.offC + beta] = add_down((double)C[I.offC + beta], md);
-            ct[I.offC + twin] = add_down((double)C[I.offC + twin], md);
-        } else {
-            ct[x] = add_down((double)C[x], md);
-        }
+    if (lane == 0) ct[x] = add_down((double)C[x], mul_down((double)(I.N - 2), m));
+}
+
+// One stored block per complementary pair (pair-major): the N-2 rows of the
+// blocks of one facility pair are N-2 runs of N (N-1) (N-2) entries, so a
+// workgroup takes a stretch of locations pairs (certPairs of them) and reads
+// the same stretch of every run, each thread the same entries of each, then
+// takes the minimum over a block's N-2 columns in LDS; ct of both blocks of
+// the pair is written.  Bound by HBM: every load is a run of consecutive
+// entries, kCertRows rows in flight per thread (one wave per block, rows of
+// N-2 entries, took 0.83 ms at N = 33 in FP32).
+constexpr int kCertThreads = 256, kCertRegs = 4, kCertRows = 4;
+__host__ __device__ inline int cert_pairs(int N) { return kCertThreads * kCertRegs / (N - 2); }
+// Workgroups of an instance: stretches per facility pair times the pairs.
+__host__ __device__ inline int cert_stretches(int N) { return (N * (N - 1) + cert_pairs(N) - 1) / cert_pairs(N); }
+
+template <typename T>
+__global__ __launch_bounds__(kCertThreads) void k_cert_pairs(const T* __restrict__ Dd, const T* __restrict__ C,
+                                                             double* __restrict__ ct, const Inst* __restrict__ inst,
+                                                             const long long* __restrict__ pre, int K)
+{
+    __shared__ T low[kCertThreads * kCertRegs];
+    const int kk = find_seg(pre, K, (long long)blockIdx.x);
+    const Inst I = inst[kk];
+    const int N = I.N, n2 = N - 2, NL = N * (N - 1);
+    const int w = (int)((long long)blockIdx.x - pre[kk]);
+    const int stretches = cert_stretches(N);
+    const int P = w / stretches, L0 = (w - P * stretches) * cert_pairs(N);
+    const int pairs = min(cert_pairs(N), NL - L0), len = pairs * n2;
+    const long long run = (long long)NL * n2;
+    const T* __restrict__ first = Dd + I.offD + (long long)P * n2 * run + (long long)L0 * n2;
+    const int tid = threadIdx.x;
+    T m[kCertRegs];
+#pragma unroll
+    for (int u = 0; u < kCertRegs; ++u) m[u] = (T)0;
+    // Indices past the stretch (rows past the last) read its last entry (row)
+    // again, which changes no minimum.
+    for (int r0 = 0; r0 < n2; r0 += kCertRows) {
+        T x[kCertRows][kCertRegs];
+#pragma unroll
+        for (int e = 0; e < kCertRows; ++e)
+#pragma unroll
+            for (int u = 0; u < kCertRegs; ++u)
+                x[e][u] = first[(long long)min(r0 + e, n2 - 1) * run + min(tid + u * kCertThreads, len - 1)];
+#pragma unroll
+        for (int e = 0; e < kCertRows; ++e)
+#pragma unroll
+            for (int u = 0; u < kCertRegs; ++u) m[u] = x[e][u] < m[u] ? x[e][u] : m[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kCertRegs; ++u) low[tid + u * kCertThreads] = m[u];
+    __syncthreads();
+    for (int q = tid; q < pairs; q += kCertThreads) {
+        double lo = 0.0;
+        for (int c = 0; c < n2; ++c) lo = __builtin_fmin(lo, (double)low[q * n2 + c]);
+        const double md = mul_down((double)n2, lo);
+        long long beta, twin, base;
+        pair_block(N, (long long)P * NL + L0 + q, &beta, &twin, &base);
+        ct[I.offC + beta] = add_down((double)C[I.offC + beta], md);
+        ct[I.offC + twin] = add_down((double)C[I.offC + twin], md);
     }
 }
 

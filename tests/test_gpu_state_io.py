@@ -239,3 +239,32 @@ def test_snapshot_batch_and_mismatch():
         b.restore(snap[:-9])  # truncated
     for h in (ref, a, b, other):
         h.close()
+
+
+# Stretches of the streaming minimum over the stored blocks: one block row
+# (N = 3), a stretch longer than the pair's locations (4, 12), exactly whole
+# stretches and a short last one (18, 20).
+@pytest.mark.parametrize("N,precision", [(3, "fp64"), (4, "fp32"), (12, "fp64"), (18, "fp32n"), (20, "fp64")])
+def test_certify_finds_every_blocks_minimum(N, precision):
+    F, D = qapgen.uniform(N, 2)
+    g = Rlt2(F, D, precision=precision)
+    rng = np.random.default_rng(N)
+    n1, n2 = N - 1, N - 2
+    I, J, K, Nn = layout.c_index_arrays(N)
+    twin = ((K * N + Nn) * n1 + I - (I > K)) * n1 + J - (J > Nn)
+    keep = I < K
+    # One negative entry per stored block, at a random place; each block's in
+    # turn is by far the smallest, so a block left out changes the bound.
+    Dn = np.zeros((len(I), n2 * n2))
+    C = np.zeros(len(I))
+    B = np.zeros(N * N)
+    stored = np.flatnonzero(keep)
+    Dn[stored, rng.integers(0, n2 * n2, size=len(stored))] = -1.0 / 1024
+    Dn[twin[stored]] = Dn[stored]
+    for beta in rng.choice(stored, min(6, len(stored)), replace=False):
+        X = Dn.copy()
+        X[beta, rng.integers(0, n2 * n2)] = -64.0
+        X[twin[beta]] = X[beta]
+        g.load_state(0, 0.0, B, C, X.ravel())
+        assert g.certify() == pytest.approx(_host_cascade(N, 0.0, B, C, X.ravel()), rel=1e-12)
+    g.close()
