@@ -56,11 +56,11 @@ struct AuctionEps {
 constexpr int kAuctionMaxRounds = 1 << 14;
 
 // Same contract as lap_concentrate:
-// solve, write the residual (R, row stride ldr), duals [uc | vc | ur | vr],
+// solve, write the residual, duals [uc | vc | ur | vr],
 // the assignment, and return S to every lane of the segment.
-template <typename T, int SEG, bool DOWN>
-__device__ __forceinline__ double lap_auction_flat(const LapScratch<T>& sc, int n, T* __restrict__ R,
-                                                   long long ldr, T* __restrict__ duals,
+template <typename T, int SEG, bool DOWN, typename Rows>
+__device__ __forceinline__ double lap_auction_flat(const LapScratch<T>& sc, int n, const Rows& rows, bool write,
+                                                   T* __restrict__ duals,
                                                    int32_t* __restrict__ assign)
 {
     using S = SegS<SEG>;
@@ -156,7 +156,7 @@ __device__ __forceinline__ double lap_auction_flat(const LapScratch<T>& sc, int 
         vcol = (T)(-price[l]);
     }
     wave_sync();
-    return lap_complete<T, SEG, DOWN>(sc, n, R, ldr, duals, assign, vcol, urow, my);
+    return lap_complete<T, SEG, DOWN>(sc, n, rows, write, duals, assign, vcol, urow, my);
 }
 
 }  // namespace qap

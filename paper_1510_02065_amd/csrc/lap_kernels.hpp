@@ -29,38 +29,32 @@ enum DStorage : int {
                        // problem h is stored block h, parents c_beta and c_twin
 };
 
-// Copy an n x n block (row stride ld in global memory) into LDS (row stride
+// Copy an n x n block (rows `rows` in global memory) into LDS (row stride
 // ldm).  Each lane issues the loads of a whole chunk of rows before it writes
 // any of them, so a wave waits for HBM once per chunk instead of once per row:
 // the first kStageRows rows (all of them up to n = 24) in straight-line code,
 // the rest kStageTail at a time.  Rows past the end re-read row n-1 and write
 // it again (the same value to the same place), so no write is guarded.  Row
-// offsets are 24-bit products: ld < 2^24 (at most N (N-1) (N-2) < 2^18 for
-// N <= 64) and the offsets stay below 2^32 bytes.
+// offsets in LDS are 24-bit products; those in global memory stay below 2^32
+// bytes (a row stride is at most N (N-1) (N-2) < 2^18 entries for N <= 64).
 constexpr int kStageRows = 24;
 constexpr int kStageTail = 8;
 
-template <typename T, int SEG>
-__device__ __forceinline__ void stage_block(T* __restrict__ M, int ldm, const T* __restrict__ blk, long long ld,
-                                            int n, int c)
+template <typename T, typename Rows>
+__device__ __forceinline__ void stage_block(T* __restrict__ M, int ldm, const Rows& rows, int n, int c)
 {
-    const unsigned ldb = (unsigned)ld * (unsigned)sizeof(T);   // row stride in bytes (< 2^24 * 8)
     if (c >= n) return;
-    const char* __restrict__ col = reinterpret_cast<const char*>(blk + c);
-    auto row_at = [&](int r) -> T {
-        return *reinterpret_cast<const T*>(col + (size_t)(unsigned)__umul24((unsigned)r, ldb));
-    };
     {
         T t[kStageRows];
 #pragma unroll
-        for (int u = 0; u < kStageRows; ++u) t[u] = row_at(min(u, n - 1));
+        for (int u = 0; u < kStageRows; ++u) t[u] = rows.at(min(u, n - 1));
 #pragma unroll
         for (int u = 0; u < kStageRows; ++u) M[__umul24((unsigned)min(u, n - 1), (unsigned)ldm) + c] = t[u];
     }
     for (int r0 = kStageRows; r0 < n; r0 += kStageTail) {
         T t[kStageTail];
 #pragma unroll
-        for (int u = 0; u < kStageTail; ++u) t[u] = row_at(min(r0 + u, n - 1));
+        for (int u = 0; u < kStageTail; ++u) t[u] = rows.at(min(r0 + u, n - 1));
 #pragma unroll
         for (int u = 0; u < kStageTail; ++u) M[__umul24((unsigned)min(r0 + u, n - 1), (unsigned)ldm) + c] = t[u];
     }
@@ -80,24 +74,23 @@ __device__ __forceinline__ long long xcd_major(long long b, long long grid)
 }
 
 // Stage one problem per segment and solve it (the residual written over the
-// block when blk is not null); S to every lane.  Called twice by the kernel
-// below: with the size as a scalar (readfirstlane) when every problem of the
-// wave has it, as in every wave of one instance's family, so that loop
-// counts, clamps, bit masks and LDS offsets that depend only on n run on the
-// scalar unit, and with the per-lane size otherwise (a wave across an
-// instance boundary, or with segments past the last problem, whose n is 0).
-// Both compute the same values.
-template <typename T, int SEG, bool AUC, bool DOWN, bool UNI>
-__device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, int lane, int nmax, int n, T* blk,
-                                                  long long ld, int32_t* assign = nullptr)
+// block where `active`); S to every lane.  UNI: the size is a scalar, as when
+// every problem of the wave belongs to one instance, so that loop counts,
+// clamps, bit masks and LDS offsets that depend only on n run on the scalar
+// unit; otherwise it is a lane's (a wave across an instance boundary, or with
+// segments past the last problem, whose n is 0).  Both compute the same values.
+template <typename T, int SEG, bool AUC, bool DOWN, bool UNI, typename Rows>
+__device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, int lane, int nmax, int n,
+                                                  const Rows& rows, bool active, int32_t* assign = nullptr)
 {
     const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(nmax), n);
-    stage_block<T, SEG>(sc.M, sc.ld, blk, ld, n, lane);
+    stage_block(sc.M, sc.ld, rows, n, lane);
     wave_sync();
+    T* const no_duals = nullptr;
     if constexpr (AUC)
-        return lap_auction_flat<T, SEG, DOWN>(sc, n, blk, ld, nullptr, assign);
+        return lap_auction_flat<T, SEG, DOWN>(sc, n, rows, active, no_duals, assign);
     else
-        return lap_concentrate<T, SEG, DOWN, UNI>(sc, n, blk, ld, nullptr, assign);
+        return lap_concentrate<T, SEG, DOWN, UNI>(sc, n, rows, active, no_duals, assign);
 }
 
 // D -> C (FAM kFamD: blocks D_beta of size N-2, parent c_beta) or C -> B
@@ -107,9 +100,17 @@ __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, 
 // are packed like the parents).  `mode` applies to the D family only.  AUC:
 // the auction solver.  Registers: the FP32 kernels are held to 72 VGPRs (seven
 // waves per SIMD; held to 64, eight waves, they spill 11 and N = 25 took 474
-// against 462 us) and the FP64 ones of up to 32 lanes to 80 (six waves; 4
-// spilled; with 96, five waves, N = 20 took 219 against 208 us and N = 25 the
-// same).
+// against 462 us) and the FP64 ones of up to 32 lanes to 80 (six waves; with
+// 96, five waves, N = 20 took 219 against 208 us and N = 25 the same).
+//
+// What bounds it is the chain of dependent instructions of each wave, at as
+// many waves as LDS admits; FP32 and small sizes are also close to the VALU's
+// rate, so work that a wave has in common goes to the scalar unit.  All
+// problems of a wave belong to one instance except where it crosses into the
+// next (every wave of a single instance but the last, all but one wave per
+// instance of a batch): such a wave finds its instance, its rows' addresses
+// and its loop counts with scalar instructions (N = 25 FP32 468 -> 448 us, N =
+// 33 2720 -> 2612; a batch of 160 nodes of N = 17..22 52.3 -> 50.2 ms).
 template <int PM, int SEG, int FAM, bool AUC = false>
 __global__ __launch_bounds__(64, PM != kPrecF64 ? 7 : (SEG <= 32 ? 6 : 1))
 void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, StoreT<PM>* __restrict__ B,
@@ -122,58 +123,72 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
     constexpr int LPW = 64 / SEG;
     const int seg = threadIdx.x / SEG;
     const int lane = threadIdx.x & (SEG - 1);
-    const long long x = xcd_major(blockIdx.x, gridDim.x) * LPW + seg;
+    T* __restrict__ const parent = (FAM == kFamD) ? C : B;
+    // Problem b of instance I: size, offset of its block in D (C), row stride
+    // in entries, and this lane's parent at up + p (lane 0 has the first,
+    // lane 1 the twin's; p < 0: none).
+    struct Problem {
+        int n;
+        long long off, ld, up;
+        int p;
+    };
+    const int only = lane == 0 ? 0 : -1;
+    auto problem = [&](const Inst& I, long long b) __attribute__((always_inline)) -> Problem {
+        if constexpr (FAM == kFamD) {
+            const int n = I.N - 2;
+            if (mode == kAllBlocks) return {n, I.offD + b * I.ldD, n, I.offC, (int)b | only};
+            long long beta, twin, first;
+            pair_block(I.N, b, &beta, &twin, &first);
+            return {n, I.offD + first, (long long)I.N * (I.N - 1) * n, I.offC,
+                    lane == 0 ? (int)beta : lane == 1 ? (int)twin : -1};
+        } else {
+            const int n = I.N - 1;
+            return {n, I.offC + b * (long long)(n * n), n, I.offB, (int)b | only};
+        }
+    };
+    T* const blocks = FAM == kFamD ? D : C;
+    auto finish = [&](const Problem& q, T par, double S) __attribute__((always_inline)) {
+        if (q.p < 0) return;
+        (parent + q.up)[q.p] = store_add<PM>(par, S);
+        if (values) (values + q.up)[q.p] = S;
+    };
+    // The parents are read before the solve, so that the wave does not wait
+    // for them at its end.
+    const long long x0 = xcd_major(blockIdx.x, gridDim.x) * LPW;
+    const int k0 = find_seg(fc.pre, fc.Kc, x0);
+    const int id0 = fc.cls[k0];
+    const long long end0 = k0 + 1 < fc.Kc ? fc.pre[k0 + 1] : fc.total;
+    if (x0 + LPW <= end0) {
+        // Every problem of the wave belongs to instance id0; its blocks lie at growing offsets, less than 2^32 bytes
+        // apart (a facility pair's stored rows are below 2^27).
+        if (!act[id0]) return;
+        const Inst I = inst[id0];
+        const Problem q = problem(I, x0 - fc.pre[k0] + seg);
+        const T par = q.p >= 0 ? (parent + q.up)[q.p] : (T)0;
+        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)q.off);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(q.off >> 32));
+        const long long first = (long long)(((unsigned long long)hi << 32) | lo);
+        const int n = FAM == kFamD ? I.N - 2 : I.N - 1;
+        const unsigned ld = FAM == kFamD && mode != kAllBlocks ? (unsigned)(I.N * (I.N - 1) * n) : (unsigned)n;
+        const WaveRows<T> rows{reinterpret_cast<char*>(blocks + first), ld * (unsigned)sizeof(T),
+                               (unsigned)(q.off - first + lane) * (unsigned)sizeof(T)};
+        const double S = stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, n, rows, true);
+        finish(q, par, S);
+        return;
+    }
+    const long long x = x0 + seg;
     int kk = 0;
     if (x < fc.total) kk = find_seg(fc.pre, fc.Kc, x);
     const bool active = x < fc.total && act[fc.cls[kk]];
-    int n = 0;
-    T* blk = nullptr;
-    long long ld = 0;   // row stride of the block in global memory
-    long long pidx = 0, pidx2 = -1;
+    Problem q{0, 0, 0, 0, -1};
+    T par = 0;
     if (active) {
-        const Inst I = inst[fc.cls[kk]];
-        const long long b = x - fc.pre[kk];
-        if (FAM == kFamD) {
-            n = I.N - 2;
-            if (mode == kAllBlocks) {
-                blk = D + I.offD + b * I.ldD;
-                ld = n;
-                pidx = I.offC + b;
-            } else {
-                long long beta, tb, base;
-                pair_block(I.N, b, &beta, &tb, &base);
-                blk = D + I.offD + base;
-                ld = (long long)I.N * (I.N - 1) * n;
-                pidx = I.offC + beta;
-                pidx2 = I.offC + tb;
-            }
-        } else {
-            n = I.N - 1;
-            blk = C + I.offC + b * (long long)(I.N - 1) * (I.N - 1);
-            ld = n;
-            pidx = I.offB + b;
-        }
+        q = problem(inst[fc.cls[kk]], x - fc.pre[kk]);
+        if (q.p >= 0) par = (parent + q.up)[q.p];
     }
-    // The parents are read now, so that the wave does not wait for them at its end.
-    T* __restrict__ const parent = (FAM == kFamD) ? C : B;
-    T par = 0, par2 = 0;
-    if (active) {
-        par = parent[pidx];
-        par2 = pidx2 >= 0 ? parent[pidx2] : (T)0;
-    }
-    const int nu = __builtin_amdgcn_readfirstlane(n);
-    T* const bw = active ? blk : nullptr;
-    const double S = ballot64(n != nu) == 0
-                         ? stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, nu, bw, ld)
-                         : stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, n, bw, ld);
-    if (active && lane == 0) {
-        parent[pidx] = store_add<PM>(par, S);
-        if (pidx2 >= 0) parent[pidx2] = store_add<PM>(par2, S);
-        if (values) {
-            values[pidx] = S;
-            if (pidx2 >= 0) values[pidx2] = S;
-        }
-    }
+    const LaneRows<T> rows{blocks + q.off + lane, q.ld};
+    const double S = stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, q.n, rows, active);
+    if (active) finish(q, par, S);
 }
 
 // B -> LB' and LB += LB' (steps 7-8), one problem of size N per instance of
@@ -205,11 +220,11 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     const int n = active ? I.N : 0;
     T* blk = B + I.offB;
     int32_t* sg = (active && sigma) ? sigma + I.offB : nullptr;
-    T* const bw = active ? blk : nullptr;
+    const LaneRows<T> rows{blk + lane, n};
     const int nu = __builtin_amdgcn_readfirstlane(n);
     const double S = ballot64(n != nu) == 0
-                         ? stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, nu, bw, nu, sg)
-                         : stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, n, bw, n, sg);
+                         ? stage_and_solve<T, SEG, AUC, DOWN, true>(smem, seg, lane, nmax, nu, rows, active, sg)
+                         : stage_and_solve<T, SEG, AUC, DOWN, false>(smem, seg, lane, nmax, n, rows, active, sg);
     if (active && lane == 0) {
         const double L = DOWN ? add_down(lb[2 * k], S) : lb[2 * k] + S;
         lb[2 * k] = L;
@@ -255,21 +270,21 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     int n = in ? nv[b] : 0;
     const bool bad = n < 0 || n > SEG;
     if (bad) n = 0;
-    T* mat = (in && !bad) ? cost + mat_off[b] : nullptr;
-    const int64_t vo = (in && !bad && vec_off) ? vec_off[b] : 0;
-    T* const Rw = (write_residual && n > 0) ? mat : nullptr;
+    T* const mat = n > 0 ? cost + mat_off[b] : cost;
+    const int64_t vo = (n > 0 && vec_off) ? vec_off[b] : 0;
+    const bool wr = write_residual && n > 0;
     T* const dw = (duals && n > 0) ? duals + 4 * vo : nullptr;
     int32_t* const aw = (assign && n > 0) ? assign + vo : nullptr;
-    // The size as a scalar when every problem of the wave has it, as in
-    // k_lap_family_s.
+    // The size as a scalar when every problem of the wave has it.
     auto solve = [&](int nn, auto uni) __attribute__((always_inline)) -> double {
         const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(SEG), nn);
-        stage_block<T, SEG>(sc.M, sc.ld, mat, nn, nn, lane);
+        const LaneRows<T> rows{mat + lane, nn};
+        stage_block(sc.M, sc.ld, rows, nn, lane);
         wave_sync();
         if constexpr (AUC)
-            return lap_auction_flat<T, SEG, PM == kPrecF32Down>(sc, nn, Rw, nn, dw, aw);
+            return lap_auction_flat<T, SEG, PM == kPrecF32Down>(sc, nn, rows, wr, dw, aw);
         else
-            return lap_concentrate<T, SEG, PM == kPrecF32Down, decltype(uni)::value>(sc, nn, Rw, nn, dw, aw);
+            return lap_concentrate<T, SEG, PM == kPrecF32Down, decltype(uni)::value>(sc, nn, rows, wr, dw, aw);
     };
     const int nu = __builtin_amdgcn_readfirstlane(n);
     const double S = ballot64(n != nu) == 0 ? solve(nu, std::true_type{}) : solve(n, std::false_type{});

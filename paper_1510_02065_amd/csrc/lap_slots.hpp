@@ -256,6 +256,31 @@ __device__ __forceinline__ int wave_size(int n)
     return nw;
 }
 
+// The rows of this lane's column in global memory: entry r is at(r).
+// LaneRows: a pointer and a stride (in entries) per lane.  WaveRows: one base
+// pointer and stride (in bytes) for the wave and a 32-bit offset per lane, so
+// that a row's address is scalar work.
+template <typename T>
+struct LaneRows {
+    T* p;   // this lane's column in row 0
+    long long ld;
+    __device__ __forceinline__ T& at(int r) const
+    {
+        return *reinterpret_cast<T*>(reinterpret_cast<char*>(p) +
+                                     (size_t)(unsigned)__umul24((unsigned)r, (unsigned)ld * (unsigned)sizeof(T)));
+    }
+};
+template <typename T>
+struct WaveRows {
+    char* base;
+    unsigned ldb;   // bytes
+    unsigned off;   // bytes
+    __device__ __forceinline__ T& at(int r) const
+    {
+        return *reinterpret_cast<T*>(base + (size_t)((unsigned)r * ldb) + off);
+    }
+};
+
 // From two dual points to the residual and S: vc (this lane's column's dual of
 // the column point), ur (its row's dual of the row point) and sg (its row's
 // column, for `assign`).  The other halves of the two points are completed
@@ -263,8 +288,8 @@ __device__ __forceinline__ int wave_size(int n)
 // DOWN selects the FP32 certified completion (every written value rounded
 // toward -inf); otherwise the completion runs in T with round-to-nearest and
 // S is summed in FP64.
-template <typename T, int SEG, bool DOWN>
-__device__ __forceinline__ double lap_complete(const LapScratch<T>& sc, int n, T* __restrict__ R, long long ldr,
+template <typename T, int SEG, bool DOWN, typename Rows>
+__device__ __forceinline__ double lap_complete(const LapScratch<T>& sc, int n, const Rows& rows, bool write,
                                                T* __restrict__ duals, int32_t* __restrict__ assign, T vc, T ur, int sg)
 {
     using S = SegS<SEG>;
@@ -282,6 +307,9 @@ __device__ __forceinline__ double lap_complete(const LapScratch<T>& sc, int n, T
         T* __restrict__ avc = sc.template arr<T>(n, 0);
         T* __restrict__ aur = sc.template arr<T>(n, 1);
         T* __restrict__ auc = sc.template arr<T>(n, 2);
+        struct RowIn {
+            T m, u, w;
+        };
         if (ok) {
             avc[l] = vc;
             aur[l] = ur;
@@ -294,14 +322,10 @@ __device__ __forceinline__ double lap_complete(const LapScratch<T>& sc, int n, T
             chunked<true>(n, [&](int r) { return Mcol[__umul24(r, ldm)] - aur[r]; }, [&](int, T x) { vr = tmin(x, vr); });
         }
         wave_sync();
-        if (ok && R != nullptr) {
-            T* Rr = R + l;
-            for (int r = 0; r < n; ++r, Rr += ldr) {
-                const T m = Mcol[__umul24(r, ldm)];
-                const T r1 = (m - vc) - auc[r];
-                const T r2 = (m - aur[r]) - vr;
-                *Rr = (T)0.5 * (r1 + r2);
-            }
+        if (ok && write) {
+            chunked<false>(
+                n, [&](int r) { return RowIn{Mcol[__umul24(r, ldm)], auc[r], aur[r]}; },
+                [&](int r, const RowIn& x) { rows.at(r) = (T)0.5 * (((x.m - vc) - x.u) + ((x.m - x.w) - vr)); });
         }
         if (ok) {
             if (duals != nullptr) {
@@ -357,18 +381,22 @@ __device__ __forceinline__ double lap_complete(const LapScratch<T>& sc, int n, T
         wave_sync();
         if (ok) au[l] = U;
         wave_sync();
-        if (ok && R != nullptr) {
-            T* Rr = R + l;
+        if (ok && write) {
             const double aV = __builtin_fabs(V) * 0x1p-50;
-            for (int r = 0; r < n; ++r, Rr += ldr) {
-                const double m = (double)Mcol[__umul24(r, ldm)];
-                const double ur_ = au[r];
-                const double t = (m - V) - ur_;
-                // 2^-50 (|M| + |U| + |V|), the sum rounded once before
-                // the FMA and once in it: >= (1 - 2^-52) of the exact one.
-                const double margin = __builtin_fma(__builtin_fabs(m) + __builtin_fabs(ur_), 0x1p-50, aV);
-                *Rr = to_float_down_nonneg(__builtin_fmax(t - margin, 0.0));
-            }
+            struct RowIn {
+                T m;
+                double u;
+            };
+            chunked<false>(
+                n, [&](int r) { return RowIn{Mcol[__umul24(r, ldm)], au[r]}; },
+                [&](int r, const RowIn& x) {
+                    const double m = (double)x.m;
+                    const double t = (m - V) - x.u;
+                    // 2^-50 (|M| + |U| + |V|), the sum rounded once before
+                    // the FMA and once in it: >= (1 - 2^-52) of the exact one.
+                    const double margin = __builtin_fma(__builtin_fabs(m) + __builtin_fabs(x.u), 0x1p-50, aV);
+                    rows.at(r) = to_float_down_nonneg(__builtin_fmax(t - margin, 0.0));
+                });
         }
         if (ok) {
             if (duals != nullptr) {
@@ -431,16 +459,26 @@ __device__ __forceinline__ unsigned long long lap_start(const LapScratch<T>& sc,
     const int last = ::max(n - 1, 0);
     unsigned long long freec = ballot64(ok);
     int cnt = 0;
-    for (int r0 = 0; r0 < nw; r0 += kLapChunk) {
+    auto take = [&](unsigned long long z) __attribute__((always_inline)) {
+        freec &= ~SegBits<SEG>::lowest(z & freec);
+        cnt += lane_bit(freec) ? 1 : 0;
+    };
+    int r0 = 0;
+    if constexpr (UNI) {   // whole chunks: no clamps, no rows past the end
+        for (; r0 + kLapChunk <= n; r0 += kLapChunk) {
+            T x[kLapChunk];
+#pragma unroll
+            for (int e = 0; e < kLapChunk; ++e) x[e] = reduced(r0 + e);
+#pragma unroll
+            for (int e = 0; e < kLapChunk; ++e) take(ballot64(x[e] == v));
+        }
+    }
+    for (; r0 < nw; r0 += kLapChunk) {
         T x[kLapChunk];
 #pragma unroll
         for (int e = 0; e < kLapChunk; ++e) x[e] = reduced(min(r0 + e, last));
 #pragma unroll
-        for (int e = 0; e < kLapChunk; ++e) {
-            const unsigned long long z = ballot64(x[e] == v) & ballot64(r0 + e < n) & freec;
-            freec &= ~SegBits<SEG>::lowest(z);
-            cnt += lane_bit(freec) ? 1 : 0;
-        }
+        for (int e = 0; e < kLapChunk; ++e) take(ballot64(x[e] == v) & ballot64(r0 + e < n));
     }
     prow = ok && !lane_bit(freec) ? cnt : -1;
     if (prow >= 0) taken[prow] = l;
@@ -588,8 +626,8 @@ __device__ __forceinline__ void canonical_split(const LapScratch<T>& sc, int n, 
 }
 
 // Solve, canonicalise and write residuals for the n x n matrix sc.M (in LDS,
-// row stride sc.ld, left unchanged).  R (nullable) receives the residual (row
-// stride ldr), duals (nullable) [uc | vc | ur | vr], assign (nullable) the
+// row stride sc.ld, left unchanged).  The residual goes to `rows` when
+// `write`, duals (nullable) get [uc | vc | ur | vr], assign (nullable) the
 // solver's assignment.  Returns S to every lane of the segment.  Called by
 // whole waves; segments may have different n (0 <= n <= SEG), unless UNI (n is
 // then a scalar).
@@ -602,8 +640,8 @@ __device__ __forceinline__ void canonical_split(const LapScratch<T>& sc, int n, 
 // per row.  The column reached is the lowest candidate of the key minimum.  An
 // augmenting path is walked on the scalar unit, one segment at a time.  Every pass of an active segment
 // adds a column to its tree or uses up a free row, so the loop ends.
-template <typename T, int SEG, bool DOWN, bool UNI>
-__device__ __forceinline__ double lap_concentrate(const LapScratch<T>& sc, int n, T* __restrict__ R, long long ldr,
+template <typename T, int SEG, bool DOWN, bool UNI, typename Rows>
+__device__ __forceinline__ double lap_concentrate(const LapScratch<T>& sc, int n, const Rows& rows, bool write,
                                                   T* __restrict__ duals, int32_t* __restrict__ assign)
 {
     using S = SegS<SEG>;
@@ -754,7 +792,7 @@ __device__ __forceinline__ double lap_concentrate(const LapScratch<T>& sc, int n
     T vc, ur;
     int sg;
     canonical_split<T, SEG, UNI>(sc, n, v, ucol, prow, vc, ur, sg);
-    return lap_complete<T, SEG, DOWN>(sc, n, R, ldr, duals, assign, vc, ur, sg);
+    return lap_complete<T, SEG, DOWN>(sc, n, rows, write, duals, assign, vc, ur, sg);
 }
 
 }  // namespace qap

@@ -231,44 +231,50 @@ __host__ __device__ __forceinline__ long long pair_row(int N, int a, int la, int
 // N (N-1) (N-2) apart).
 // The quotients are taken in FP32 and corrected once: h < N^2 (N-1)^2 / 2 <
 // 2^23 for N <= 64 is exact in FP32 and the computed quotient is within
-// 2^-22 relative (less than 1/2) of the true one.  Facility a of pair index
+// 2^-20 relative (less than 1/2) of the true one.  Facility a of pair index
 // P is the largest a with S(a) = a (2N - a - 1) / 2 <= P, from the root of
-// that quadratic, corrected the same way.
+// that quadratic, corrected the same way.  On the device the reciprocals and
+// the root are the hardware's (within a few units in the last place) and the
+// products 24-bit (full rate): every factor is below 2^24.
+__host__ __device__ __forceinline__ int quotient24(int x, int d)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)d));
+    const int r = x - __mul24(q, d);
+#else
+    const int q = (int)((float)x * (1.0f / (float)d));
+    const int r = x - q * d;
+#endif
+    return q + (r >= d) - (r < 0);
+}
 __host__ __device__ __forceinline__ void pair_block(int N, long long h, long long* beta, long long* twin,
                                                     long long* base)
 {
+#ifdef __HIP_DEVICE_COMPILE__
+    auto mul = [](int x, int y) { return __mul24(x, y); };
+    auto root = [](float x) { return __builtin_amdgcn_sqrtf(x); };
+#else
+    auto mul = [](int x, int y) { return x * y; };
+    auto root = [](float x) { return sqrtf(x); };
+#endif
     const int n1 = N - 1;
-    const int NL = N * n1;
+    const int NL = mul(N, n1);
     const int hh = (int)h;
-    int P = (int)((float)hh * (1.0f / (float)NL));
-    int L = hh - P * NL;
-    if (L < 0) {
-        --P;
-        L += NL;
-    } else if (L >= NL) {
-        ++P;
-        L -= NL;
-    }
+    const int P = quotient24(hh, NL);
+    const int L = hh - mul(P, NL);
     // 32-bit products up to the last multiplication (block numbers are below
     // N^2 (N-1)^2 < 2^24); the first-row offset needs 64 bits.
-    *base = (long long)(((unsigned long long)(unsigned)(P * (N - 2)) * (unsigned)NL + (unsigned)L) * (unsigned)(N - 2));
+    *base = (long long)(((unsigned long long)(unsigned)mul(P, N - 2) * (unsigned)NL + (unsigned)L) * (unsigned)(N - 2));
     const float tw = (float)(2 * N - 1);
-    int a = (int)((tw - sqrtf(tw * tw - 8.0f * (float)P)) * 0.5f);
-    if (a * (2 * N - a - 1) / 2 > P) --a;
-    else if ((a + 1) * (2 * N - a - 2) / 2 <= P) ++a;
-    const int b = a + 1 + (P - a * (2 * N - a - 1) / 2);
-    int la = (int)((float)L * (1.0f / (float)n1));
-    int lq = L - la * n1;
-    if (lq < 0) {
-        --la;
-        lq += n1;
-    } else if (lq >= n1) {
-        ++la;
-        lq -= n1;
-    }
+    int a = (int)((tw - root(tw * tw - 8.0f * (float)P)) * 0.5f);
+    auto S = [&](int x) { return mul(x, 2 * N - 1 - x) >> 1; };
+    a += (S(a + 1) <= P) - (S(a) > P);
+    const int b = a + 1 + (P - S(a));
+    const int la = quotient24(L, n1);
+    const int lq = L - mul(la, n1);
     const int lb = lq + (lq >= la);
-    *beta = ((a * N + la) * n1 + (b - 1)) * n1 + lq;
-    *twin = ((b * N + lb) * n1 + a) * n1 + (la - (la > lb));
+    *beta = mul(mul(mul(a, N) + la, n1) + (b - 1), n1) + lq;
+    *twin = mul(mul(mul(b, N) + lb, n1) + a, n1) + (la - (la > lb));
 }
 
 // Offset of d_{(a,la),(b,lb),(c,lc)} inside block beta_of(a,la,b,lb).
