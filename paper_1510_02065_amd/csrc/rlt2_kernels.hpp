@@ -629,8 +629,15 @@ struct RunBuf {
 // consecutive among that XCD's ids (as in k_sweep), so the lines its boxes
 // share meet in that XCD's L2.  pre/ids as in k_sweep_triple, with
 // 8 ceil(ntri / 8) box_tiles^2 workgroups per instance.
+//
+// Registers: the FP32 kernels of edges up to 19 are held to 128 (four waves
+// per SIMD, as many workgroups as LDS admits; without the cap the compiler
+// takes up to 144 and one workgroup less fits: certified N = 33 2.33 ms, now
+// 1.71, N = 38 4.32, now 3.55).  Edges from 20 keep four runs of 20 or more
+// entries and spill 80 at that cap (N = 40 5.6 against 9.1 ms), so they and
+// the FP64 kernels (N = 40 8.1 ms with two workgroups) have 256.
 template <int PM, int BS>
-__global__ __launch_bounds__(BoxShape<BS>::NT, 2) void k_sweep_box(
+__global__ __launch_bounds__(BoxShape<BS>::NT, PM != kPrecF64 && BS < 20 ? 4 : 2) void k_sweep_box(
     StoreT<PM>* __restrict__ Dd, const StoreT<PM>* __restrict__ CC, StoreT<PM>* __restrict__ B,
     const int* __restrict__ tri, const Inst* __restrict__ inst, const long long* __restrict__ pre,
     const int* __restrict__ ids, int K, const int* __restrict__ act)
