@@ -97,8 +97,10 @@ typedef struct {
     int trace_level;  /* 0: bound only; 1: per-iteration LB and LB' (default);
                          2: also the value moved by every concentration of the
                          most recent iteration (qap_rlt2_lap_values)           */
-    int use_graph;    /* 1 (default): qap_rlt2_ascend replays one captured HIP
-                         graph per iteration; 0: plain launches                */
+    int use_graph;    /* 1 (default): once a handle has run 64 iterations,
+                         qap_rlt2_ascend replays a captured HIP graph of eight
+                         at a time (not with the overlapped schedule); before
+                         that, and with 0: plain launches                      */
     int autotune;     /* accepted and not used: the concentration kernels'
                          launch shape follows from the problem size (every
                          shape gives the same results)                       */
@@ -123,8 +125,9 @@ typedef struct {
                          sizes, qap_rlt2_ascend runs the sweep of each size
                          and then its D->C concentration on a second stream,
                          beside the next size's sweep (both streams at the
-                         default priority; the same results bit for bit);
-                         0: one step after the other                         */
+                         default priority; the same results bit for bit),
+                         when the largest size is 16 or more; 0: one step
+                         after the other                                     */
 } qap_rlt2_opts;
 
 typedef struct qap_rlt2 qap_rlt2;
@@ -219,8 +222,7 @@ void qap_rlt2_destroy(qap_rlt2* h);
  * constant (see qap_subproblem).  A batch handle holds `count` independent
  * instances of possibly different sizes and advances all of them together:
  * every step of an iteration is one launch over all instances (one per
- * segment-size class for the concentration steps), and qap_rlt2_ascend
- * replays one HIP graph per iteration.  Every call above applies to all
+ * segment-size class for the concentration steps).  Every call above applies to all
  * instances; the calls that return one instance's data (bound, trace,
  * lap_values, read_state) return instance 0's.
  *

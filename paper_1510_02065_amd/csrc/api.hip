@@ -34,6 +34,9 @@ namespace {
 
 hipError_t enqueue_step_any(qap_rlt2* h, int step) { return QAP_OPS(h->precision, enqueue_step(h, step)); }
 
+// The overlapped schedule's smallest largest instance (see make_handle).
+constexpr int kOverlapMinN = 16;
+
 // A whole iteration.  With one stored block per complementary pair step 5 is
 // left out: steps 1-2 clear every c, so the concentration of step 4 leaves the
 // same value S in c_ijkn and c_knij and their mean is that value (exactly, in
@@ -129,6 +132,52 @@ qap_status mark_broken(qap_rlt2* h, hipError_t e, const char* what)
 {
     h->broken = true;
     return fail(QAP_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+// `count` iterations on the stream: launched one by one, or as replays of one
+// captured graph of kGraphIters of them.
+//
+// The device never waits for the host either way: an iteration is five
+// launches of some 3 us of host time each against 30 us of kernels at N = 4 and
+// 44 at N = 10.  A graph of a single iteration cost 7 to 10 us of device time
+// per replay (N = 10 53 us per iteration against 46 launched directly, N = 16
+// 150 against 140); one of eight runs at the direct launches' pace (N = 4 30.1
+// against 29.8 us, N = 14 77.0 against 76.2) and takes an eighth of the
+// host's time, but capturing it costs 110 us.  So a handle runs its first
+// kGraphAfter iterations directly.  The overlapped schedule always does: the
+// fork and join of its two streams cost more as graph nodes (48 nodes of N =
+// 10..22, FP64: 27.7 ms for four iterations as graphs, 26.4 directly).
+constexpr int kGraphIters = 8;
+constexpr int64_t kGraphAfter = 64;
+
+qap_status enqueue_iterations(qap_rlt2* h, int count)
+{
+    int t = 0;
+    while (t < count) {
+        if (!h->use_graph || h->overlap || h->launched < kGraphAfter || count - t < kGraphIters) {
+            const hipError_t e = enqueue_iteration(h);
+            if (e != hipSuccess) return mark_broken(h, e, "kernel launch");
+            ++t;
+            ++h->launched;
+            continue;
+        }
+        if (!h->graph_exec) {
+            hipError_t e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal);
+            if (e != hipSuccess) return mark_broken(h, e, "hipStreamBeginCapture");
+            hipError_t el = hipSuccess;
+            for (int x = 0; x < kGraphIters && el == hipSuccess; ++x) el = enqueue_iteration(h);
+            e = hipStreamEndCapture(h->stream, &h->graph);
+            if (el != hipSuccess) return mark_broken(h, el, "kernel launch during capture");
+            if (e != hipSuccess) return mark_broken(h, e, "hipStreamEndCapture");
+            e = hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0);
+            if (e != hipSuccess) return mark_broken(h, e, "hipGraphInstantiate");
+        }
+        const hipError_t e = hipGraphLaunch(h->graph_exec, h->stream);
+        if (e != hipSuccess) return mark_broken(h, e, "hipGraphLaunch");
+        t += kGraphIters;
+        h->launched += kGraphIters;
+    }
+    return QAP_OK;
 }
 
 template <typename X>
@@ -283,7 +332,14 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, qap
     }
     // The overlapped schedule: the D family split by instance size, in the
     // sweep classes' order, a second stream and the events between them.
-    if (o.overlap && h->level == 2 && h->dmode == qap::kHalfStore && h->sweep_cls.size() > 1) {
+    // Where every size is small the launches and events per size take longer
+    // than what they overlap (ten iterations: 40 nodes of N = 3..6 1.42 ms
+    // overlapped and 0.70 in sequence, 40 of 8..14 5.1 and 4.8; four of 100
+    // nodes of N = 10..14 6.96 and 6.92); with larger ones it is the faster
+    // schedule (14 nodes of N = 10..16 4.02 and 4.07, 48 of 10..18 8.0 and
+    // 8.3, 48 of 10..22 26.4 and 27.9).
+    if (o.overlap && h->level == 2 && h->dmode == qap::kHalfStore && h->sweep_cls.size() > 1 &&
+        h->Nmax >= kOverlapMinN) {
         for (const qap::SweepClass& sc : h->sweep_cls) {
             qap::ClassHost c;
             c.nmax = sc.N - 2;
@@ -591,27 +647,7 @@ qap_status qap_rlt2_ascend(qap_rlt2* h, int iters, double* bound)
         // With the stop rule on, iterations go in small chunks so that the
         // call returns soon after every instance has stopped.
         const int chunk = (int)std::min<long long>(left, stop_rule ? 8 : qap::kTraceCap);
-        if (h->use_graph) {
-            if (!h->graph_exec) {
-                hipError_t e = hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal);
-                if (e != hipSuccess) return mark_broken(h, e, "hipStreamBeginCapture");
-                hipError_t el = enqueue_iteration(h);
-                e = hipStreamEndCapture(h->stream, &h->graph);
-                if (el != hipSuccess) return mark_broken(h, el, "kernel launch during capture");
-                if (e != hipSuccess) return mark_broken(h, e, "hipStreamEndCapture");
-                e = hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0);
-                if (e != hipSuccess) return mark_broken(h, e, "hipGraphInstantiate");
-            }
-            for (int t = 0; t < chunk; ++t) {
-                hipError_t e = hipGraphLaunch(h->graph_exec, h->stream);
-                if (e != hipSuccess) return mark_broken(h, e, "hipGraphLaunch");
-            }
-        } else {
-            for (int t = 0; t < chunk; ++t) {
-                hipError_t e = enqueue_iteration(h);
-                if (e != hipSuccess) return mark_broken(h, e, "kernel launch");
-            }
-        }
+        if ((st = enqueue_iterations(h, chunk)) != QAP_OK) return st;
         hipError_t e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return mark_broken(h, e, "hipStreamSynchronize");
         st = drain_trace(h);

@@ -127,7 +127,8 @@ struct qap_rlt2 {
     double* dCt = nullptr;      // certification: c~ (packed like C), allocated by the first certification
     double* dBt = nullptr;      // certification: b~ (packed like B)
     double* dCert = nullptr;    // certification result per instance
-    hipGraphExec_t graph_exec = nullptr;
+    hipGraphExec_t graph_exec = nullptr;   // kGraphIters iterations
+    int64_t launched = 0;                  // iterations enqueued by qap_rlt2_ascend
     hipGraph_t graph = nullptr;
     std::vector<std::vector<double>> tLB, tLBp;
     std::vector<int64_t> itk;       // loop iterations each instance has run

@@ -163,6 +163,26 @@ def test_determinism_and_graph_equivalence():
         np.testing.assert_array_equal(Dst, runs[0][1])
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_graph_replay_of_later_iterations_equals_launches(precision):
+    # The first 64 iterations of a handle are launched one by one, later ones
+    # as graphs of eight with a remainder launched: calls that end inside
+    # either, with single steps between them.
+    F, D = qapgen.small(7, 5)
+    runs = []
+    for use_graph in (True, False):
+        g = Rlt2(F, D, precision=precision, use_graph=use_graph)
+        for iters in (61, 20, 3, 8, 17):
+            g.ascend(iters)
+            for s in (3, 4, 5, 6, 7):
+                g.step(s)
+        runs.append((g.trace()[0], *g.read_state()[1:]))
+        g.close()
+    assert len(runs[0][0]) == 1 + 61 + 20 + 3 + 8 + 17 + 5
+    for x, y in zip(*runs):
+        np.testing.assert_array_equal(x, y)
+
+
 def test_step_by_step_equals_ascend():
     F, D = qapgen.small(8, 7)
     a = Rlt2(F, D)
