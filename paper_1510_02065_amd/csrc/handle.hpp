@@ -108,18 +108,22 @@ struct qap_rlt2 {
     std::vector<hipEvent_t> ev_size;          // one per sweep class: its sweep is done
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     std::vector<int> tri;                     // facility triples of every instance
+    void* arena = nullptr;   // every device array below but D, dCt and dBt
     qap::Inst* dInst = nullptr;
     long long *dPreB = nullptr, *dPreC = nullptr, *dPreWG = nullptr, *dPreCert = nullptr;
     void* dB = nullptr;
     void* dC = nullptr;
     void* dD = nullptr;
     void* dCC = nullptr;
+    double *dF = nullptr, *dDm = nullptr, *dB0 = nullptr;   // the instances' data, N^2 entries each
+    int* dFix = nullptr;        // a children handle's (facility, location) pairs
     double* dLB = nullptr;      // [LB, LB'] per instance
     double* dValD = nullptr;    // per-block values of the last step 4 (packed like C)
     double* dValC = nullptr;    // per-block values of the last step 6 (packed like B)
     double* dValB = nullptr;    // per-instance value of the last step 7
-    double* dTrace = nullptr;   // K x kTraceCap x (LB, LB')
-    long long* dCounter = nullptr;
+    // One record, read back in one copy: dCounter (K), dLB (2 K), dTrace.
+    double* dTrace = nullptr;   // kTraceCap x K x (LB, LB')
+    long long* dCounter = nullptr;   // trace entries of each instance since the last readback
     int* dTri = nullptr;
     int* dAct = nullptr;        // per-instance flag: the dual ascent still runs
     double* dStop = nullptr;    // (K, UB) of the stop rule

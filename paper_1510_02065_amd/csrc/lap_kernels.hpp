@@ -194,7 +194,8 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
 // B -> LB' and LB += LB' (steps 7-8), one problem of size N per instance of
 // the class.  lb[2k] = LB, lb[2k+1] = LB' (FP64; in FP32
 // certified mode the bound accumulates rounding toward -inf).  The instance's
-// trace gets (LB, LB') at position counter[k]++ when below trace_cap, and
+// trace gets (LB, LB') at position t = counter[k]++ when below trace_cap
+// (entry t of the handle's `count` instances next to each other), and
 // sigma (nullable, packed like B) the assignment of the B problem, a
 // permutation of the instance.  Stop rule of Algorithm 1, with stop[0] = K and
 // stop[1] = UB (UB <= 0: none): the instance's act flag is cleared once
@@ -203,7 +204,7 @@ template <int PM, int SEG, bool AUC = false>
 __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, const Inst* __restrict__ inst,
                                                 FamilyClass fc, int nmax, double* __restrict__ lb,
                                                 double* __restrict__ trace, long long* __restrict__ counter,
-                                                long long trace_cap, double* __restrict__ values,
+                                                long long trace_cap, int count, double* __restrict__ values,
                                                 int32_t* __restrict__ sigma, int* __restrict__ act,
                                                 const double* __restrict__ stop)
 {
@@ -233,8 +234,8 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
         if (counter) {
             const long long t = counter[k];
             if (trace && t < trace_cap) {
-                trace[(k * trace_cap + t) * 2] = L;
-                trace[(k * trace_cap + t) * 2 + 1] = S;
+                trace[(t * count + k) * 2] = L;
+                trace[(t * count + k) * 2 + 1] = S;
             }
             counter[k] = t + 1;
         }
