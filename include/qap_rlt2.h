@@ -283,9 +283,9 @@ qap_status qap_subproblem(int N, const double* F, const double* D, int m, const 
  *         assignment (not unique when there are ties).
  * flags   QAP_LAP_DEVICE: every pointer above is device memory (of the
  *         calling thread's current device) and the call is asynchronous on
- *         `stream`; a device pass sorts the problems by size into a
- *         workspace of 16 bytes per problem taken from the stream-ordered
- *         allocator (hipMallocAsync) and released the same way.  Sizes
+ *         `stream`; for more than 1024 problems a device pass sorts
+ *         them by size into a workspace of 4 bytes per problem taken from the
+ *         stream-ordered allocator (hipMallocAsync) and released the same way.  Sizes
  *         outside [0, 64] are not checked on the host: such a problem's
  *         value is NaN and nothing else of it is written.  Otherwise all
  *         pointers are host memory, sizes are checked (QAP_EINVAL) and the
@@ -311,8 +311,8 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off,
  * capture, tight serving loops, harnesses that forbid allocation).  Same
  * arguments and results as qap_lap_solve with QAP_LAP_DEVICE (every pointer
  * is device memory of the calling thread's current device; asynchronous on
- * `stream`).  The size bucketing uses a static device array of the library
- * (16 MiB, one per device, held until the process ends) instead of a
+ * `stream`).  The sort by size uses a static device array of the library
+ * (4 MiB, one per device, held until the process ends) instead of a
  * workspace.  Errors: QAP_EINVAL when flags lack QAP_LAP_DEVICE or when
  * batch > QAP_LAP_NOALLOC_MAX_BATCH; QAP_EDEVICE for HIP errors.  Every call
  * on a device shares that device's array (each call clears what it needs on

@@ -156,11 +156,11 @@ struct Ops {
     static int sweep_threads(int N, size_t lds_limit);
     // Location tiles per axis of k_sweep_box at size N.
     static int sweep_tiles(int N);
-    // Batched assignment problems (qap_lap_solve) with `seg` lanes per
-    // problem: slot s < count (count = *dcount if dcount is not null, the
-    // grid sized for `count`) solves problem idx[s] (s if idx is null), by
-    // the canonical dual or the auction (solver, a qap_lap_solver value).
-    static hipError_t lap_batch(hipStream_t st, int seg, int count, const int* dcount, const int32_t* idx,
+    // Batched assignment problems (qap_lap_solve) of sizes up to nmax (at
+    // least 16): the first `count` (of idx when it is not null) or, with
+    // `range` in device memory, the range[1] (at most `count`) from
+    // idx[range[0]] on, by the canonical dual or the auction (solver, a qap_lap_solver value).
+    static hipError_t lap_batch(hipStream_t st, int nmax, int count, const int* range, const int32_t* idx,
                                 const int32_t* n, const int64_t* mo, const int64_t* vo, void* cost, double* value,
                                 void* duals, int32_t* assign, int wr, int solver);
     // Children of parent instance pk of handle ph (fixings fix[2c], fix[2c+1]

@@ -245,14 +245,16 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
 }
 
 // Generic batch (qap_lap_solve): launch slot s < count solves problem
-// b = idx[s] (b = s when idx is null); count = *dcount when dcount is not
-// null, else `count`.  Problem b has size n[b] (<= SEG, else its value is NaN
-// and nothing else is written), matrix at cost + mat_off[b], vectors at
-// vec_off[b] (vec_off may be null when duals and assign are).  AUC: the
+// b = idx[first + s] (b = s when idx is null).  With `range` (device memory)
+// first = range[0] and count = range[1]; without it they are 0 and `count`.  Problem b has size n[b] (<=
+// nmax <= SEG, else its value is NaN and nothing else is written), matrix at
+// cost + mat_off[b], vectors at vec_off[b] (vec_off may be null when duals and
+// assign are).  The launch's LDS holds problems of up to nmax.  AUC: the
 // auction solver (lap_auction_flat) instead of the canonical dual.
 template <int PM, int SEG, bool AUC>
-__global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restrict__ dcount,
-                                                  const int32_t* __restrict__ idx, const int32_t* __restrict__ nv,
+__global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restrict__ range,
+                                                  const int32_t* __restrict__ idx, int nmax,
+                                                  const int32_t* __restrict__ nv,
                                                   const int64_t* __restrict__ mat_off,
                                                   const int64_t* __restrict__ vec_off,
                                                   StoreT<PM>* __restrict__ cost, double* __restrict__ value,
@@ -264,12 +266,13 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     constexpr int LPW = 64 / SEG;
     const int seg = threadIdx.x / SEG;
     const int lane = threadIdx.x & (SEG - 1);
-    const int cnt = dcount ? *dcount : count;
+    const int cnt = range ? range[1] : count;
+    if ((int64_t)blockIdx.x * LPW >= cnt) return;
     const int64_t s = (int64_t)blockIdx.x * LPW + seg;
     const bool in = s < cnt;
-    const int64_t b = in ? (idx ? (int64_t)idx[s] : s) : 0;
+    const int64_t b = !in ? 0 : idx ? (int64_t)idx[(range ? range[0] : 0) + s] : s;
     int n = in ? nv[b] : 0;
-    const bool bad = n < 0 || n > SEG;
+    const bool bad = n < 0 || n > nmax;
     if (bad) n = 0;
     T* const mat = n > 0 ? cost + mat_off[b] : cost;
     const int64_t vo = (n > 0 && vec_off) ? vec_off[b] : 0;
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     int32_t* const aw = (assign && n > 0) ? assign + vo : nullptr;
     // The size as a scalar when every problem of the wave has it.
     auto solve = [&](int nn, auto uni) __attribute__((always_inline)) -> double {
-        const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(SEG), nn);
+        const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(nmax), nn);
         const LaneRows<T> rows{mat + lane, nn};
         stage_block(sc.M, sc.ld, rows, nn, lane);
         wave_sync();

@@ -2,13 +2,15 @@
 // cost concentration performs (Section 4.1 of arXiv 1510.02065), offered on
 // its own for host or device buffers.
 //
-// Problems of different sizes run in segments of different widths: a problem
-// of size n takes the narrowest segment of 8, 16, 32 or 64 lanes that holds
-// it, so a wave carries 8, 4, 2 or 1 problems and small problems do not each
-// occupy a whole wave.  With host buffers the host sorts the problems into the
-// four size classes; with device buffers (whose sizes the host does not read)
-// a device pass writes the four work lists into a workspace and each class's
-// launch reads its count from there.
+// A batch that the chip holds at once runs as one launch, a wave per problem.
+// Larger ones run in size classes, one launch each with segments of 16, 32 or
+// 64 lanes per problem (4, 2 or 1 problems per wave), so that small problems
+// do not each occupy a whole wave.  Within a class the problems go by falling size: a wave's
+// problems then mostly have one size (its loop counts are scalars and none of
+// its problems waits for a larger one), and the launch ends on short ones.
+// With host buffers the host sorts the problems; with device buffers (whose
+// sizes the host does not read) a device pass writes the order into a workspace
+// and each class's launch reads its range from there.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -23,62 +25,129 @@ using qap::fail;
 
 namespace qap {
 
-// Size class of a problem of size n (0 .. 3 for 8, 16, 32, 64 lanes).  Sizes
-// outside [0, 64] go to the widest class, whose kernel marks them unsolved.
-__host__ __device__ inline int size_class(int n)
+// Size classes of a batch, one launch each.  A launch's width (lanes per
+// problem) and LDS are those of its largest size, and the next one starts when
+// its last problem is done, so classes cost latency and save lanes and LDS.
+// Measured (us, problems of uniform sizes, FP64 | FP32):
+//   classes up to      64           16,32,64     16,32,48,64  16,32,48,56,64
+//   1000 of 2..64      125 | 115    186 | 163
+//   1000 of 3..14       46 |  53     52 |  56
+//   4000 of 2..64      185 | 128    239 | 182
+//   6000 of 3..14       95 |  71     80 |  74     73 |  83     85 |  83
+//   6000 of 2..64      258 | 142    304 | 203    336 | 256    391 | 325
+//   20000 of 2..64     807 | 347    752 | 366    716 | 392    731 | 432
+//   20000 of 2..30     355 | 178    172 | 136    178 | 146    186 | 150
+//   20000 of 33..50   1024 | 449   1039 | 458    748 | 401    721 | 403
+//   40000 of 50..64   3026 | 1254  3040 | 1257  3061 | 1273  2773 | 1265
+//   40000 of 33..50   1997 | 838   2016 | 851   1376 | 720   1311 | 727
+// (With classes of 8, 16, 32 and 64 lanes in any order of sizes: 203 | 179,
+// 73 | 80, 254 | 200, 83 | 79, 346 | 234, 840 | 411, 223 | 175, 1063 | 477,
+// 3095 | 1283 and 2064 | 868.)  So: one class while the chip holds all but a
+// few rounds of the problems at once, a wave each (its LDS holds 1024 of 64
+// rows in FP64 and 2304 in FP32), and more the more problems there are.
+struct Classes {
+    int count;
+    int limit[5];   // largest size of each class, rising
+};
+inline Classes classes_for(int batch, int dtype)
 {
-    return n <= 8 ? 0 : n <= 16 ? 1 : n <= 32 ? 2 : 3;
+    if (dtype == QAP_FP64)
+        return batch <= 4096 ? Classes{1, {64}} : batch <= 8192 ? Classes{3, {16, 32, 64}} : Classes{5, {16, 32, 48, 56, 64}};
+    return batch <= 8192 ? Classes{1, {64}} : batch <= 32768 ? Classes{3, {16, 32, 64}} : Classes{4, {16, 32, 48, 64}};
 }
+// Up to this many problems all start at once, and their order does not matter.
+constexpr int kUnsorted = 1024;
 
-// Workspace of the device-side bucketing: kBucketHeader ints (the four class
-// counters, padded to 256 bytes) followed by four lists of `cap` problem
-// indices, list c at lists + c * cap.
-constexpr int kBucketHeader = 64;
+// Workspace of the device-side sort: kSortHeader ints (first place and number
+// of problems of each class, the problems of each size and the places handed
+// out of each size) followed by the `cap` problem indices in order.
+constexpr int kSortHeader = 256;
+constexpr int kSizes = QAP_RLT2_MAX_N + 1;
+constexpr int kSizeCount = 64, kSizePlace = 160;   // first int of either in the header
+static_assert(kSizeCount + kSizes <= kSizePlace && kSizePlace + kSizes <= kSortHeader, "header fields apart");
 
-inline size_t bucket_bytes(long long cap) { return (size_t)(kBucketHeader + 4 * cap) * sizeof(int32_t); }
+inline size_t sort_bytes(long long cap) { return (size_t)(kSortHeader + cap) * sizeof(int32_t); }
 
-__global__ __launch_bounds__(64) void k_bucket_clear(int32_t* __restrict__ counts)
+__global__ __launch_bounds__(kSortHeader) void k_sort_clear(int32_t* __restrict__ head) { head[threadIdx.x] = 0; }
+
+// The problems by falling size, a counting sort (an unsolvable one sorts as the
+// largest).  Each workgroup counts its problems by size in LDS, where the
+// counting atomic is also a problem's rank among its workgroup's of that size.
+// Up to kSortOne problems one workgroup does it all (PASS 0: no counters to
+// clear, one launch); larger batches count in one launch (PASS 1) and write
+// the list in a second one (PASS 2), with one global atomic per size and
+// workgroup in each.  20000 problems took 16.5 us when every wave reserved its
+// places class by class, and SORT_NOW in both passes now.  The order among
+// problems of one size is not fixed; each problem's result depends only on its
+// own matrix and the segment width, so it does not matter.
+constexpr int kSortThreads = 1024, kSortEach = 4, kSortOne = kSortThreads * kSortEach;
+template <int PASS>
+__global__ __launch_bounds__(kSortThreads) void k_sort(int batch, const int32_t* __restrict__ n,
+                                                       int32_t* __restrict__ head, int32_t* __restrict__ list,
+                                                       Classes cl)
 {
-    if (threadIdx.x < 4) counts[threadIdx.x] = 0;
-}
-
-// One thread per problem: append b to the list of its size class.  Each wave
-// reserves the places of its problems of a class with one atomic on that
-// class's counter (a ballot gives the count and each lane's rank), so the
-// counters see one request per wave and class instead of one per problem.
-// The order within a list is not fixed; each problem's result depends only
-// on its own matrix and the segment width, so it does not matter.
-__global__ __launch_bounds__(256) void k_bucket(int batch, const int32_t* __restrict__ n,
-                                                int32_t* __restrict__ counts, int32_t* __restrict__ lists,
-                                                long long cap)
-{
-    const long long b = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool in = b < batch;
-    const int c = in ? size_class(n[b]) : -1;
-    const unsigned lane = threadIdx.x & 63u;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int k = 0; k < 4; ++k) {
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(c == k);
-        if (m == 0ull) continue;
-        const int leader = __builtin_ctzll(m);
-        int base = 0;
-        if ((int)lane == leader) base = atomicAdd(&counts[k], __builtin_popcountll(m));
-        base = __builtin_amdgcn_readlane(base, leader);
-        if (c == k) lists[k * cap + base + __builtin_popcountll(m & below)] = (int32_t)b;
+    __shared__ int cnt[kSizes], tot[kSizes], start[kSizes];
+    const int t = threadIdx.x;
+    if (t < kSizes) {
+        cnt[t] = 0;
+        tot[t] = PASS == 2 ? head[kSizeCount + t] : 0;
     }
+    __syncthreads();
+    int size[kSortEach], rank[kSortEach];
+    const long long b0 = (long long)blockIdx.x * kSortOne + t;
+#pragma unroll
+    for (int u = 0; u < kSortEach; ++u) {
+        const long long b = b0 + u * kSortThreads;
+        size[u] = -1;
+        if (b >= batch) continue;
+        const int s = n[b];
+        size[u] = s < 0 || s > QAP_RLT2_MAX_N ? QAP_RLT2_MAX_N : s;
+    }
+#pragma unroll
+    for (int u = 0; u < kSortEach; ++u) rank[u] = size[u] >= 0 ? atomicAdd(&cnt[size[u]], 1) : 0;
+    __syncthreads();
+    if constexpr (PASS == 1) {
+        if (t < kSizes && cnt[t] > 0) atomicAdd(&head[kSizeCount + t], cnt[t]);
+        return;
+    }
+    if (t < kSizes) {
+        // Problems of larger sizes come first.
+        const int* all = PASS == 0 ? cnt : tot;
+        int place = 0;
+        for (int s = t + 1; s < kSizes; ++s) place += all[s];
+        if (blockIdx.x == 0) {
+            // A class starts with its largest size and ends with the size
+            // above the next smaller class's.
+            for (int c = 0; c < cl.count; ++c) {
+                if (t == cl.limit[c]) head[2 * c] = place;
+                if (t == (c > 0 ? cl.limit[c - 1] + 1 : 0)) {
+                    int above = 0;   // larger sizes than the class's
+                    for (int s = cl.limit[c] + 1; s < kSizes; ++s) above += all[s];
+                    head[2 * c + 1] = place + all[t] - above;
+                }
+            }
+        }
+        if (PASS == 2 && cnt[t] > 0) place += atomicAdd(&head[kSizePlace + t], cnt[t]);
+        start[t] = place;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSortEach; ++u)
+        if (size[u] >= 0)
+            list[start[size[u]] + rank[u]] = (int32_t)(b0 + u * kSortThreads);
 }
 
-// Largest batch of qap_lap_solve_noalloc: its bucketing workspace is the
-// static array below, 16 MiB per device.
+// Largest batch of qap_lap_solve_noalloc: its work list is in the
+// static array below, 4 MiB per device.
 constexpr long long kNoAllocMaxBatch = QAP_LAP_NOALLOC_MAX_BATCH;
 
 }  // namespace qap
 
-// Bucketing workspace of qap_lap_solve_noalloc, one copy on every device the
+// Work list of qap_lap_solve_noalloc, one copy on every device the
 // library runs on, held until the process ends.  In host code this name is a
 // host-side stand-in, not a device address: kernels and copies get the
 // device address from hipGetSymbolAddress (scratch_address below).
-static __device__ __align__(256) int32_t scratch[qap::kBucketHeader + 4 * qap::kNoAllocMaxBatch];
+static __device__ __align__(256) int32_t scratch[qap::kSortHeader + qap::kNoAllocMaxBatch];
 
 namespace {
 
@@ -105,25 +174,35 @@ hipError_t scratch_address(int32_t** out)
     return hipSuccess;
 }
 
-// The device-pointer solve, given a workspace of bucket_bytes(batch) bytes:
-// clear the counters, bucket, then one launch per class with its grid sized
-// for the whole batch (the kernel reads the class count and idle slots exit).
+// The device-pointer solve, given a workspace of sort_bytes(batch) bytes (null
+// up to kUnsorted problems): sort, then one launch per class with its grid
+// sized for the whole batch (the kernel reads the class's range and idle
+// waves exit), large problems first.
 hipError_t solve_device(int batch, const int32_t* n, const int64_t* mat_off, const int64_t* vec_off, void* cost,
                         int dtype, double* value, void* duals, int32_t* assign, int wr, int solver, hipStream_t st,
                         int32_t* ws)
 {
-    int32_t* counts = ws;
-    int32_t* lists = ws + qap::kBucketHeader;
-    hipLaunchKernelGGL(qap::k_bucket_clear, dim3(1), dim3(64), 0, st, counts);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(qap::k_bucket, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0, st, batch, n, counts, lists,
-                       (long long)batch);
+    const qap::Classes cl = qap::classes_for(batch, dtype);
+    if (!ws)
+        return QAP_OPS(dtype, lap_batch(st, cl.limit[0], batch, nullptr, nullptr, n, mat_off, vec_off, cost, value,
+                                        duals, assign, wr, solver));
+    int32_t* list = ws + qap::kSortHeader;
+    const dim3 threads(qap::kSortThreads);
+    hipError_t e = hipSuccess;
+    if (batch <= qap::kSortOne) {
+        hipLaunchKernelGGL(qap::k_sort<0>, dim3(1), threads, 0, st, batch, n, ws, list, cl);
+    } else {
+        const dim3 grid((unsigned)(((long long)batch + qap::kSortOne - 1) / qap::kSortOne));
+        hipLaunchKernelGGL(qap::k_sort_clear, dim3(1), dim3(qap::kSortHeader), 0, st, ws);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(qap::k_sort<1>, grid, threads, 0, st, batch, n, ws, list, cl);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(qap::k_sort<2>, grid, threads, 0, st, batch, n, ws, list, cl);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int segs[4] = {8, 16, 32, 64};
-    for (int c = 0; c < 4; ++c) {
-        e = QAP_OPS(dtype, lap_batch(st, segs[c], batch, counts + c, lists + (long long)c * batch, n, mat_off,
-                                     vec_off, cost, value, duals, assign, wr, solver));
+    for (int c = cl.count - 1; c >= 0; --c) {
+        e = QAP_OPS(dtype, lap_batch(st, cl.limit[c], batch, ws + 2 * c, list, n, mat_off, vec_off, cost, value, duals,
+                                     assign, wr, solver));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -156,23 +235,23 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
     const int wr = (flags & QAP_LAP_RESIDUAL) ? 1 : 0;
     const int solver = (flags & QAP_LAP_AUCTION) ? QAP_LAP_SOLVER_AUCTION : QAP_LAP_SOLVER_CANONICAL;
     if (flags & QAP_LAP_DEVICE) {
-        // The bucketing workspace comes from the stream-ordered allocator, so
+        // The work list's memory comes from the stream-ordered allocator, so
         // the call stays asynchronous and calls on other streams get their own.
         void* ws = nullptr;
-        hipError_t e = hipMallocAsync(&ws, qap::bucket_bytes(batch), st);
+        hipError_t e = batch > qap::kUnsorted ? hipMallocAsync(&ws, qap::sort_bytes(batch), st) : hipSuccess;
         if (e != hipSuccess)
             return fail(e == hipErrorOutOfMemory ? QAP_ENOMEM : QAP_EDEVICE,
                         std::string("hipMallocAsync: ") + hipGetErrorString(e));
         e = solve_device(batch, n, mat_off, vec_off, cost, dtype, value, duals, assign, wr, solver, st,
                          static_cast<int32_t*>(ws));
-        const hipError_t ef = hipFreeAsync(ws, st);
+        const hipError_t ef = ws ? hipFreeAsync(ws, st) : hipSuccess;
         if (e != hipSuccess) return fail(QAP_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
         if (ef != hipSuccess) return fail(QAP_EDEVICE, std::string("hipFreeAsync: ") + hipGetErrorString(ef));
         return QAP_OK;
     }
-    // Host pointers: validate, bucket by size, stage, solve, copy back.
+    // Host pointers: validate, sort by size, stage, solve, copy back.
     int64_t mat_end = 0, vec_end = 0;
-    std::vector<int32_t> order[4];   // problems of each size class
+    std::vector<int32_t> idx(batch);   // problems by falling size
     for (int b = 0; b < batch; ++b) {
         if (n[b] < 0 || n[b] > QAP_RLT2_MAX_N) return fail(QAP_EINVAL, "n[b] must be in [0, 64]");
         if (mat_off[b] < 0) return fail(QAP_EINVAL, "negative mat_off");
@@ -186,10 +265,9 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
             if (vec_off[b] < 0) return fail(QAP_EINVAL, "negative vec_off");
             vec_end = std::max(vec_end, vec_off[b] + (int64_t)n[b]);
         }
-        order[qap::size_class(n[b])].push_back(b);
+        idx[b] = b;
     }
-    std::vector<int32_t> idx;
-    for (auto& o : order) idx.insert(idx.end(), o.begin(), o.end());
+    std::stable_sort(idx.begin(), idx.end(), [n](int32_t x, int32_t y) { return n[x] > n[y]; });
     int32_t *dn = nullptr, *didx = nullptr;
     int64_t *dmo = nullptr, *dvo = nullptr;
     void *dcost = nullptr, *ddual = nullptr;
@@ -227,14 +305,15 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
     if (duals) CK2(hipMalloc(&ddual, std::max<int64_t>(4 * vec_end, 1) * es));
     if (assign) CK2(hipMalloc(&dassign, std::max<int64_t>(vec_end, 1) * sizeof(int32_t)));
     // One launch per size class.
-    int64_t first = 0;
-    const int segs[4] = {8, 16, 32, 64};
-    for (int c = 0; c < 4; ++c) {
-        const int cnt = (int)order[c].size();
-        if (cnt > 0)
-            CK2(QAP_OPS(dtype, lap_batch(st, segs[c], cnt, nullptr, didx + first, dn, dmo, dvo, dcost, dval, ddual,
-                                         dassign, wr, solver)));
-        first += cnt;
+    const qap::Classes cl = qap::classes_for(batch, dtype);
+    int first = 0;
+    for (int c = cl.count - 1; c >= 0; --c) {
+        int end = first;
+        while (end < batch && (c == 0 || n[idx[end]] > cl.limit[c - 1])) ++end;
+        if (end > first)
+            CK2(QAP_OPS(dtype, lap_batch(st, cl.limit[c], end - first, nullptr, didx + first, dn, dmo, dvo, dcost, dval,
+                                         ddual, dassign, wr, solver)));
+        first = end;
     }
     CK2(hipMemcpyAsync(value, dval, batch * sizeof(double), hipMemcpyDeviceToHost, st));
     if (wr && mat_end > 0) CK2(hipMemcpyAsync(cost, dcost, mat_end * es, hipMemcpyDeviceToHost, st));
@@ -260,7 +339,7 @@ qap_status qap_lap_solve_noalloc(int batch, const int32_t* n, const int64_t* mat
         return fail(QAP_EINVAL, "batch exceeds QAP_LAP_NOALLOC_MAX_BATCH (" +
                                     std::to_string(qap::kNoAllocMaxBatch) + ") problems");
     int32_t* ws = nullptr;
-    hipError_t e = scratch_address(&ws);
+    hipError_t e = batch > qap::kUnsorted ? scratch_address(&ws) : hipSuccess;
     if (e != hipSuccess) return fail(QAP_EDEVICE, std::string("hipGetSymbolAddress: ") + hipGetErrorString(e));
     e = solve_device(batch, n, mat_off, vec_off, cost, dtype, value, duals, assign,
                      (flags & QAP_LAP_RESIDUAL) ? 1 : 0,

@@ -109,16 +109,16 @@ hipError_t launch_B(qap_rlt2* h)
 }
 
 template <int PM, int SEG, bool AUC>
-hipError_t launch_batch_seg(hipStream_t st, int count, const int* dcount, const int32_t* idx, const int32_t* n,
-                            const int64_t* mo, const int64_t* vo, StoreT<PM>* cost, double* value,
+hipError_t launch_batch_seg(hipStream_t st, int nmax, int count, const int* range, const int32_t* idx,
+                            const int32_t* n, const int64_t* mo, const int64_t* vo, StoreT<PM>* cost, double* value,
                             StoreT<PM>* duals, int32_t* assign, int wr)
 {
     using T = StoreT<PM>;
     if (count <= 0) return hipSuccess;
     constexpr int LPW = 64 / SEG;
-    const size_t lds = slot_lds<T, SEG, AUC>(SEG);
+    const size_t lds = slot_lds<T, SEG, AUC>(nmax);
     const unsigned grid = (unsigned)((count + LPW - 1) / LPW);
-    hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, count, dcount, idx, n, mo, vo, cost,
+    hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, count, range, idx, nmax, n, mo, vo, cost,
                        value, duals, assign, wr);
     return hipGetLastError();
 }
@@ -344,7 +344,7 @@ hipError_t Ops<PM>::init_instance(qap_rlt2* h, int k, const double* dF, const do
 }
 
 template <int PM>
-hipError_t Ops<PM>::lap_batch(hipStream_t st, int seg, int count, const int* dcount, const int32_t* idx,
+hipError_t Ops<PM>::lap_batch(hipStream_t st, int nmax, int count, const int* range, const int32_t* idx,
                               const int32_t* n, const int64_t* mo, const int64_t* vo, void* cost, double* value,
                               void* duals, int32_t* assign, int wr, int solver)
 {
@@ -353,10 +353,9 @@ hipError_t Ops<PM>::lap_batch(hipStream_t st, int seg, int count, const int* dco
     T* d = static_cast<T*>(duals);
 #define QAP_SEG(SG)                                                                                            \
     return solver == QAP_LAP_SOLVER_AUCTION                                                                    \
-               ? launch_batch_seg<PM, SG, true>(st, count, dcount, idx, n, mo, vo, c, value, d, assign, wr)  \
-               : launch_batch_seg<PM, SG, false>(st, count, dcount, idx, n, mo, vo, c, value, d, assign, wr)
-    switch (seg) {
-    case 8: QAP_SEG(8);
+               ? launch_batch_seg<PM, SG, true>(st, nmax, count, range, idx, n, mo, vo, c, value, d, assign, wr)  \
+               : launch_batch_seg<PM, SG, false>(st, nmax, count, range, idx, n, mo, vo, c, value, d, assign, wr)
+    switch (seg_for(nmax)) {
     case 16: QAP_SEG(16);
     case 32: QAP_SEG(32);
     default: QAP_SEG(64);

@@ -163,3 +163,40 @@ def test_lap_device_buckets_match_host_bitwise(dtype):
     np.testing.assert_array_equal(cost.cpu().numpy(), cost_h)
     np.testing.assert_array_equal(duals.cpu().numpy(), dual_h)
     np.testing.assert_array_equal(assign.cpu().numpy(), asg_h)
+
+
+@pytest.mark.parametrize("dtype", ["fp64", "fp32n"])
+@pytest.mark.parametrize("batch", [1, 1024, 1025, 4096, 4097, 8193, 32769])
+def test_lap_device_batches_of_every_route(batch, dtype):
+    """Batches on either side of each change of route (unsorted, sorted by one
+    workgroup, by several, and the numbers of size classes), most problems
+    tiny, some of each class, some of an unsolvable size.  Integer costs, so
+    that the optimal value is exact in every precision."""
+    torch = pytest.importorskip("torch")
+    from scipy.optimize import linear_sum_assignment
+    from paper_1510_02065_amd import lap_solve_device
+    rng = np.random.default_rng(batch)
+    sizes = rng.integers(0, 5, size=batch).astype(np.int32)
+    edges = np.array([1, 64, 8, 9, 16, 17, 32, 33, 48, 49, 56, 57, 63, -1, 65], np.int32)
+    at = rng.choice(batch, size=min(batch, 4 * len(edges)), replace=False)
+    sizes[at] = np.resize(edges, len(at))
+    solved = np.where((sizes < 0) | (sizes > 64), 0, sizes).astype(np.int64)
+    mo = np.concatenate([[0], np.cumsum(solved ** 2)[:-1]])
+    vo = np.concatenate([[0], np.cumsum(solved)[:-1]])
+    cost = rng.integers(0, 100, size=int((solved ** 2).sum()) + 1).astype(np.float64)
+    dev, tdt = torch.device("cuda:0"), torch.float64 if dtype == "fp64" else torch.float32
+    value = torch.zeros(batch, dtype=torch.float64, device=dev)
+    assign = torch.zeros(int(solved.sum()) + 1, dtype=torch.int32, device=dev)
+    lap_solve_device(torch.tensor(sizes, device=dev), torch.tensor(mo, device=dev), torch.tensor(vo, device=dev),
+                     torch.tensor(cost, device=dev).to(tdt), value, None, assign, fp32=dtype != "fp64",
+                     nearest=dtype == "fp32n", stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    v, a = value.cpu().numpy(), assign.cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(v), (sizes < 0) | (sizes > 64))
+    for b in np.flatnonzero(~np.isnan(v)):
+        n = int(solved[b])
+        M = cost[mo[b]:mo[b] + n * n].reshape(n, n)
+        r, c = linear_sum_assignment(M)
+        got = a[vo[b]:vo[b] + n]
+        assert v[b] == M[r, c].sum(), (b, n)
+        assert sorted(got) == list(range(n)) and M[np.arange(n), got].sum() == v[b], (b, n)
