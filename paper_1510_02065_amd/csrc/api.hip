@@ -12,6 +12,7 @@
 #include <cstring>
 #include <functional>
 #include <limits>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -90,13 +91,81 @@ qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = fal
     return QAP_OK;
 }
 
-void release(qap_rlt2* h)
+// The D of the handle closed last on each device, kept for the next handle of
+// about its size.  The driver wipes freed device memory at some 57 GB/s and
+// holds later frees back once enough waits for that: a program that opens and
+// closes handles of N = 35 (3.1 GB) every 27 ms waited 60 ms in every close.
+// One block per device, at most 1/16 of its memory, and only while half of
+// the device's memory is free; given back when a handle of another size is
+// made, when any allocation of the library fails, and when a later close
+// finds less than half of the memory free.  A block comes back only after its
+// handle's stream has drained, and its next handle clears it like a new one.
+class BlockCache {
+public:
+    // A kept block for `bytes`, or nullptr; one of another size is freed.
+    void* take(int dev, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        Block b = slot(dev);
+        if (!b.p) return nullptr;
+        slot(dev) = {};
+        if (b.bytes >= bytes && b.bytes - bytes <= bytes / 4) return b.p;
+        (void)hipFree(b.p);
+        return nullptr;
+    }
+    // Keep `p` or free it.
+    void put(int dev, void* p, size_t bytes)
+    {
+        size_t freeb = 0, total = 0;
+        const bool known = hipMemGetInfo(&freeb, &total) == hipSuccess;
+        std::lock_guard<std::mutex> lock(mu_);
+        Block& b = slot(dev);
+        if (b.p) (void)hipFree(b.p);
+        b = {};
+        if (dev >= 0 && dev < kDevices && known && bytes <= total / 16 && freeb >= total / 2)
+            b = {p, bytes};
+        else
+            (void)hipFree(p);
+    }
+    // Free the device's block; whether there was one.
+    bool drop(int dev)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        Block& b = slot(dev);
+        if (!b.p) return false;
+        (void)hipFree(b.p);
+        b = {};
+        return true;
+    }
+
+private:
+    static constexpr int kDevices = 64;
+    struct Block {
+        void* p = nullptr;
+        size_t bytes = 0;
+    };
+    Block& slot(int dev) { return blocks_[dev >= 0 && dev < kDevices ? dev : kDevices]; }
+    std::mutex mu_;
+    Block blocks_[kDevices + 1];   // the last one stays empty
+};
+BlockCache& block_cache()
+{
+    static BlockCache* c = new BlockCache;   // never destroyed: the device may be gone by then
+    return *c;
+}
+
+// `drained`: nothing on the device uses the handle's memory any more.
+void release(qap_rlt2* h, bool drained = false)
 {
     if (!h) return;
     if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
     if (h->graph) (void)hipGraphDestroy(h->graph);
-    for (void* p : {h->arena, h->dD, static_cast<void*>(h->dCt), static_cast<void*>(h->dBt)})
+    for (void* p : {h->arena, static_cast<void*>(h->dCt), static_cast<void*>(h->dBt)})
         if (p) (void)hipFree(p);
+    if (h->dD && drained)
+        block_cache().put(h->device, h->dD, h->bytesD);
+    else if (h->dD)
+        (void)hipFree(h->dD);
     for (hipEvent_t ev : h->ev_size)
         if (ev) (void)hipEventDestroy(ev);
     if (h->ev_fork) (void)hipEventDestroy(h->ev_fork);
@@ -197,7 +266,7 @@ struct Arena {
             if (p.filled) head = total + p.filled;
             total += (p.bytes + 255) / 256 * 256;
         }
-        hipError_t e = hipMalloc(base, total);
+        hipError_t e = qap::device_malloc(base, total);
         if (e != hipSuccess) return e;
         std::vector<char> image(head);
         for (const Part& p : parts) {
@@ -390,10 +459,16 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     }
 
     const size_t bytesD = (size_t)h->totalD * h->elem;
+    if (h->level == 2) {
+        h->bytesD = std::max<size_t>(bytesD, 1);
+        h->dD = block_cache().take(h->device, h->bytesD);
+    }
     size_t freeb = 0, totalb = 0;
     CK(hipMemGetInfo(&freeb, &totalb));
     const size_t ccbytes = h->level == 2 ? (size_t)h->totalC * h->elem : 0;
-    if (bytesD + ccbytes + (size_t)h->totalC * (h->elem + 8) > freeb)
+    const size_t need = (h->dD ? 0 : bytesD) + ccbytes + (size_t)h->totalC * (h->elem + 8);
+    if (need > freeb && block_cache().drop(h->device)) CK(hipMemGetInfo(&freeb, &totalb));
+    if (need > freeb)
         return bail(fail(QAP_ENOMEM, "reduced-cost arrays do not fit in free device memory"));
 
     const std::vector<int> ones(count, 1);
@@ -445,8 +520,8 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     h->dLB = record + count;
     h->dTrace = record + 3 * (size_t)count;
     CK(hipMemsetAsync(h->dSigma, 0, h->totalB * sizeof(int32_t), h->stream));
-    if (h->level == 2) CK(hipMalloc(&h->dD, std::max<size_t>(bytesD, 1)));
-    if (h->level == 2) CK(hipMemsetAsync(h->dD, 0, std::max<size_t>(bytesD, 1), h->stream));
+    if (h->level == 2 && !h->dD) CK(qap::device_malloc(&h->dD, h->bytesD));
+    if (h->level == 2) CK(hipMemsetAsync(h->dD, 0, h->bytesD, h->stream));
 #undef CK
     *out = h;
     return QAP_OK;
@@ -456,8 +531,7 @@ void destroy_handle(qap_rlt2* h)
 {
     if (!h) return;
     (void)hipSetDevice(h->device);
-    if (h->stream) (void)hipStreamSynchronize(h->stream);
-    release(h);
+    release(h, h->stream && hipStreamSynchronize(h->stream) == hipSuccess && !h->broken);
     delete h;
 }
 
@@ -548,6 +622,13 @@ std::vector<char> snap_header(const qap_rlt2* h)
 }
 
 }  // namespace
+
+bool qap::give_back_kept_memory()
+{
+    int dev = 0;
+    (void)hipGetLastError();   // the failed allocation's
+    return hipGetDevice(&dev) == hipSuccess && block_cache().drop(dev);
+}
 
 extern "C" {
 
@@ -721,8 +802,8 @@ qap_status qap_rlt2_batch_bounds(qap_rlt2* h, double* lb, double* certified)
     if (st != QAP_OK) return st;
     if (certified) {
         hipError_t e = hipSuccess;
-        if (!h->dCt) e = hipMalloc(&h->dCt, h->totalC * sizeof(double));
-        if (e == hipSuccess && !h->dBt) e = hipMalloc(&h->dBt, h->totalB * sizeof(double));
+        if (!h->dCt) e = qap::device_malloc(&h->dCt, h->totalC * sizeof(double));
+        if (e == hipSuccess && !h->dBt) e = qap::device_malloc(&h->dBt, h->totalB * sizeof(double));
         if (e != hipSuccess) return fail(QAP_ENOMEM, std::string("certification buffers: ") + hipGetErrorString(e));
         e = QAP_OPS(h->precision, certify(h));
         if (e != hipSuccess) return mark_broken(h, e, "certification launch");

@@ -90,6 +90,7 @@ struct qap_rlt2 {
     size_t lds_limit = 65536;   // dynamic LDS a workgroup may request
     int num_cu = 256;           // compute units of the device
     size_t elem = 8;   // bytes per reduced cost
+    size_t bytesD = 0;   // of dD's allocation, or less
     double stopK = 0.0, stopUB = 0.0;   // stop rule of Algorithm 1 (UB <= 0: off)
     std::vector<qap::Inst> inst;
     long long totalB = 0, totalC = 0, totalD = 0, totalWG = 0;
@@ -140,6 +141,19 @@ struct qap_rlt2 {
 };
 
 namespace qap {
+
+// Free the memory kept on the current device for later handles (after a failed
+// allocation); whether there was any.
+bool give_back_kept_memory();
+
+// hipMalloc, tried again without the kept memory when it fails for space.
+template <typename X>
+hipError_t device_malloc(X** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && give_back_kept_memory()) e = hipMalloc(p, bytes);
+    return e;
+}
 
 // Launch code of one precision mode (ops_impl.hpp, instantiated in
 // ops_f64.hip, ops_f32d.hip and ops_f32n.hip).

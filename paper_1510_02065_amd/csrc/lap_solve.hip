@@ -239,6 +239,8 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
         // the call stays asynchronous and calls on other streams get their own.
         void* ws = nullptr;
         hipError_t e = batch > qap::kUnsorted ? hipMallocAsync(&ws, qap::sort_bytes(batch), st) : hipSuccess;
+        if (e == hipErrorOutOfMemory && qap::give_back_kept_memory())
+            e = hipMallocAsync(&ws, qap::sort_bytes(batch), st);
         if (e != hipSuccess)
             return fail(e == hipErrorOutOfMemory ? QAP_ENOMEM : QAP_EDEVICE,
                         std::string("hipMallocAsync: ") + hipGetErrorString(e));
@@ -289,21 +291,21 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
             return result;                                                                           \
         }                                                                                            \
     } while (0)
-    CK2(hipMalloc(&dn, batch * sizeof(int32_t)));
-    CK2(hipMalloc(&didx, batch * sizeof(int32_t)));
-    CK2(hipMalloc(&dmo, batch * sizeof(int64_t)));
-    CK2(hipMalloc(&dcost, std::max<int64_t>(mat_end, 1) * es));
-    CK2(hipMalloc(&dval, batch * sizeof(double)));
+    CK2(qap::device_malloc(&dn, batch * sizeof(int32_t)));
+    CK2(qap::device_malloc(&didx, batch * sizeof(int32_t)));
+    CK2(qap::device_malloc(&dmo, batch * sizeof(int64_t)));
+    CK2(qap::device_malloc(&dcost, std::max<int64_t>(mat_end, 1) * es));
+    CK2(qap::device_malloc(&dval, batch * sizeof(double)));
     CK2(hipMemcpyAsync(dn, n, batch * sizeof(int32_t), hipMemcpyHostToDevice, st));
     CK2(hipMemcpyAsync(didx, idx.data(), batch * sizeof(int32_t), hipMemcpyHostToDevice, st));
     CK2(hipMemcpyAsync(dmo, mat_off, batch * sizeof(int64_t), hipMemcpyHostToDevice, st));
     if (mat_end > 0) CK2(hipMemcpyAsync(dcost, cost, mat_end * es, hipMemcpyHostToDevice, st));
     if (vec_off) {
-        CK2(hipMalloc(&dvo, batch * sizeof(int64_t)));
+        CK2(qap::device_malloc(&dvo, batch * sizeof(int64_t)));
         CK2(hipMemcpyAsync(dvo, vec_off, batch * sizeof(int64_t), hipMemcpyHostToDevice, st));
     }
-    if (duals) CK2(hipMalloc(&ddual, std::max<int64_t>(4 * vec_end, 1) * es));
-    if (assign) CK2(hipMalloc(&dassign, std::max<int64_t>(vec_end, 1) * sizeof(int32_t)));
+    if (duals) CK2(qap::device_malloc(&ddual, std::max<int64_t>(4 * vec_end, 1) * es));
+    if (assign) CK2(qap::device_malloc(&dassign, std::max<int64_t>(vec_end, 1) * sizeof(int32_t)));
     // One launch per size class.
     const qap::Classes cl = qap::classes_for(batch, dtype);
     int first = 0;

@@ -268,3 +268,42 @@ def test_certify_finds_every_blocks_minimum(N, precision):
         g.load_state(0, 0.0, B, C, X.ravel())
         assert g.certify() == pytest.approx(_host_cascade(N, 0.0, B, C, X.ravel()), rel=1e-12)
     g.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_handles_after_a_closed_one_start_clean(precision):
+    # A new handle may get the memory of one closed before it: of its own size,
+    # a little larger, or another precision's.  Its results are those of the
+    # first handle of the process, also with handles open side by side and from
+    # several threads.
+    import threading
+    F, D = qapgen.small(12, 3)
+    F11, D11 = qapgen.small(11, 4)
+
+    def run(f, d, prec=precision):
+        with Rlt2(f, d, precision=prec) as g:
+            g.ascend(3)
+            return (g.trace()[0], *g.read_state()[1:])
+
+    first, other = run(F, D), run(F11, D11)
+    run(F, D, "fp32n" if precision == "fp64" else "fp64")
+    with Rlt2(F, D, precision=precision) as g:
+        g.ascend(2)
+        again, other2 = run(F, D), run(F11, D11)
+        g.ascend(1)
+        beside = (g.trace()[0], *g.read_state()[1:])
+    from_threads = [None] * 4
+
+    def work(i):
+        for _ in range(5):
+            from_threads[i] = run(F, D) if i % 2 else run(F11, D11)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for got, want in [(again, first), (other2, other), (beside, first), (from_threads[0], other),
+                      (from_threads[1], first), (from_threads[2], other), (from_threads[3], first)]:
+        for x, y in zip(got, want):
+            np.testing.assert_array_equal(x, y)
