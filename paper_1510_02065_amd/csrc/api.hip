@@ -46,15 +46,17 @@ constexpr int kOverlapMinN = 16;
 hipError_t enqueue_iteration(qap_rlt2* h)
 {
     hipError_t e = hipSuccess;
-    if (h->overlap) {
+    if (h->level == 1) {
+        e = QAP_OPS(h->precision, enqueue_spread_transfer(h));
+    } else if (h->overlap) {
         e = QAP_OPS(h->precision, enqueue_sweep_concentrate_overlapped(h));
     } else {
         for (int s : {3, 4})
             if (e == hipSuccess) e = enqueue_step_any(h, s);
     }
-    const bool pairs_equal = h->level == 2 && h->dmode == qap::kHalfStore;
-    for (int s : {5, 6, 7})
-        if (e == hipSuccess && !(s == 5 && pairs_equal)) e = enqueue_step_any(h, s);
+    if (e == hipSuccess && h->level == 2 && h->dmode == qap::kAllBlocks) e = enqueue_step_any(h, 5);
+    for (int s : {6, 7})
+        if (e == hipSuccess) e = enqueue_step_any(h, s);
     return e;
 }
 
@@ -378,6 +380,8 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
         h->preB.push_back(h->totalB);
         h->preC.push_back(h->totalC);
         h->preWG.push_back(h->totalWG);
+        h->preP.push_back(h->totalP);
+        h->totalP += N * n1 / 2;
         h->preCert.push_back(h->totalCert);
         h->totalCert += (long long)(N * n1 / 2) * qap::cert_stretches(N);
         const long long nC = (long long)N * N * n1 * n1;
@@ -484,6 +488,7 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     ar.add(&h->dPreC, h->preC);
     ar.add(&h->dPreWG, h->preWG);
     ar.add(&h->dPreCert, h->preCert);
+    ar.add(&h->dPreP, h->preP);
     ar.add(&h->dAct, ones);
     ar.add(&h->dStop, 2, stop, 2);
     for (auto& c : h->sweep_cls) {
@@ -521,7 +526,9 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     h->dTrace = record + 3 * (size_t)count;
     CK(hipMemsetAsync(h->dSigma, 0, h->totalB * sizeof(int32_t), h->stream));
     if (h->level == 2 && !h->dD) CK(qap::device_malloc(&h->dD, h->bytesD));
-    if (h->level == 2) CK(hipMemsetAsync(h->dD, 0, h->bytesD, h->stream));
+    // The children of a handle with paired blocks get all of D from it.
+    const bool inherited = !in.fix.empty() && h->dmode == qap::kHalfStore;
+    if (h->level == 2 && !inherited) CK(hipMemsetAsync(h->dD, 0, h->bytesD, h->stream));
 #undef CK
     *out = h;
     return QAP_OK;

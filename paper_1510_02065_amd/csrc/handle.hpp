@@ -95,6 +95,8 @@ struct qap_rlt2 {
     std::vector<qap::Inst> inst;
     long long totalB = 0, totalC = 0, totalD = 0, totalWG = 0;
     std::vector<long long> preB, preC, preWG;
+    std::vector<long long> preP;      // first facility pair of each instance
+    long long totalP = 0;
     std::vector<long long> preCert;   // first k_cert_pairs workgroup of each instance
     long long totalCert = 0;
     qap::ClassHost fam[3][4];   // [D, C, B][segment class]
@@ -111,7 +113,7 @@ struct qap_rlt2 {
     std::vector<int> tri;                     // facility triples of every instance
     void* arena = nullptr;   // every device array below but D, dCt and dBt
     qap::Inst* dInst = nullptr;
-    long long *dPreB = nullptr, *dPreC = nullptr, *dPreWG = nullptr, *dPreCert = nullptr;
+    long long *dPreB = nullptr, *dPreC = nullptr, *dPreWG = nullptr, *dPreCert = nullptr, *dPreP = nullptr;
     void* dB = nullptr;
     void* dC = nullptr;
     void* dD = nullptr;
@@ -162,6 +164,8 @@ struct Ops {
     // One step of an iteration: 3 (steps 1-3, or step 1 at level 1), 4, 5,
     // 6, 7 (steps 7-8).
     static hipError_t enqueue_step(qap_rlt2* h, int step);
+    // Steps 1 and 5 of a level-1 iteration (3 and 5 of enqueue_step).
+    static hipError_t enqueue_spread_transfer(qap_rlt2* h);
     // FP64 certification cascade into h->dCert.
     static hipError_t certify(qap_rlt2* h);
     // Initial dual of instance k from device copies of F, D and B0 (nullable).

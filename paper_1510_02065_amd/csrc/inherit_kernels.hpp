@@ -80,21 +80,20 @@ __global__ __launch_bounds__(256) void k_child_B(ChildSrc<StoreT<PM>> src, Store
     }
 }
 
-// One thread per child C entry: c'_{ij kn}.
+// One thread per child C entry: c'_{ij kn}; `blocks` workgroups per child.
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_C(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ C,
-                                                 const Inst* __restrict__ inst, int K)
+                                                 const Inst* __restrict__ inst, unsigned blocks)
 {
     const int M = src.N - 1, m1 = M - 1;
-    const long long per = (long long)M * M * m1 * m1;
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= (long long)K * per) return;
-    const int c = (int)(x / per);
-    const long long e = x - (long long)c * per;
+    const int c = (int)(blockIdx.x / blocks);
+    const int e = (int)(blockIdx.x % blocks) * 256 + (int)threadIdx.x;
+    if (e >= M * M * m1 * m1) return;
     const int a = src.fix[2 * c], b = src.fix[2 * c + 1];
-    const int ij = (int)(e / (m1 * m1)), rem = (int)(e % (m1 * m1));
-    const int ic = ij / M, jc = ij % M;
-    const int kc = skip1(rem / m1, ic), nc = skip1(rem % m1, jc);   // child indices
+    const int ij = quotient24(e, m1 * m1), rem = e - ij * (m1 * m1);
+    const int ic = quotient24(ij, M), jc = ij - ic * M;
+    const int kr = quotient24(rem, m1);
+    const int kc = skip1(kr, ic), nc = skip1(rem - kr * m1, jc);   // child indices
     const int i = skip1(ic, a), j = skip1(jc, b), k = skip1(kc, a), n = skip1(nc, b);
     const int N = src.N;
     const double v0 = (double)src.C[beta_of(N, i, j, k, n)];
@@ -111,11 +110,11 @@ __global__ __launch_bounds__(256) void k_child_C(ChildSrc<StoreT<PM>> src, Store
         C[I.offC + e] = (StoreT<PM>)(((v0 + v1) + v2) + v3);
 }
 
-// One thread per stored child D entry (level-2 children of a level-2
-// parent; child storage `cmode`, the parent's): d'_{ij kn pq} = d_{ij kn pq}.
+// D of level-2 children of a parent that stores every block, one thread per
+// stored entry: d'_{ij kn pq} = d_{ij kn pq}.
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_D(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ D,
-                                                 const Inst* __restrict__ inst, int K, long long per, int cmode)
+                                                 const Inst* __restrict__ inst, int K, long long per)
 {
     const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= (long long)K * per) return;
@@ -124,45 +123,55 @@ __global__ __launch_bounds__(256) void k_child_D(ChildSrc<StoreT<PM>> src, Store
     const int a = src.fix[2 * c], b = src.fix[2 * c + 1];
     const int M = src.N - 1, m1 = M - 1, m2 = M - 2;
     const Inst I = inst[c];
-    int ic, jc, kc, nc, pr, qr;   // child block (ic,jc,kc,nc), compact row and column
-    long long off;
-    if (cmode == kAllBlocks) {
-        const long long blk = (long long)m2 * m2;
-        const long long beta = e / I.ldD;
-        const int w = (int)(e - beta * I.ldD);
-        if (w >= blk) return;   // block padding
-        const int ij = (int)(beta / (m1 * m1)), rem = (int)(beta % (m1 * m1));
-        ic = ij / M;
-        jc = ij % M;
-        kc = skip1(rem / m1, ic);
-        nc = skip1(rem % m1, jc);
-        pr = w / m2;
-        qr = w % m2;
-        off = e;
-    } else {
-        // pair-major: ((P(ic,kc) m2 + pr) M m1 + L(jc,nc)) m2 + qr
-        qr = (int)(e % m2);
-        long long r = e / m2;
-        const int L = (int)(r % ((long long)M * m1));
-        r /= (long long)M * m1;
-        pr = (int)(r % m2);
-        int P = (int)(r / m2);
-        int a0 = 0;
-        while (P >= m1 - a0) {
-            P -= m1 - a0;
-            ++a0;
-        }
-        ic = a0;
-        kc = a0 + 1 + P;
-        jc = L / m1;
-        nc = skip1(L % m1, jc);
-        off = e;
-    }
+    const long long blk = (long long)m2 * m2;
+    const long long beta = e / I.ldD;
+    const int w = (int)(e - beta * I.ldD);
+    if (w >= blk) return;   // block padding
+    const int ij = (int)(beta / (m1 * m1)), rem = (int)(beta % (m1 * m1));
+    const int ic = ij / M, jc = ij % M;
+    const int kc = skip1(rem / m1, ic), nc = skip1(rem % m1, jc);   // child block, compact row and column
+    const int pr = w / m2, qr = w % m2;
     const int pc = skip2(pr, min(ic, kc), max(ic, kc));
     const int qc = skip2(qr, min(jc, nc), max(jc, nc));
     const int i = skip1(ic, a), j = skip1(jc, b), k = skip1(kc, a), n = skip1(nc, b);
     const int p = skip1(pc, a), q = skip1(qc, b);
-    D[I.offD + off] = src.D[d_entry(src.N, src.mode, src.ldD, i, j, k, n, p, q)];
+    D[I.offD + e] = src.D[d_entry(src.N, src.mode, src.ldD, i, j, k, n, p, q)];
+}
+
+// The same with one block stored per complementary pair: one workgroup per
+// run of a child, row pr of the facility pair (ic, kc) for all locations, which
+// comes from one run of the parent.  The facilities are scalar work, the
+// entries of both runs go in order, and the offsets within a run are 24-bit
+// products.  Bound by memory.  (With a thread per entry of D and 64-bit
+// divisions for its indices the 18 children of an N = 18 node took 863 us for
+// their 1.2 GB; now 407.)  The first workgroup of a child clears the entries
+// up to the next child's start.
+template <int PM>
+__global__ __launch_bounds__(256) void k_child_runs(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ D,
+                                                    const Inst* __restrict__ inst, unsigned runs, int pad)
+{
+    using T = StoreT<PM>;
+    const unsigned wg = (unsigned)xcd_major(blockIdx.x, gridDim.x);
+    const int c = (int)(wg / runs), r = (int)(wg % runs);
+    const int a = src.fix[2 * c], b = src.fix[2 * c + 1];
+    const int N = src.N, n1 = N - 1, n2 = N - 2, M = N - 1, m1 = M - 1, m2 = M - 2;
+    const int P = r / m2, pr = r - P * m2;
+    int ic, kc;
+    facility_pair(M, P, &ic, &kc);
+    const int i = skip1(ic, a), k = skip1(kc, a), p = skip1(skip2(pr, ic, kc), a);
+    const int run = M * m1 * m2;
+    T* __restrict__ const to = D + inst[c].offD + (long long)r * run;
+    const T* __restrict__ const from =
+        src.D + (pair_index(N, i, k) * n2 + drop2(p, i, k)) * (long long)(N * n1 * n2);
+    if (r == 0 && (int)threadIdx.x < pad) to[(long long)runs * run + threadIdx.x] = (T)0;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < run; e += 256) {
+        const int L = quotient24(e, m2), qr = e - __mul24(L, m2);
+        const int jc = quotient24(L, m1), nc = skip1(L - __mul24(jc, m1), jc);
+        const int qc = skip2(qr, min(jc, nc), max(jc, nc));
+        const int j = skip1(jc, b), n = skip1(nc, b), q = skip1(qc, b);
+        to[e] = from[__mul24(__mul24(j, n1) + n - (n > j), n2) + q - (q > j) - (q > n)];
+    }
 }
 
 // Level-1 certification: no D, so c~ = c.

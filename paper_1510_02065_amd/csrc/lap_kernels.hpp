@@ -60,19 +60,6 @@ __device__ __forceinline__ void stage_block(T* __restrict__ M, int ldm, const Ro
     }
 }
 
-// XCD-aware order of the assignment workgroups.  The hardware hands
-// workgroup b to XCD b mod 8, and each XCD has its own L2; consecutive
-// problems' block rows are adjacent in memory (they share the 128-byte lines
-// at their ends), so each XCD takes one contiguous range of the workgroups'
-// problems: workgroup b runs position xcd_major(b) of the problem order,
-// ranges of q or q + 1 positions (q = grid / 8, the first grid % 8 XCDs
-// taking one more).  A bijection of [0, grid).
-__device__ __forceinline__ long long xcd_major(long long b, long long grid)
-{
-    const long long q = grid >> 3, r = grid & 7, x = b & 7;
-    return x * q + (x < r ? x : r) + (b >> 3);
-}
-
 // Stage one problem per segment and solve it (the residual written over the
 // block where `active`); S to every lane.  UNI: the size is a scalar, as when
 // every problem of the wave belongs to one instance, so that loop counts,

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kSortHeader) void k_sort_clear(int32_t* __restrict_
 // clear, one launch); larger batches count in one launch (PASS 1) and write
 // the list in a second one (PASS 2), with one global atomic per size and
 // workgroup in each.  20000 problems took 16.5 us when every wave reserved its
-// places class by class, and SORT_NOW in both passes now.  The order among
+// places class by class, and 13 in both passes now.  The order among
 // problems of one size is not fixed; each problem's result depends only on its
 // own matrix and the segment width, so it does not matter.
 constexpr int kSortThreads = 1024, kSortEach = 4, kSortOne = kSortThreads * kSortEach;

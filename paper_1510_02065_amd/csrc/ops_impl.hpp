@@ -225,6 +225,31 @@ int Ops<PM>::sweep_tiles(int N)
     return box_tiles<StoreT<PM>>(N);
 }
 
+template <int PM, bool SPREAD>
+hipError_t launch_transfer_C(qap_rlt2* h)
+{
+    using T = StoreT<PM>;
+    hipLaunchKernelGGL((k_transfer_C<PM, SPREAD>), dim3((unsigned)h->totalP), dim3(256), 0, h->stream,
+                       static_cast<T*>(h->dC), static_cast<const T*>(h->dB), h->dInst, h->dPreP, h->K, h->dAct);
+    return hipGetLastError();
+}
+
+template <int PM>
+hipError_t launch_clear_B(qap_rlt2* h)
+{
+    hipLaunchKernelGGL((k_clear_B<PM>), dim3(grid_for(h->totalB, 256)), dim3(256), 0, h->stream,
+                       static_cast<StoreT<PM>*>(h->dB), h->dPreB, h->K, h->totalB, h->dAct);
+    return hipGetLastError();
+}
+
+// Steps 1 and 5 of a level-1 iteration in one pass over C.
+template <int PM>
+hipError_t Ops<PM>::enqueue_spread_transfer(qap_rlt2* h)
+{
+    const hipError_t e = launch_transfer_C<PM, true>(h);
+    return e == hipSuccess ? launch_clear_B<PM>(h) : e;
+}
+
 template <int PM>
 hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
 {
@@ -241,10 +266,7 @@ hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
             hipLaunchKernelGGL((k_spread_B<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st, C, B, h->dInst,
                                h->dPreC, h->K, h->totalC, h->dAct);
             hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_clear_B<PM>), dim3(grid_for(h->totalB, 256)), dim3(256), 0, st, B, h->dPreB, h->K,
-                               h->totalB, h->dAct);
-            return hipGetLastError();
+            return e == hipSuccess ? launch_clear_B<PM>(h) : e;
         }
         hipLaunchKernelGGL((k_spread_prep<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st, C, B, CC,
                            h->dInst, h->dPreC, h->K, h->totalC, h->dAct);
@@ -265,9 +287,7 @@ hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
         if (h->level == 1) return hipSuccess;
         return launch_family<PM>(h, kFamD, vals ? h->dValD : nullptr);
     case 5:
-        hipLaunchKernelGGL((k_transfer_C<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st, C, h->dInst,
-                           h->dPreC, h->K, h->totalC, h->dAct);
-        return hipGetLastError();
+        return launch_transfer_C<PM, false>(h);
     case 6:
         return launch_family<PM>(h, kFamC, vals ? h->dValC : nullptr);
     case 7:
@@ -384,16 +404,24 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const long long perC = (long long)M * M * (M - 1) * (M - 1);
-    hipLaunchKernelGGL((k_child_C<PM>), dim3(grid_for(K * perC, 256)), dim3(256), 0, st, src,
-                       static_cast<T*>(ch->dC), ch->dInst, K);
+    const unsigned blocksC = grid_for(perC, 256);
+    hipLaunchKernelGGL((k_child_C<PM>), dim3((unsigned)K * blocksC), dim3(256), 0, st, src, static_cast<T*>(ch->dC),
+                       ch->dInst, blocksC);
     e = hipGetLastError();
     if (e != hipSuccess || ch->level == 1) return e;
     const Inst& I0 = ch->inst[0];
-    const long long perD = ch->dmode == kAllBlocks ? perC * I0.ldD : (perC / 2) * (M - 2) * (M - 2);
-    // Children of one size are packed with 128-byte aligned starts; the kernel
-    // indexes each child's entries from its own offD.
-    hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src,
-                       static_cast<T*>(ch->dD), ch->dInst, K, perD, ch->dmode);
+    T* D = static_cast<T*>(ch->dD);
+    // Children of one size are packed with 128-byte aligned starts; the kernels
+    // index each child's entries from its own offD.
+    if (ch->dmode == kAllBlocks) {
+        const long long perD = perC * I0.ldD;
+        hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src, D, ch->dInst, K, perD);
+    } else {
+        const unsigned runs = (unsigned)(M * (M - 1) / 2 * (M - 2));
+        const long long perD = (perC / 2) * (M - 2) * (M - 2);
+        hipLaunchKernelGGL((k_child_runs<PM>), dim3((unsigned)K * runs), dim3(256), 0, st, src, D, ch->dInst, runs,
+                           (int)(ch->totalD / K - perD));
+    }
     return hipGetLastError();
 }
 

@@ -247,16 +247,33 @@ __host__ __device__ __forceinline__ int quotient24(int x, int d)
 #endif
     return q + (r >= d) - (r < 0);
 }
+__host__ __device__ __forceinline__ int product24(int x, int y)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __mul24(x, y);
+#else
+    return x * y;
+#endif
+}
+__host__ __device__ __forceinline__ void facility_pair(int N, int P, int* a, int* b)
+{
+    const float tw = (float)(2 * N - 1);
+    const float q = tw * tw - 8.0f * (float)P;
+#ifdef __HIP_DEVICE_COMPILE__
+    const float root = __builtin_amdgcn_sqrtf(q);
+#else
+    const float root = sqrtf(q);
+#endif
+    int x = (int)((tw - root) * 0.5f);
+    auto S = [&](int y) { return product24(y, 2 * N - 1 - y) >> 1; };
+    x += (S(x + 1) <= P) - (S(x) > P);
+    *a = x;
+    *b = x + 1 + (P - S(x));
+}
 __host__ __device__ __forceinline__ void pair_block(int N, long long h, long long* beta, long long* twin,
                                                     long long* base)
 {
-#ifdef __HIP_DEVICE_COMPILE__
-    auto mul = [](int x, int y) { return __mul24(x, y); };
-    auto root = [](float x) { return __builtin_amdgcn_sqrtf(x); };
-#else
-    auto mul = [](int x, int y) { return x * y; };
-    auto root = [](float x) { return sqrtf(x); };
-#endif
+    auto mul = [](int x, int y) { return product24(x, y); };
     const int n1 = N - 1;
     const int NL = mul(N, n1);
     const int hh = (int)h;
@@ -265,11 +282,8 @@ __host__ __device__ __forceinline__ void pair_block(int N, long long h, long lon
     // 32-bit products up to the last multiplication (block numbers are below
     // N^2 (N-1)^2 < 2^24); the first-row offset needs 64 bits.
     *base = (long long)(((unsigned long long)(unsigned)mul(P, N - 2) * (unsigned)NL + (unsigned)L) * (unsigned)(N - 2));
-    const float tw = (float)(2 * N - 1);
-    int a = (int)((tw - root(tw * tw - 8.0f * (float)P)) * 0.5f);
-    auto S = [&](int x) { return mul(x, 2 * N - 1 - x) >> 1; };
-    a += (S(a + 1) <= P) - (S(a) > P);
-    const int b = a + 1 + (P - S(a));
+    int a, b;
+    facility_pair(N, P, &a, &b);
     const int la = quotient24(L, n1);
     const int lq = L - mul(la, n1);
     const int lb = lq + (lq >= la);
@@ -313,6 +327,27 @@ __device__ __forceinline__ int find_seg(const long long* __restrict__ pre, int K
             hi = mid - 1;
     }
     return lo;
+}
+
+// find_seg of x by way of a workgroup's first x0 (scalar work): the segment is
+// x0's or one of the next.
+__device__ __forceinline__ int find_seg_from(const long long* __restrict__ pre, int K, long long x0, long long x) {
+    int k = find_seg(pre, K, x0);
+    while (k + 1 < K && pre[k + 1] <= x) ++k;
+    return k;
+}
+
+// XCD-aware order of workgroups.  The hardware hands
+// workgroup b to XCD b mod 8, and each XCD has its own L2; consecutive
+// problems' block rows are adjacent in memory (they share the 128-byte lines
+// at their ends), so each XCD takes one contiguous range of the workgroups'
+// problems: workgroup b runs position xcd_major(b) of the problem order,
+// ranges of q or q + 1 positions (q = grid / 8, the first grid % 8 XCDs
+// taking one more).  A bijection of [0, grid).
+__device__ __forceinline__ long long xcd_major(long long b, long long grid)
+{
+    const long long q = grid >> 3, r = grid & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
 }
 
 // Initial dual of one instance (the lines of Algorithm 1 before its loop):
@@ -360,13 +395,13 @@ __global__ __launch_bounds__(256) void k_spread_prep(StoreT<PM>* __restrict__ C,
                                                      long long totalC, const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
     if (x >= totalC) return;
-    const int kk = find_seg(preC, K, x);
+    const int kk = find_seg_from(preC, K, (long long)blockIdx.x * 256, x);
     if (!act[kk]) return;
     const Inst I = inst[kk];
     const int N = I.N, n1 = N - 1;
-    const int ij = (int)((x - I.offC) / (n1 * n1));
+    const int ij = quotient24((int)(x - I.offC), n1 * n1);
     const T bij = B[I.offB + ij];
     if constexpr (PM == kPrecF32Down) {
         const double c = add_down((double)C[x], div_down((double)bij, (double)(N - 1)));
@@ -379,6 +414,16 @@ __global__ __launch_bounds__(256) void k_spread_prep(StoreT<PM>* __restrict__ C,
     C[x] = (T)0;
 }
 
+// c + b / (N-1) as written into the state.
+template <int PM, typename T = StoreT<PM>>
+__device__ __forceinline__ T spread_b(T c, T b, int N)
+{
+    if constexpr (PM == kPrecF32Down)
+        return to_float_down(add_down((double)c, div_down((double)b, (double)(N - 1))));
+    else
+        return (T)((double)c + (double)b / (double)(N - 1));
+}
+
 // Step 1 alone (the level-1 dual ascent, which has no D): c += b_ij / (N-1)
 // over every C entry of the active instances.  B is cleared by k_clear_B.
 template <int PM>
@@ -387,18 +432,15 @@ __global__ __launch_bounds__(256) void k_spread_B(StoreT<PM>* __restrict__ C, co
                                                   int K, long long totalC, const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
     if (x >= totalC) return;
-    const int kk = find_seg(preC, K, x);
+    const int kk = find_seg_from(preC, K, (long long)blockIdx.x * 256, x);
     if (!act[kk]) return;
     const Inst I = inst[kk];
     const int N = I.N, n1 = N - 1;
-    const int ij = (int)((x - I.offC) / (n1 * n1));
+    const int ij = quotient24((int)(x - I.offC), n1 * n1);
     const T bij = B[I.offB + ij];
-    if constexpr (PM == kPrecF32Down)
-        C[x] = to_float_down(add_down((double)C[x], div_down((double)bij, (double)(N - 1))));
-    else
-        C[x] = (T)((double)C[x] + (double)bij / (double)(N - 1));
+    C[x] = spread_b<PM>(C[x], bij, N);
 }
 
 // b = 0 over the active instances (after step 1 of the level-1 ascent).
@@ -406,9 +448,9 @@ template <int PM>
 __global__ __launch_bounds__(256) void k_clear_B(StoreT<PM>* __restrict__ B, const long long* __restrict__ preB,
                                                  int K, long long totalB, const int* __restrict__ act)
 {
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
     if (x >= totalB) return;
-    if (act[find_seg(preB, K, x)]) B[x] = (StoreT<PM>)0;
+    if (act[find_seg_from(preB, K, (long long)blockIdx.x * 256, x)]) B[x] = (StoreT<PM>)0;
 }
 
 // The sweep kernels clear instance I's B (N^2 entries) from the workgroup
@@ -1206,33 +1248,48 @@ __global__ __launch_bounds__(kTripleThreads) void k_sweep_triple_p(StoreT<PM>* _
 }
 
 // Step 5: the complementary pair c_ijkn, c_knij (equation (10)) both become
-// their mean.  One thread per C entry; the thread with i < k does the pair.
-template <int PM>
-__global__ __launch_bounds__(256) void k_transfer_C(StoreT<PM>* __restrict__ C, const Inst* __restrict__ inst,
-                                                    const long long* __restrict__ preC, int K, long long totalC,
+// their mean; with SPREAD, step 1 (k_spread_B's) on the way, so that a level-1
+// iteration passes over C once instead of twice.  One workgroup per facility
+// pair i < k of an instance: the entries c_knij that its lanes touch, a
+// column each of N rows of n1 entries, lie in as many lines as the L1 holds,
+// and consecutive pairs, which share the lines at their runs' ends, run on one
+// XCD.  Bound by memory.  (With a thread per entry of C, half of them idle, a
+// 64-bit division and a search for the instance each, 196 children of N = 13
+// took 58 us, and 38 for step 1 before it; both take 26 us here.)
+template <int PM, bool SPREAD>
+__global__ __launch_bounds__(256) void k_transfer_C(StoreT<PM>* __restrict__ C, const StoreT<PM>* __restrict__ B,
+                                                    const Inst* __restrict__ inst,
+                                                    const long long* __restrict__ preP, int K,
                                                     const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= totalC) return;
-    const int kk = find_seg(preC, K, x);
+    const long long wg = xcd_major(blockIdx.x, gridDim.x);
+    const int kk = find_seg(preP, K, wg);
     if (!act[kk]) return;
     const Inst I = inst[kk];
-    const int N = I.N, n1 = N - 1;
-    const long long lx = x - I.offC;
-    const int ij = (int)(lx / (n1 * n1));
-    const int rem = (int)(lx % (n1 * n1));
-    const int i = ij / N, j = ij % N;
-    const int k = skip1(rem / n1, i), n = skip1(rem % n1, j);
-    if (i >= k) return;
-    const long long y = I.offC + beta_of(N, k, n, i, j);
-    T mean;
-    if constexpr (PM == kPrecF32Down)
-        mean = to_float_down(div_down(add_down((double)C[x], (double)C[y]), 2.0));
-    else
-        mean = (T)(((double)C[x] + (double)C[y]) / 2.0);
-    C[x] = mean;
-    C[y] = mean;
+    const int N = I.N, n1 = N - 1, P = (int)(wg - preP[kk]);
+    int i, k;
+    facility_pair(N, P, &i, &k);
+    T* __restrict__ const Ck = C + I.offC;
+    const T* __restrict__ const Bk = B + I.offB;
+    for (int e = threadIdx.x; e < N * n1; e += 256) {
+        const int j = quotient24(e, n1), nn = e - j * n1;
+        const int n = skip1(nn, j);
+        const int x = ((i * N + j) * n1 + (k - 1)) * n1 + nn;
+        const int y = ((k * N + n) * n1 + i) * n1 + (j - (j > n));
+        T cx = Ck[x], cy = Ck[y];
+        if constexpr (SPREAD) {
+            cx = spread_b<PM>(cx, Bk[i * N + j], N);
+            cy = spread_b<PM>(cy, Bk[k * N + n], N);
+        }
+        T mean;
+        if constexpr (PM == kPrecF32Down)
+            mean = to_float_down(div_down(add_down((double)cx, (double)cy), 2.0));
+        else
+            mean = (T)(((double)cx + (double)cy) / 2.0);
+        Ck[x] = mean;
+        Ck[y] = mean;
+    }
 }
 
 // ---- FP64 certification cascade (every rounding toward -inf) ----------------

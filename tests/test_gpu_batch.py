@@ -152,3 +152,24 @@ def test_overlapped_schedule_equals_sequential_bitwise(precision, use_graph):
             np.testing.assert_array_equal(x, y)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32n"])
+def test_level1_iterations_equal_their_steps_bitwise(precision):
+    # A level-1 ascend spreads B and averages the pairs of C in one pass, the
+    # single steps in two.  Pairs of fewer and of more entries than a workgroup
+    # has threads (N (N-1) around 256), and the smallest instance.
+    inst = [qapgen.small(n, n) for n in (3, 4, 16, 17, 7, 24)]
+    print(f"level 1, {precision}, N =", [len(f) for f, _ in inst], flush=True)
+    a = Rlt2.batch([f for f, _ in inst], [d for _, d in inst], precision=precision, level=1)
+    b = Rlt2.batch([f for f, _ in inst], [d for _, d in inst], precision=precision, level=1)
+    a.ascend(3)
+    for _ in range(3):
+        for s in (3, 5, 6, 7):
+            b.step(s)
+    np.testing.assert_array_equal(a.bounds(), b.bounds())
+    for k in range(len(inst)):
+        for x, y in zip(a.read_state_k(k, want_D=False)[1:3], b.read_state_k(k, want_D=False)[1:3]):
+            np.testing.assert_array_equal(x, y)
+    a.close()
+    b.close()
