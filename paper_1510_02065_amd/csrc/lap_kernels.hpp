@@ -32,31 +32,35 @@ enum DStorage : int {
 // Copy an n x n block (rows `rows` in global memory) into LDS (row stride
 // ldm).  Each lane issues the loads of a whole chunk of rows before it writes
 // any of them, so a wave waits for HBM once per chunk instead of once per row:
-// the first kStageRows rows (all of them up to n = 24) in straight-line code,
-// the rest kStageTail at a time.  Rows past the end re-read row n-1 and write
+// the first 24 rows (16 and 8 for the segments of that width, which hold no
+// more; with 24 in all of them N = 18 took 83.2 us for step 4, now 81.4) in
+// straight-line code, the rest kStageTail at a time.  Rows past the end re-read row n-1 and write
 // it again (the same value to the same place), so no write is guarded.  Row
 // offsets in LDS are 24-bit products; those in global memory stay below 2^32
 // bytes (a row stride is at most N (N-1) (N-2) < 2^18 entries for N <= 64).
-constexpr int kStageRows = 24;
+template <int SEG>
+constexpr int kStageRows = SEG < 24 ? SEG : 24;
 constexpr int kStageTail = 8;
 
-template <typename T, typename Rows>
+template <typename T, int SEG, typename Rows>
 __device__ __forceinline__ void stage_block(T* __restrict__ M, int ldm, const Rows& rows, int n, int c)
 {
     if (c >= n) return;
     {
-        T t[kStageRows];
+        T t[kStageRows<SEG>];
 #pragma unroll
-        for (int u = 0; u < kStageRows; ++u) t[u] = rows.at(min(u, n - 1));
+        for (int u = 0; u < kStageRows<SEG>; ++u) t[u] = rows.at(min(u, n - 1));
 #pragma unroll
-        for (int u = 0; u < kStageRows; ++u) M[__umul24((unsigned)min(u, n - 1), (unsigned)ldm) + c] = t[u];
+        for (int u = 0; u < kStageRows<SEG>; ++u) M[__umul24((unsigned)min(u, n - 1), (unsigned)ldm) + c] = t[u];
     }
-    for (int r0 = kStageRows; r0 < n; r0 += kStageTail) {
-        T t[kStageTail];
+    if constexpr (SEG > kStageRows<SEG>) {
+        for (int r0 = kStageRows<SEG>; r0 < n; r0 += kStageTail) {
+            T t[kStageTail];
 #pragma unroll
-        for (int u = 0; u < kStageTail; ++u) t[u] = rows.at(min(r0 + u, n - 1));
+            for (int u = 0; u < kStageTail; ++u) t[u] = rows.at(min(r0 + u, n - 1));
 #pragma unroll
-        for (int u = 0; u < kStageTail; ++u) M[__umul24((unsigned)min(r0 + u, n - 1), (unsigned)ldm) + c] = t[u];
+            for (int u = 0; u < kStageTail; ++u) M[__umul24((unsigned)min(r0 + u, n - 1), (unsigned)ldm) + c] = t[u];
+        }
     }
 }
 
@@ -71,7 +75,7 @@ __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, 
                                                   const Rows& rows, bool active, int32_t* assign = nullptr)
 {
     const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(nmax), n);
-    stage_block(sc.M, sc.ld, rows, n, lane);
+    stage_block<T, SEG>(sc.M, sc.ld, rows, n, lane);
     wave_sync();
     T* const no_duals = nullptr;
     if constexpr (AUC)
@@ -97,7 +101,7 @@ __device__ __forceinline__ double stage_and_solve(unsigned char* smem, int seg, 
 // next (every wave of a single instance but the last, all but one wave per
 // instance of a batch): such a wave finds its instance, its rows' addresses
 // and its loop counts with scalar instructions (N = 25 FP32 468 -> 448 us, N =
-// 33 2720 -> 2612; a batch of 160 nodes of N = 17..22 52.3 -> 50.2 ms).
+// 33 2720 -> 2612; a batch of 160 nodes of N = 10..22 52.3 -> 50.2 ms).
 template <int PM, int SEG, int FAM, bool AUC = false>
 __global__ __launch_bounds__(64, PM != kPrecF64 ? 7 : (SEG <= 32 ? 6 : 1))
 void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, StoreT<PM>* __restrict__ B,
@@ -146,8 +150,9 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
     const int id0 = fc.cls[k0];
     const long long end0 = k0 + 1 < fc.Kc ? fc.pre[k0 + 1] : fc.total;
     if (x0 + LPW <= end0) {
-        // Every problem of the wave belongs to instance id0; its blocks lie at growing offsets, less than 2^32 bytes
-        // apart (a facility pair's stored rows are below 2^27).
+        // Every problem of the wave belongs to instance id0; its blocks lie at
+        // growing offsets, less than 2^32 bytes apart (a facility pair's
+        // stored rows are below 2^27).
         if (!act[id0]) return;
         const Inst I = inst[id0];
         const Problem q = problem(I, x0 - fc.pre[k0] + seg);
@@ -270,7 +275,7 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     auto solve = [&](int nn, auto uni) __attribute__((always_inline)) -> double {
         const LapScratch<T> sc(smem + seg * LapLds<T, AUC>::bytes(nmax), nn);
         const LaneRows<T> rows{mat + lane, nn};
-        stage_block(sc.M, sc.ld, rows, nn, lane);
+        stage_block<T, SEG>(sc.M, sc.ld, rows, nn, lane);
         wave_sync();
         if constexpr (AUC)
             return lap_auction_flat<T, SEG, PM == kPrecF32Down>(sc, nn, rows, wr, dw, aw);

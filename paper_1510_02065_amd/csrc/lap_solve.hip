@@ -52,8 +52,12 @@ struct Classes {
 inline Classes classes_for(int batch, int dtype)
 {
     if (dtype == QAP_FP64)
-        return batch <= 4096 ? Classes{1, {64}} : batch <= 8192 ? Classes{3, {16, 32, 64}} : Classes{5, {16, 32, 48, 56, 64}};
-    return batch <= 8192 ? Classes{1, {64}} : batch <= 32768 ? Classes{3, {16, 32, 64}} : Classes{4, {16, 32, 48, 64}};
+        return batch <= 4096   ? Classes{1, {64}}
+               : batch <= 8192 ? Classes{3, {16, 32, 64}}
+                               : Classes{5, {16, 32, 48, 56, 64}};
+    return batch <= 8192    ? Classes{1, {64}}
+           : batch <= 32768 ? Classes{3, {16, 32, 64}}
+                            : Classes{4, {16, 32, 48, 64}};
 }
 // Up to this many problems all start at once, and their order does not matter.
 constexpr int kUnsorted = 1024;

@@ -415,7 +415,8 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     // index each child's entries from its own offD.
     if (ch->dmode == kAllBlocks) {
         const long long perD = perC * I0.ldD;
-        hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src, D, ch->dInst, K, perD);
+        hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src, D, ch->dInst, K,
+                           perD);
     } else {
         const unsigned runs = (unsigned)(M * (M - 1) / 2 * (M - 2));
         const long long perD = (perC / 2) * (M - 2) * (M - 2);
