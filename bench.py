@@ -6,8 +6,8 @@ concentrations C->B, B->LB') on the clustered N=25 instance (seed 0), with the
 whole state resident in HBM.  The timed region launches the iterations step by
 step with HIP events around every step on the stream the library launches on,
 so the per-kernel durations behind the roofline figure come from the timed
-iterations themselves; the next iterations, launched as one HIP graph each
-(the library's ascend), are timed after it as `graph_iters_per_s`.
+iterations themselves; the next iterations, in one call of the library's
+ascend, are timed after it as `graph_iters_per_s`.
 
 Every other leg is timed the same two ways over the same iteration counts, so
 rates compare like for like: certified FP32 and round-to-nearest FP32 on the
@@ -40,16 +40,16 @@ HBM_PEAK_GBS = 8000.0
 # until the counters are taken again.
 TRAFFIC = {
     # (step, N, precision, complementary pairs once): (csrc digest, scaled FETCH bytes, scaled WRITE bytes)
-    (4, 25, "fp64", True): ("48ce863f5d0130d8", 373952.4 * 1024 * 2.0, 774286.3 * 1024 * 1.0),
-    (3, 25, "fp64", True): ("48ce863f5d0130d8", 397714.9 * 1024 * 2.0, 743996.1 * 1024 * 1.0),
-    (4, 25, "fp32", True): ("48ce863f5d0130d8", 187197.0 * 1024 * 2.0, 385420.4 * 1024 * 1.0),
-    (3, 25, "fp32", True): ("48ce863f5d0130d8", 211227.3 * 1024 * 2.0, 390437.3 * 1024 * 1.0),
-    (4, 25, "fp32n", True): ("48ce863f5d0130d8", 187172.3 * 1024 * 2.0, 386180.9 * 1024 * 1.0),
-    (3, 25, "fp32n", True): ("48ce863f5d0130d8", 201844.8 * 1024 * 2.0, 372027.2 * 1024 * 1.0),
-    (4, 40, "fp64", True): ("48ce863f5d0130d8", 6877959.3 * 1024 * 2.0, 14611774.7 * 1024 * 1.0),
-    (3, 40, "fp64", True): ("48ce863f5d0130d8", 7947267.8 * 1024 * 2.0, 17150922.9 * 1024 * 1.0),
-    (4, 40, "fp32", True): ("48ce863f5d0130d8", 3441542.8 * 1024 * 2.0, 7922078.5 * 1024 * 1.0),
-    (3, 40, "fp32", True): ("48ce863f5d0130d8", 3716187.3 * 1024 * 2.0, 13650580.4 * 1024 * 1.0),
+    (4, 25, "fp64", True): ("830b74868359d9a4", 374148.4 * 1024 * 2.0, 776457.5 * 1024 * 1.0),
+    (3, 25, "fp64", True): ("830b74868359d9a4", 397701.1 * 1024 * 2.0, 743985.9 * 1024 * 1.0),
+    (4, 25, "fp32", True): ("830b74868359d9a4", 187225.0 * 1024 * 2.0, 380895.2 * 1024 * 1.0),
+    (3, 25, "fp32", True): ("830b74868359d9a4", 211186.4 * 1024 * 2.0, 390438.6 * 1024 * 1.0),
+    (4, 25, "fp32n", True): ("830b74868359d9a4", 187192.9 * 1024 * 2.0, 386455.8 * 1024 * 1.0),
+    (3, 25, "fp32n", True): ("830b74868359d9a4", 201855.3 * 1024 * 2.0, 372027.9 * 1024 * 1.0),
+    (4, 40, "fp64", True): ("830b74868359d9a4", 6876860.7 * 1024 * 2.0, 14666254.0 * 1024 * 1.0),
+    (3, 40, "fp64", True): ("830b74868359d9a4", 10694057.1 * 1024 * 2.0, 16854063.1 * 1024 * 1.0),
+    (4, 40, "fp32", True): ("830b74868359d9a4", 3441420.8 * 1024 * 2.0, 7976761.6 * 1024 * 1.0),
+    (3, 40, "fp32", True): ("830b74868359d9a4", 4254256.1 * 1024 * 2.0, 8223786.0 * 1024 * 1.0),
 }
 
 
@@ -128,8 +128,8 @@ def cpu_baseline(F, D, iters, budget_s=12.0):
 def batched_leg(stream, iters=20):
     """The batched workload: 256 branch-and-bound nodes cut from one clustered
     N=24 instance (seed 0) by fixing 2..14 assignments (N' = 10..22), all in
-    one handle, FP64 and certified FP32; iterations launched as HIP graphs
-    after one untimed iteration (which runs the tuner).  Each size's D->C
+    one handle, FP64 and certified FP32; iterations in one call of ascend
+    after one untimed iteration.  Each size's D->C
     concentration overlaps the next size's sweep; FP64 is also timed with the
     steps one after the other."""
     import numpy as np
@@ -225,10 +225,9 @@ def laps_per_iteration(N, pair):
 
 
 def timed_leg(F, D, precision, pair, warmup, steps, graph_iters, stream, lap_solver="canonical"):
-    """One handle on the stream: `warmup` untimed iterations (the first runs
-    the tuner), `steps` iterations launched step by step with HIP events
-    around every step, then `graph_iters` iterations launched as one HIP graph
-    each (the library's ascend).  Both timed regions are bracketed by
+    """One handle on the stream: `warmup` untimed iterations, `steps` iterations
+    launched step by step with HIP events around every step, then
+    `graph_iters` iterations in one call of the library's ascend.  Both timed regions are bracketed by
     synchronisation."""
     import torch
 
@@ -408,15 +407,14 @@ def main():
     stream = torch.cuda.Stream(device=dev)
     pair = not args.all_blocks
     digest = csrc_digest()
-    # Further iterations as one HIP graph launch each, up to the iteration at
-    # which the bound is compared with the oracle.
+    # Further iterations in one ascend, up to the iteration at which the bound is compared with the oracle.
     extra = max(args.steps, args.bound_iters - args.warmup - args.steps)
     total_iters = args.warmup + args.steps + extra
 
     def log(msg):
         print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
-    log(f"FP64 N={N}: {args.warmup} warm-up, {args.steps} step-launched, {extra} graph-launched iterations")
+    log(f"FP64 N={N}: {args.warmup} warm-up, {args.steps} step-launched, {extra} ascend iterations")
     main_leg = timed_leg(F, D, "fp64", pair, args.warmup, args.steps, extra, stream)
     it_s = 1000.0 / main_leg["ms_step"]
     lb_trace = main_leg["lb_trace"]
