@@ -61,35 +61,45 @@ hipError_t enqueue_iteration(qap_rlt2* h)
 }
 
 // Copy the trace entries written since the counters were last reset, add the
-// iteration counts, then reset the counters.  `upto`: no instance has run more
-// iterations since then.  `counts_iteration0`: the entries come from iteration
-// 0 (recorded in the trace, not counted).  `lb0` (nullable): LB of instance 0.
-// One copy: the counters, the bounds and the trace lie behind each other, the
-// trace with all instances' first entries first, and only `upto` of its rows
-// are read (with 16 KB per instance read whenever an entry was new, the 196
-// level-1 children of an N = 14 node spent 0.2 of 1.0 ms here).
+// iteration counts, then reset the counters.  `upto`: the iterations the
+// library has enqueued since then.  `counts_iteration0`: the entries come from
+// iteration 0 (recorded in the trace, not counted).  `lb0` (nullable): LB of
+// instance 0.  One copy: the counters, the bounds and the trace lie behind each
+// other, the trace with all instances' first entries first, and only `upto` of
+// its rows are read (with 16 KB per instance read whenever an entry was new, the
+// 196 level-1 children of an N = 14 node spent 0.2 of 1.0 ms here).  A caller
+// that replays steps from a graph of its own has run more iterations than the
+// library knows of: their rows take a second copy.  Nothing is left on the
+// stream: the caller may go on with the handle's steps on another one.
 qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = false, double* lb0 = nullptr)
 {
     const size_t K = h->K;
-    const long long rows = h->trace_level >= 1 ? std::min(upto, qap::kTraceCap) : 0;
+    const long long cap = h->trace_level >= 1 ? qap::kTraceCap : 0;
+    const long long rows = std::min(upto, cap);
     std::vector<double> buf(3 * K + 2 * K * (size_t)rows);
     QAP_HIP(hipMemcpyAsync(buf.data(), h->dCounter, buf.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    QAP_HIP(hipMemsetAsync(h->dCounter, 0, K * sizeof(long long), h->stream));
     QAP_HIP(hipStreamSynchronize(h->stream));
     static_assert(sizeof(long long) == sizeof(double), "one slot per counter");
     std::vector<long long> cnt(K);
     std::memcpy(cnt.data(), buf.data(), K * sizeof(long long));
+    const long long all = std::min(*std::max_element(cnt.begin(), cnt.end()), cap);
+    if (all > rows) {
+        const size_t have = buf.size();
+        buf.resize(3 * K + 2 * K * (size_t)all);
+        QAP_HIP(hipMemcpyAsync(buf.data() + have, reinterpret_cast<const double*>(h->dCounter) + have,
+                               (buf.size() - have) * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+        QAP_HIP(hipStreamSynchronize(h->stream));
+    }
     const double* trace = buf.data() + 3 * K;
-    bool any = false;
     for (size_t k = 0; k < K; ++k) {
-        any |= cnt[k] != 0;
-        for (long long t = 0; t < std::min(cnt[k], rows); ++t) {
+        for (long long t = 0; t < std::min(cnt[k], all); ++t) {
             h->tLB[k].push_back(trace[((size_t)t * K + k) * 2]);
             h->tLBp[k].push_back(trace[((size_t)t * K + k) * 2 + 1]);
         }
         if (!counts_iteration0) h->itk[k] += cnt[k];
     }
     if (lb0) *lb0 = buf[K];
-    if (any) QAP_HIP(hipMemsetAsync(h->dCounter, 0, K * sizeof(long long), h->stream));
     return QAP_OK;
 }
 

@@ -310,3 +310,37 @@ def test_relabel_and_flow_distance_swap_invariance(precision):
     tol = 1e-12 if precision == "fp64" else 1e-5
     for t in trajs[1:]:
         np.testing.assert_allclose(t, trajs[0], rtol=tol)
+
+
+def test_trace_holds_every_replayed_step():
+    # Steps captured into a caller's graph run once per replay; the trace and
+    # the iteration count hold every one of them, as they do for an ascend.
+    torch = pytest.importorskip("torch")
+    F, D = qapgen.small(8, 9)
+    a = Rlt2(F, D)
+    a.ascend(9)
+    stream = torch.cuda.Stream()
+    b = Rlt2(F, D, stream=stream.cuda_stream)
+    for s in (3, 4, 5, 6, 7):
+        b.step(s)
+    assert b.bound()[1] == 1
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for s in (3, 4, 5, 6, 7):
+            b.step(s)
+    with torch.cuda.stream(stream):
+        for _ in range(3):
+            graph.replay()
+        stream.synchronize()
+        assert b.bound() == (a.trace()[0][4], 4)
+        for _ in range(4):
+            graph.replay()
+    stream.synchronize()
+    b.ascend(1)
+    assert b.bound()[1] == 9
+    for x, y in zip(a.trace(), b.trace()):
+        np.testing.assert_array_equal(x, y)
+    for x, y in zip(a.read_state()[1:], b.read_state()[1:]):
+        np.testing.assert_array_equal(x, y)
+    a.close()
+    b.close()
