@@ -638,6 +638,18 @@ std::vector<char> snap_header(const qap_rlt2* h)
     return v;
 }
 
+// Whether a class of problems of up to nmax could run with `lanes` lanes per
+// problem and `columns` columns per lane: a pair that some build has had, wide
+// enough for the problems, its wave's problems within a workgroup's LDS.
+bool snap_config_fits(const qap_rlt2* h, int nmax, int lanes, int columns)
+{
+    const int most = lanes == 8 ? 8 : lanes == 16 ? 4 : lanes == 32 ? 2 : lanes == 64 ? 1 : 0;
+    if (columns < 1 || columns > most || (lanes == 8 && columns == 7) || lanes * columns < nmax) return false;
+    const size_t lds = h->elem == sizeof(double) ? qap::LapLds<double, true>::bytes(nmax)
+                                                 : qap::LapLds<float, true>::bytes(nmax);
+    return (64 / lanes) * lds <= h->lds_limit;
+}
+
 }  // namespace
 
 bool qap::give_back_kept_memory()
@@ -1130,10 +1142,13 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
     if ((size_t)(end - p) < dev_bytes) return fail(QAP_EINVAL, "truncated snapshot");
     // Parse the host part before touching the device.
     const char* q = p + dev_bytes;
-    // The kernel configurations do not depend on the snapshot.
-    int32_t cfg = 0;
-    for (int x = 0; x < 1 + 3 * 4 * 2; ++x)
-        if (!get(q, end, cfg)) return fail(QAP_EINVAL, "truncated snapshot");
+    // The kernel configurations are read to be checked only: this build's
+    // follow from the problem sizes.
+    int32_t flag = 0, cfg[3][4][2];
+    if (!get(q, end, flag)) return fail(QAP_EINVAL, "truncated snapshot");
+    for (auto& f : cfg)
+        for (auto& c : f)
+            if (!get(q, end, c[0]) || !get(q, end, c[1])) return fail(QAP_EINVAL, "truncated snapshot");
     std::vector<int64_t> itk(h->K);
     std::vector<std::vector<double>> tl(h->K), tp(h->K);
     for (int k = 0; k < h->K; ++k) {
@@ -1147,6 +1162,10 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
             get(q, end, tp[k][t]);
         }
     }
+    for (int f = 0; f < 3; ++f)
+        for (int c = 0; c < 4; ++c)
+            if (h->fam[f][c].total > 0 && !snap_config_fits(h, h->fam[f][c].nmax, cfg[f][c][0], cfg[f][c][1]))
+                return fail(QAP_EINVAL, "snapshot holds a kernel configuration this device cannot run");
     QAP_HIP(hipStreamSynchronize(h->stream));
     for (const SnapPart& s : parts) {
         if (s.bytes) QAP_HIP(hipMemcpy(s.dev, p, s.bytes, hipMemcpyHostToDevice));

@@ -307,3 +307,44 @@ def test_handles_after_a_closed_one_start_clean(precision):
                       (from_threads[1], first), (from_threads[2], other), (from_threads[3], first)]:
         for x, y in zip(got, want):
             np.testing.assert_array_equal(x, y)
+
+
+def test_restore_refuses_a_configuration_that_cannot_hold_the_problems():
+    # The snapshot's (lanes, columns) of every class: one of a kernel that
+    # exists, with room for the class's problems, within a workgroup's LDS.
+    F, D = qapgen.small(8, 2)   # one class in use per family, of 8 lanes
+    g = Rlt2(F, D, trace_level=0)
+    g.ascend(2)
+    snap = g.snapshot()
+    before = g.read_state()
+    # From the end: per instance the iteration count and the length of the
+    # trace (no entries at this level), before them 3 families x 4 classes x 2.
+    at = len(snap) - 16 - 3 * 4 * 2 * 4
+    cfg = np.frombuffer(snap[at:at + 96], dtype=np.int32).reshape(3, 4, 2)
+    assert (cfg[:, 0] == [8, 1]).all()
+    for f in range(3):
+        for lanes, columns in [(4, 2), (8, 7), (16, 5), (64, 2), (0, 0), (-8, -1)]:
+            bad = cfg.copy()
+            bad[f, 0] = lanes, columns
+            with pytest.raises(QapError) as e:
+                g.restore(snap[:at] + bad.tobytes() + snap[at + 96:])
+            assert e.value.status == -1, (f, lanes, columns)
+    for x, y in zip(before, g.read_state()):
+        np.testing.assert_array_equal(x, y)
+    wider = cfg.copy()   # what an earlier build may have chosen
+    wider[:, 0] = [[8, 2], [16, 1], [8, 8]]
+    g.restore(snap[:at] + wider.tobytes() + snap[at + 96:])
+    g.ascend(1)
+    h = Rlt2(F, D, trace_level=0)
+    h.ascend(3)
+    for x, y in zip(h.read_state(), g.read_state()):
+        np.testing.assert_array_equal(x, y)
+    big = Rlt2(*qapgen.uniform(24, 1), trace_level=0)   # 32-lane classes
+    snap = big.snapshot()
+    cfg = np.frombuffer(snap[-16 - 96:-16], dtype=np.int32).reshape(3, 4, 2).copy()
+    assert (cfg[:, 2] == [32, 1]).all()
+    cfg[0, 2] = 16, 1   # 16 columns for problems of 22
+    with pytest.raises(QapError):
+        big.restore(snap[:-16 - 96] + cfg.tobytes() + snap[-16:])
+    for x in (g, h, big):
+        x.close()
