@@ -114,18 +114,22 @@ qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = fal
 // handle's stream has drained, and its next handle clears it like a new one.
 class BlockCache {
 public:
-    // A kept block for `bytes`, or nullptr; one of another size is freed.
-    void* take(int dev, size_t bytes)
+    // A kept block for `bytes`, at most a quarter larger, and its size; or
+    // nullptr, and one of another size is freed.
+    void* take(int dev, size_t bytes, size_t* size)
     {
         std::lock_guard<std::mutex> lock(mu_);
         Block b = slot(dev);
         if (!b.p) return nullptr;
         slot(dev) = {};
-        if (b.bytes >= bytes && b.bytes - bytes <= bytes / 4) return b.p;
+        if (b.bytes >= bytes && b.bytes - bytes <= bytes / 4) {
+            *size = b.bytes;
+            return b.p;
+        }
         (void)hipFree(b.p);
         return nullptr;
     }
-    // Keep `p` or free it.
+    // Keep `p`, an allocation of `bytes`, or free it.
     void put(int dev, void* p, size_t bytes)
     {
         size_t freeb = 0, total = 0;
@@ -175,7 +179,7 @@ void release(qap_rlt2* h, bool drained = false)
     for (void* p : {h->arena, static_cast<void*>(h->dCt), static_cast<void*>(h->dBt)})
         if (p) (void)hipFree(p);
     if (h->dD && drained)
-        block_cache().put(h->device, h->dD, h->bytesD);
+        block_cache().put(h->device, h->dD, h->allocD);
     else if (h->dD)
         (void)hipFree(h->dD);
     for (hipEvent_t ev : h->ev_size)
@@ -475,7 +479,8 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     const size_t bytesD = (size_t)h->totalD * h->elem;
     if (h->level == 2) {
         h->bytesD = std::max<size_t>(bytesD, 1);
-        h->dD = block_cache().take(h->device, h->bytesD);
+        h->allocD = h->bytesD;
+        h->dD = block_cache().take(h->device, h->bytesD, &h->allocD);
     }
     size_t freeb = 0, totalb = 0;
     CK(hipMemGetInfo(&freeb, &totalb));

@@ -90,7 +90,8 @@ struct qap_rlt2 {
     size_t lds_limit = 65536;   // dynamic LDS a workgroup may request
     int num_cu = 256;           // compute units of the device
     size_t elem = 8;   // bytes per reduced cost
-    size_t bytesD = 0;   // of dD's allocation, or less
+    size_t bytesD = 0;   // of D
+    size_t allocD = 0;   // of the allocation it is in
     double stopK = 0.0, stopUB = 0.0;   // stop rule of Algorithm 1 (UB <= 0: off)
     std::vector<qap::Inst> inst;
     long long totalB = 0, totalC = 0, totalD = 0, totalWG = 0;

@@ -348,3 +348,28 @@ def test_restore_refuses_a_configuration_that_cannot_hold_the_problems():
         big.restore(snap[:-16 - 96] + cfg.tobytes() + snap[-16:])
     for x in (g, h, big):
         x.close()
+
+
+def _free_bytes():
+    torch = pytest.importorskip("torch")
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_a_reused_block_counts_at_its_real_size():
+    # Batches whose D shrinks by about a tenth from one to the next: each may
+    # use the memory of one closed before it, but none may hold more than a
+    # quarter beyond its own need.
+    F, D = qapgen.uniform(16, 1)
+    one = 16 ** 2 * 15 ** 2 * 14 ** 2 // 2 * 8   # bytes of an instance's D
+    Rlt2(F, D).close()
+    Rlt2(*qapgen.small(8, 0)).close()   # next to nothing is kept now
+    free = _free_bytes()
+    for count in (10, 9, 8):
+        for _ in range(3):
+            Rlt2.batch([F] * count, [D] * count).close()
+    g = Rlt2.batch([F] * 7, [D] * 7)
+    held = free - _free_bytes()
+    g.close()
+    print(f"held {held / one:.2f} instances' D for 7", flush=True)
+    assert held <= 1.25 * 7 * one + 0.6 * one   # the rest: B, C, the trace and the allocator's granularity
