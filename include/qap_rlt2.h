@@ -213,13 +213,18 @@ qap_status qap_rlt2_lap_values(qap_rlt2* h, double* sD, double* sC, double* sB);
  * be NULL. */
 qap_status qap_rlt2_read_state(qap_rlt2* h, double* lb, double* B, double* C, double* D);
 
-/* Release the handle and its device memory.  NULL-safe.  The D of the handle
- * closed last on a device stays allocated for the next handle of about its
- * size (clearing and mapping it anew costs more than an iteration): at most
- * 1/16 of the device's memory, and only while half of that is free.  It is
- * given back when a handle of another size is created, when an allocation of
- * the library fails, and when a later close finds less memory free. */
+/* Release the handle and all of its device memory.  NULL-safe.  From the second
+ * close in a row of handles whose D has about one size, on one device, that D
+ * stays allocated for the next such handle (clearing and mapping it anew costs
+ * more than an iteration): one D per device, at most 1/16 of the device's
+ * memory, and only while half of that is free.  It is given back by
+ * qap_rlt2_release_memory, when a handle of another size is created or closed,
+ * when an allocation of the library fails, and when a later close finds less
+ * memory free. */
 void qap_rlt2_destroy(qap_rlt2* h);
+
+/* Free what qap_rlt2_destroy has kept, on every device. */
+void qap_rlt2_release_memory(void);
 
 /* ---- many instances in one handle (branch-and-bound nodes) ------------------
  * Section 6 of the paper runs the dual ascent at every node of a

@@ -6,4 +6,4 @@ include/qap_rlt2.h); this package is its thin Python binding.
 """
 from ._binding import (MAX_N, QAP_FP32_CERTIFIED, QAP_FP32_NEAREST, QAP_FP64, QapError, Rlt2,  # noqa: F401
                        bnb_solve, lap_solve, lap_solve_device, lib, LIB_PATH, local_search, objective,
-                       subproblem)
+                       release_memory, subproblem)

@@ -63,6 +63,7 @@ SIGNATURES = {
     "qap_rlt2_lap_values": (ctypes.c_int, [_vp, _dp, _dp, _dp]),
     "qap_rlt2_read_state": (ctypes.c_int, [_vp, _dp, _dp, _dp, _dp]),
     "qap_rlt2_destroy": (None, [_vp]),
+    "qap_rlt2_release_memory": (None, []),
     "qap_lap_solve": (ctypes.c_int, [ctypes.c_int, _vp, _vp, _vp, _vp, ctypes.c_int, _vp, _vp, _vp,
                                      ctypes.c_int, _vp]),
     "qap_lap_solve_noalloc": (ctypes.c_int, [ctypes.c_int, _vp, _vp, _vp, _vp, ctypes.c_int, _vp, _vp, _vp,
@@ -384,6 +385,11 @@ class Rlt2:
         _check(lib().qap_rlt2_read_state(self._h, _dptr(lb), _dptr(B), _dptr(C), _dptr(D)),
                "qap_rlt2_read_state")
         return float(lb[0]), B, C, D
+
+
+def release_memory():
+    """Free the device memory kept from closed handles (qap_rlt2_release_memory)."""
+    lib().qap_rlt2_release_memory()
 
 
 def objective(F, D, perm, B0=None, constant=0.0):

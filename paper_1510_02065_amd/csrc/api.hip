@@ -104,12 +104,15 @@ qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = fal
 }
 
 // The D of the handle closed last on each device, kept for the next handle of
-// about its size.  The driver wipes freed device memory at some 57 GB/s and
-// holds later frees back once enough waits for that: a program that opens and
-// closes handles of N = 35 (3.1 GB) every 27 ms waited 60 ms in every close.
-// One block per device, at most 1/16 of its memory, and only while half of
-// the device's memory is free; given back when a handle of another size is
-// made, when any allocation of the library fails, and when a later close
+// about its size where a program opens and closes such handles one after the
+// other.  The driver wipes freed device memory at some 57 GB/s and holds later
+// frees back once enough waits for that: a program that opens and closes
+// handles of N = 35 (3.1 GB) every 27 ms waited 60 ms in every close.  So a
+// block is kept from the second close of about one size on, and a handle that
+// is closed for good gives all of its memory back.  One block per device, at
+// most 1/16 of its memory, and only while half of the device's memory is free;
+// given back by qap_rlt2_release_memory, when a handle of another size is made
+// or closed, when any allocation of the library fails, and when a later close
 // finds less than half of the memory free.  A block comes back only after its
 // handle's stream has drained, and its next handle clears it like a new one.
 class BlockCache {
@@ -121,7 +124,7 @@ public:
         std::lock_guard<std::mutex> lock(mu_);
         Block b = slot(dev);
         if (!b.p) return nullptr;
-        slot(dev) = {};
+        slot(dev) = {nullptr, 0, b.closed};
         if (b.bytes >= bytes && b.bytes - bytes <= bytes / 4) {
             *size = b.bytes;
             return b.p;
@@ -137,11 +140,14 @@ public:
         std::lock_guard<std::mutex> lock(mu_);
         Block& b = slot(dev);
         if (b.p) (void)hipFree(b.p);
-        b = {};
-        if (dev >= 0 && dev < kDevices && known && bytes <= total / 16 && freeb >= total / 2)
-            b = {p, bytes};
-        else
+        const size_t lo = std::min(b.closed, bytes), hi = std::max(b.closed, bytes);
+        b = {nullptr, 0, bytes};
+        if (dev >= 0 && dev < kDevices && known && hi - lo <= lo / 4 && bytes <= total / 16 && freeb >= total / 2) {
+            b.p = p;
+            b.bytes = bytes;
+        } else {
             (void)hipFree(p);
+        }
     }
     // Free the device's block; whether there was one.
     bool drop(int dev)
@@ -150,8 +156,17 @@ public:
         Block& b = slot(dev);
         if (!b.p) return false;
         (void)hipFree(b.p);
-        b = {};
+        b = {nullptr, 0, b.closed};
         return true;
+    }
+    // Free every device's block and forget what was closed.
+    void clear()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        for (Block& b : blocks_) {
+            if (b.p) (void)hipFree(b.p);
+            b = {};
+        }
     }
 
 private:
@@ -159,6 +174,7 @@ private:
     struct Block {
         void* p = nullptr;
         size_t bytes = 0;
+        size_t closed = 0;   // bytes of the D closed last
     };
     Block& slot(int dev) { return blocks_[dev >= 0 && dev < kDevices ? dev : kDevices]; }
     std::mutex mu_;
@@ -1191,6 +1207,8 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
 }
 
 void qap_rlt2_destroy(qap_rlt2* h) { destroy_handle(h); }
+
+void qap_rlt2_release_memory(void) { block_cache().clear(); }
 
 qap_status qap_rlt2_children(qap_rlt2* h, int k, int count, const int32_t* fac, const int32_t* loc, int level,
                              qap_rlt2** out)

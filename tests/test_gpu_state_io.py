@@ -373,3 +373,24 @@ def test_a_reused_block_counts_at_its_real_size():
     g.close()
     print(f"held {held / one:.2f} instances' D for 7", flush=True)
     assert held <= 1.25 * 7 * one + 0.6 * one   # the rest: B, C, the trace and the allocator's granularity
+
+
+def test_closing_gives_the_memory_back():
+    # A handle's memory is free again once it is closed.  One that is opened and
+    # closed again and again at one size may keep its D's between two of them,
+    # until the program asks for it back.
+    from paper_1510_02065_amd import release_memory
+    F, D = qapgen.uniform(24, 1)
+    one = 24 ** 2 * 23 ** 2 * 22 ** 2 // 2 * 8   # 590 MB
+    Rlt2(*qapgen.small(8, 0)).close()
+    release_memory()
+    free = _free_bytes()
+    with Rlt2(F, D) as g:
+        g.ascend(1)
+        assert _free_bytes() <= free - one
+    assert _free_bytes() >= free - one // 8
+    for _ in range(4):
+        Rlt2(F, D).close()
+    release_memory()
+    assert _free_bytes() >= free - one // 8
+    release_memory()   # nothing kept: nothing happens
