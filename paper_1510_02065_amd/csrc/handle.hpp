@@ -39,6 +39,20 @@ inline int seg_for(int n)
 
 inline unsigned grid_for(long long work, int threads) { return (unsigned)((work + threads - 1) / threads); }
 
+// A launch has fewer than 2^32 threads (their number is taken modulo that: the
+// rest does not run, and there is no error).  f(first, count) launches
+// workgroups first .. first + count - 1 of `groups` and returns its error; it is
+// called as often as that takes (once for all but the largest batches).
+template <typename F>
+hipError_t in_launches(long long groups, int threads, F f)
+{
+    const long long most = 0xffffffffll / threads / 8 * 8;
+    hipError_t e = hipSuccess;
+    for (long long first = 0; first < groups && e == hipSuccess; first += most)
+        e = f(first, (unsigned)(groups - first < most ? groups - first : most));
+    return e;
+}
+
 // Per-instance trace entries kept on the device between host reads.
 constexpr long long kTraceCap = 1024;
 
@@ -55,7 +69,7 @@ struct ClassHost {
     long long total = 0;
     int* d_ids = nullptr;
     long long* d_pre = nullptr;
-    FamilyClass dev() const { return FamilyClass{d_ids, d_pre, (int)ids.size(), total}; }
+    FamilyClass dev(long long first) const { return FamilyClass{d_ids, d_pre, (int)ids.size(), total, first}; }
 };
 
 // Instances of one size: steps 1-3 run one launch per size, with the kernel,

@@ -145,13 +145,15 @@ __global__ __launch_bounds__(256) void k_child_D(ChildSrc<StoreT<PM>> src, Store
 // products.  Bound by memory.  (With a thread per entry of D and 64-bit
 // divisions for its indices the 18 children of an N = 18 node took 863 us for
 // their 1.2 GB; now 407.)  The first workgroup of a child clears the entries
-// up to the next child's start.
+// up to the next child's start.  The launch takes the runs from `first` on (all
+// of them together are fewer than 2^32: each has 48 bytes or more).
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_runs(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ D,
-                                                    const Inst* __restrict__ inst, unsigned runs, int pad)
+                                                    const Inst* __restrict__ inst, unsigned runs, int pad,
+                                                    long long first)
 {
     using T = StoreT<PM>;
-    const unsigned wg = (unsigned)xcd_major(blockIdx.x, gridDim.x);
+    const unsigned wg = (unsigned)(first + xcd_major(blockIdx.x, gridDim.x));
     const int c = (int)(wg / runs), r = (int)(wg % runs);
     const int a = src.fix[2 * c], b = src.fix[2 * c + 1];
     const int N = src.N, n1 = N - 1, n2 = N - 2, M = N - 1, m1 = M - 1, m2 = M - 2;

@@ -12,12 +12,14 @@ namespace qap {
 
 // Problems of a family, for the instances of one segment-size class:
 // cls[0..Kc) are the instance ids and pre[] the prefix sums of their problem
-// counts, so problem x belongs to instance cls[find_seg(pre, Kc, x)].
+// counts, so problem x belongs to instance cls[find_seg(pre, Kc, x)].  A launch
+// takes the problems from `first` on.
 struct FamilyClass {
     const int* cls;
     const long long* pre;
     int Kc;
     long long total;
+    long long first;
 };
 
 enum LapFamily : int { kFamD = 0, kFamC = 1 };
@@ -145,7 +147,7 @@ void k_lap_family_s(StoreT<PM>* __restrict__ D, StoreT<PM>* __restrict__ C, Stor
     };
     // The parents are read before the solve, so that the wave does not wait
     // for them at its end.
-    const long long x0 = xcd_major(blockIdx.x, gridDim.x) * LPW;
+    const long long x0 = fc.first + xcd_major(blockIdx.x, gridDim.x) * LPW;
     const int k0 = find_seg(fc.pre, fc.Kc, x0);
     const int id0 = fc.cls[k0];
     const long long end0 = k0 + 1 < fc.Kc ? fc.pre[k0 + 1] : fc.total;
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     constexpr int LPW = 64 / SEG;
     const int seg = threadIdx.x / SEG;
     const int lane = threadIdx.x & (SEG - 1);
-    const long long x = (long long)blockIdx.x * LPW + seg;
+    const long long x = fc.first + (long long)blockIdx.x * LPW + seg;
     const int k = x < fc.total ? fc.cls[x] : 0;
     const bool active = x < fc.total && act[k];
     const Inst I = inst[k];

@@ -15,20 +15,21 @@ hipError_t launch_family_seg(qap_rlt2* h, int famk, const ClassHost& c, double* 
 {
     using T = StoreT<PM>;
     constexpr int LPW = 64 / SEG;
-    const FamilyClass fc = c.dev();
     const size_t lds = slot_lds<T, SEG, AUC>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;   // not launched
-    const unsigned grid = (unsigned)((fc.total + LPW - 1) / LPW);
     T* D = static_cast<T*>(h->dD);
     T* C = static_cast<T*>(h->dC);
     T* B = static_cast<T*>(h->dB);
-    if (famk == kFamD)
-        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamD, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
-                           h->dInst, fc, c.nmax, values, h->dmode, h->dAct);
-    else
-        hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamC, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
-                           h->dInst, fc, c.nmax, values, kAllBlocks, h->dAct);
-    return hipGetLastError();
+    return in_launches((c.total + LPW - 1) / LPW, 64, [&](long long first, unsigned grid) {
+        const FamilyClass fc = c.dev(first * LPW);
+        if (famk == kFamD)
+            hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamD, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
+                               h->dInst, fc, c.nmax, values, h->dmode, h->dAct);
+        else
+            hipLaunchKernelGGL((k_lap_family_s<PM, SEG, kFamC, AUC>), dim3(grid), dim3(64), lds, h->stream, D, C, B,
+                               h->dInst, fc, c.nmax, values, kAllBlocks, h->dAct);
+        return hipGetLastError();
+    });
 }
 
 template <int PM, int SEG, bool AUC>
@@ -38,12 +39,13 @@ hipError_t launch_B_seg(qap_rlt2* h, const ClassHost& c)
     constexpr int LPW = 64 / SEG;
     const size_t lds = slot_lds<T, SEG, AUC>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
-    const unsigned grid = (unsigned)((c.total + LPW - 1) / LPW);
     const bool tr = h->trace_level >= 1;
-    hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
-                       h->dInst, c.dev(), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter, kTraceCap, h->K,
-                       h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
-    return hipGetLastError();
+    return in_launches((c.total + LPW - 1) / LPW, 64, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
+                           h->dInst, c.dev(first * LPW), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter,
+                           kTraceCap, h->K, h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
+        return hipGetLastError();
+    });
 }
 
 // Lanes per problem: the narrowest segment that holds the class's problems
@@ -229,9 +231,11 @@ template <int PM, bool SPREAD>
 hipError_t launch_transfer_C(qap_rlt2* h)
 {
     using T = StoreT<PM>;
-    hipLaunchKernelGGL((k_transfer_C<PM, SPREAD>), dim3((unsigned)h->totalP), dim3(256), 0, h->stream,
-                       static_cast<T*>(h->dC), static_cast<const T*>(h->dB), h->dInst, h->dPreP, h->K, h->dAct);
-    return hipGetLastError();
+    return in_launches(h->totalP, 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_transfer_C<PM, SPREAD>), dim3(grid), dim3(256), 0, h->stream, static_cast<T*>(h->dC),
+                           static_cast<const T*>(h->dB), h->dInst, h->dPreP, h->K, first, h->dAct);
+        return hipGetLastError();
+    });
 }
 
 template <int PM>
@@ -420,8 +424,11 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     } else {
         const unsigned runs = (unsigned)(M * (M - 1) / 2 * (M - 2));
         const long long perD = (perC / 2) * (M - 2) * (M - 2);
-        hipLaunchKernelGGL((k_child_runs<PM>), dim3((unsigned)K * runs), dim3(256), 0, st, src, D, ch->dInst, runs,
-                           (int)(ch->totalD / K - perD));
+        return in_launches((long long)K * runs, 256, [&](long long first, unsigned grid) {
+            hipLaunchKernelGGL((k_child_runs<PM>), dim3(grid), dim3(256), 0, st, src, D, ch->dInst, runs,
+                               (int)(ch->totalD / K - perD), first);
+            return hipGetLastError();
+        });
     }
     return hipGetLastError();
 }

@@ -1253,17 +1253,18 @@ __global__ __launch_bounds__(kTripleThreads) void k_sweep_triple_p(StoreT<PM>* _
 // pair i < k of an instance: the entries c_knij that its lanes touch, a
 // column each of N rows of n1 entries, lie in as many lines as the L1 holds,
 // and consecutive pairs, which share the lines at their runs' ends, run on one
-// XCD.  Bound by memory.  (With a thread per entry of C, half of them idle, a
-// 64-bit division and a search for the instance each, 196 children of N = 13
-// took 58 us, and 38 for step 1 before it; both take 26 us here.)
+// XCD; the launch takes the pairs from `first` on.  Bound by memory.  (With a
+// thread per entry of C, half of them idle, a 64-bit division and a search for
+// the instance each, 196 children of N = 13 took 58 us, and 38 for step 1
+// before it; both take 26 us here.)
 template <int PM, bool SPREAD>
 __global__ __launch_bounds__(256) void k_transfer_C(StoreT<PM>* __restrict__ C, const StoreT<PM>* __restrict__ B,
                                                     const Inst* __restrict__ inst,
-                                                    const long long* __restrict__ preP, int K,
+                                                    const long long* __restrict__ preP, int K, long long first,
                                                     const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long wg = xcd_major(blockIdx.x, gridDim.x);
+    const long long wg = first + xcd_major(blockIdx.x, gridDim.x);
     const int kk = find_seg(preP, K, wg);
     if (!act[kk]) return;
     const Inst I = inst[kk];

@@ -9,6 +9,7 @@
   reduced costs stay >= 0.
 * A state that cannot fit in HBM (N = 64 in FP64 with every block stored:
   500 GB) is refused with QAP_ENOMEM before anything is allocated.
+* Batches with more work per step than one launch may have threads (2^32).
 """
 import numpy as np
 import pytest
@@ -46,3 +47,50 @@ def test_maximum_size_n64_fp32_nearest():
     assert Bst.min() >= 0 and Cst.min() >= 0
     print(f"N=64: GLB {glb:.6g}, LB_0 {lb0:.6g}, LB_1 {lb1:.6g}, UB {ub:.6g}", flush=True)
     g.close()
+
+
+def _same_bounds(g, F, D, iters, **kw):
+    h = Rlt2(F, D, **kw)
+    h.ascend(iters)
+    g.ascend(iters)
+    np.testing.assert_array_equal(g.bounds(), h.bounds()[0])
+    last = len(g.Ns) - 1
+    for x, y in zip(g.read_state_k(last, want_D=False), h.read_state(want_D=False)):
+        np.testing.assert_array_equal(x, y)
+    h.close()
+
+
+def test_level1_batch_of_more_pairs_than_one_launch():
+    # 306000 instances of N = 11: 16.8 million facility pairs, a workgroup of
+    # 256 threads each.
+    F, D = qapgen.small(11, 3)
+    count = 306000
+    print("level 1, 306000 instances", flush=True)
+    with Rlt2.batch([F] * count, [D] * count, precision="fp32n", level=1) as g:
+        _same_bounds(g, F, D, 2, precision="fp32n", level=1)
+
+
+def test_level2_batch_of_more_assignments_than_one_launch():
+    # 45000 instances of N = 11: 272 million blocks of D, 16 lanes each.
+    F, D = qapgen.small(11, 4)
+    count = 45000
+    print("level 2, 45000 instances", flush=True)
+    with Rlt2.batch([F] * count, [D] * count, precision="fp32n") as g:
+        _same_bounds(g, F, D, 2, precision="fp32n")
+
+
+def test_children_of_more_runs_than_one_launch():
+    # 600000 children of N = 5: 18 million runs, a workgroup of 256 threads each.
+    F, D = qapgen.small(6, 3)
+    with Rlt2(F, D, trace_level=0) as g:
+        g.ascend(2)
+        count = 600000
+        fac = np.arange(count, dtype=np.int32) % 6
+        loc = np.arange(count, dtype=np.int32) // 6 % 6
+        print("600000 children", flush=True)
+        few = g.children(0, fac[:36], loc[:36])
+        with g.children(0, fac, loc) as ch:
+            for c in (0, 35, 36 * 8000 + 7, count - 1):
+                for x, y in zip(ch.read_state_k(c), few.read_state_k(c % 36)):
+                    np.testing.assert_array_equal(x, y)
+        few.close()
