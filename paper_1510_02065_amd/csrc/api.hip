@@ -425,7 +425,9 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
         }
         h->totalWG += 8LL * ((I.ntri + 7) / 8) * I.wpt;
     }
-    // One sweep launch per instance size, the largest first.
+    // One sweep launch per instance size, the largest first; more where the
+    // instances of a size have more workgroups (of up to 1024 threads) than a
+    // launch may have.
     if (h->dmode == qap::kHalfStore && h->level == 2) {
         std::vector<int> sizes(Ns, Ns + count);
         std::sort(sizes.begin(), sizes.end(), std::greater<int>());
@@ -438,9 +440,16 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
             for (int k = 0; k < count; ++k)
                 if ((int)Ns[k] == N) {
                     const long long ntri = h->inst[k].ntri;
+                    const long long nwg = c.nt == qap::kSweepBox ? 8 * ((ntri + 7) / 8) * tiles * tiles : ntri;
+                    if (c.nwg + nwg > 0xffffffffll / 1024) {
+                        h->sweep_cls.push_back(c);
+                        c.ids.clear();
+                        c.pre.clear();
+                        c.nwg = 0;
+                    }
                     c.ids.push_back(k);
                     c.pre.push_back(c.nwg);
-                    c.nwg += c.nt == qap::kSweepBox ? 8 * ((ntri + 7) / 8) * tiles * tiles : ntri;
+                    c.nwg += nwg;
                 }
             h->sweep_cls.push_back(std::move(c));
         }

@@ -37,7 +37,8 @@ inline int seg_for(int n)
     return 64;
 }
 
-inline unsigned grid_for(long long work, int threads) { return (unsigned)((work + threads - 1) / threads); }
+// Workgroups for `work` items, `each` of them per workgroup.
+inline long long groups_of(long long work, int each) { return (work + each - 1) / each; }
 
 // A launch has fewer than 2^32 threads (their number is taken modulo that: the
 // rest does not run, and there is no error).  f(first, count) launches

@@ -51,12 +51,14 @@ struct ChildSrc {
     const int* fix;      // fix[2c], fix[2c+1]: facility and location child c fixes
 };
 
-// One thread per child B entry: b'_ij, and LB' from the thread of entry 0.
+// One thread per child B entry: b'_ij, and LB' from the thread of entry 0.  Here
+// and below a launch takes the workgroups from `first` on.
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_B(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ B,
-                                                 double* __restrict__ lb, const Inst* __restrict__ inst, int K)
+                                                 double* __restrict__ lb, const Inst* __restrict__ inst, int K,
+                                                 long long first)
 {
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (first + blockIdx.x) * 256 + threadIdx.x;
     const int M = src.N - 1;
     if (x >= (long long)K * M * M) return;
     const int c = (int)(x / (M * M));
@@ -83,11 +85,12 @@ __global__ __launch_bounds__(256) void k_child_B(ChildSrc<StoreT<PM>> src, Store
 // One thread per child C entry: c'_{ij kn}; `blocks` workgroups per child.
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_C(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ C,
-                                                 const Inst* __restrict__ inst, unsigned blocks)
+                                                 const Inst* __restrict__ inst, unsigned blocks, long long first)
 {
     const int M = src.N - 1, m1 = M - 1;
-    const int c = (int)(blockIdx.x / blocks);
-    const int e = (int)(blockIdx.x % blocks) * 256 + (int)threadIdx.x;
+    const unsigned wg = (unsigned)(first + blockIdx.x);
+    const int c = (int)(wg / blocks);
+    const int e = (int)(wg % blocks) * 256 + (int)threadIdx.x;
     if (e >= M * M * m1 * m1) return;
     const int a = src.fix[2 * c], b = src.fix[2 * c + 1];
     const int ij = quotient24(e, m1 * m1), rem = e - ij * (m1 * m1);
@@ -114,9 +117,9 @@ __global__ __launch_bounds__(256) void k_child_C(ChildSrc<StoreT<PM>> src, Store
 // stored entry: d'_{ij kn pq} = d_{ij kn pq}.
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_D(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ D,
-                                                 const Inst* __restrict__ inst, int K, long long per)
+                                                 const Inst* __restrict__ inst, int K, long long per, long long first)
 {
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (first + blockIdx.x) * 256 + threadIdx.x;
     if (x >= (long long)K * per) return;
     const int c = (int)(x / per);
     const long long e = x - (long long)c * per;
@@ -145,8 +148,8 @@ __global__ __launch_bounds__(256) void k_child_D(ChildSrc<StoreT<PM>> src, Store
 // products.  Bound by memory.  (With a thread per entry of D and 64-bit
 // divisions for its indices the 18 children of an N = 18 node took 863 us for
 // their 1.2 GB; now 407.)  The first workgroup of a child clears the entries
-// up to the next child's start.  The launch takes the runs from `first` on (all
-// of them together are fewer than 2^32: each has 48 bytes or more).
+// up to the next child's start.  (All runs together are fewer than 2^32: each
+// has 48 bytes or more.)
 template <int PM>
 __global__ __launch_bounds__(256) void k_child_runs(ChildSrc<StoreT<PM>> src, StoreT<PM>* __restrict__ D,
                                                     const Inst* __restrict__ inst, unsigned runs, int pad,
@@ -178,9 +181,10 @@ __global__ __launch_bounds__(256) void k_child_runs(ChildSrc<StoreT<PM>> src, St
 
 // Level-1 certification: no D, so c~ = c.
 template <typename T>
-__global__ __launch_bounds__(256) void k_cert_noD(const T* __restrict__ C, double* __restrict__ ct, long long totalC)
+__global__ __launch_bounds__(256) void k_cert_noD(const T* __restrict__ C, double* __restrict__ ct, long long totalC,
+                                                  long long first)
 {
-    const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long x = (first + blockIdx.x) * 256 + threadIdx.x;
     if (x < totalC) ct[x] = (double)C[x];
 }
 

@@ -238,15 +238,16 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     }
 }
 
-// Generic batch (qap_lap_solve): launch slot s < count solves problem
-// b = idx[first + s] (b = s when idx is null).  With `range` (device memory)
-// first = range[0] and count = range[1]; without it they are 0 and `count`.  Problem b has size n[b] (<=
-// nmax <= SEG, else its value is NaN and nothing else is written), matrix at
+// Generic batch (qap_lap_solve), workgroups from `first` on: slot s < count
+// solves problem
+// b = idx[r + s] (b = s when idx is null).  With `range` (device memory) r =
+// range[0] and count = range[1]; without it they are 0 and `count`.  Problem b
+// has size n[b] (<= nmax <= SEG, else its value is NaN and nothing else is written), matrix at
 // cost + mat_off[b], vectors at vec_off[b] (vec_off may be null when duals and
 // assign are).  The launch's LDS holds problems of up to nmax.  AUC: the
 // auction solver (lap_auction_flat) instead of the canonical dual.
 template <int PM, int SEG, bool AUC>
-__global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restrict__ range,
+__global__ __launch_bounds__(64) void k_lap_batch(long long first, int count, const int* __restrict__ range,
                                                   const int32_t* __restrict__ idx, int nmax,
                                                   const int32_t* __restrict__ nv,
                                                   const int64_t* __restrict__ mat_off,
@@ -261,8 +262,8 @@ __global__ __launch_bounds__(64) void k_lap_batch(int count, const int* __restri
     const int seg = threadIdx.x / SEG;
     const int lane = threadIdx.x & (SEG - 1);
     const int cnt = range ? range[1] : count;
-    if ((int64_t)blockIdx.x * LPW >= cnt) return;
-    const int64_t s = (int64_t)blockIdx.x * LPW + seg;
+    const int64_t s0 = (first + blockIdx.x) * LPW, s = s0 + seg;
+    if (s0 >= cnt) return;
     const bool in = s < cnt;
     const int64_t b = !in ? 0 : idx ? (int64_t)idx[(range ? range[0] : 0) + s] : s;
     int n = in ? nv[b] : 0;

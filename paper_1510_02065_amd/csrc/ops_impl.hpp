@@ -119,10 +119,11 @@ hipError_t launch_batch_seg(hipStream_t st, int nmax, int count, const int* rang
     if (count <= 0) return hipSuccess;
     constexpr int LPW = 64 / SEG;
     const size_t lds = slot_lds<T, SEG, AUC>(nmax);
-    const unsigned grid = (unsigned)((count + LPW - 1) / LPW);
-    hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, count, range, idx, nmax, n, mo, vo, cost,
-                       value, duals, assign, wr);
-    return hipGetLastError();
+    return in_launches(((long long)count + LPW - 1) / LPW, 64, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_lap_batch<PM, SEG, AUC>), dim3(grid), dim3(64), lds, st, first, count, range, idx, nmax,
+                           n, mo, vo, cost, value, duals, assign, wr);
+        return hipGetLastError();
+    });
 }
 
 // Workgroups of k_sweep_triple<PM, NT> a CU holds at size N (its registers
@@ -241,9 +242,23 @@ hipError_t launch_transfer_C(qap_rlt2* h)
 template <int PM>
 hipError_t launch_clear_B(qap_rlt2* h)
 {
-    hipLaunchKernelGGL((k_clear_B<PM>), dim3(grid_for(h->totalB, 256)), dim3(256), 0, h->stream,
-                       static_cast<StoreT<PM>*>(h->dB), h->dPreB, h->K, h->totalB, h->dAct);
-    return hipGetLastError();
+    return in_launches(groups_of(h->totalB, 256), 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_clear_B<PM>), dim3(grid), dim3(256), 0, h->stream, static_cast<StoreT<PM>*>(h->dB),
+                           h->dPreB, h->K, h->totalB, first * 256, h->dAct);
+        return hipGetLastError();
+    });
+}
+
+template <int PM>
+hipError_t launch_spread_prep(qap_rlt2* h)
+{
+    using T = StoreT<PM>;
+    return in_launches(groups_of(h->totalC, 256), 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_spread_prep<PM>), dim3(grid), dim3(256), 0, h->stream, static_cast<T*>(h->dC),
+                           static_cast<T*>(h->dB), static_cast<T*>(h->dCC), h->dInst, h->dPreC, h->K, h->totalC,
+                           first * 256, h->dAct);
+        return hipGetLastError();
+    });
 }
 
 // Steps 1 and 5 of a level-1 iteration in one pass over C.
@@ -267,20 +282,21 @@ hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
     switch (step) {
     case 3: {   // steps 1-3 (level 1: step 1)
         if (h->level == 1) {
-            hipLaunchKernelGGL((k_spread_B<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st, C, B, h->dInst,
-                               h->dPreC, h->K, h->totalC, h->dAct);
-            hipError_t e = hipGetLastError();
+            const hipError_t e = in_launches(groups_of(h->totalC, 256), 256, [&](long long first, unsigned grid) {
+                hipLaunchKernelGGL((k_spread_B<PM>), dim3(grid), dim3(256), 0, st, C, B, h->dInst, h->dPreC, h->K,
+                                   h->totalC, first * 256, h->dAct);
+                return hipGetLastError();
+            });
             return e == hipSuccess ? launch_clear_B<PM>(h) : e;
         }
-        hipLaunchKernelGGL((k_spread_prep<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st, C, B, CC,
-                           h->dInst, h->dPreC, h->K, h->totalC, h->dAct);
-        hipError_t e = hipGetLastError();
+        hipError_t e = launch_spread_prep<PM>(h);
         if (e != hipSuccess) return e;
-        if (h->dmode == kAllBlocks) {
-            hipLaunchKernelGGL((k_sweep<PM>), dim3((unsigned)h->totalWG), dim3(256), 0, st, D, CC, B, h->dTri,
-                               h->dInst, h->dPreWG, h->K, h->dAct);
-            return hipGetLastError();
-        }
+        if (h->dmode == kAllBlocks)
+            return in_launches(h->totalWG, 256, [&](long long first, unsigned grid) {
+                hipLaunchKernelGGL((k_sweep<PM>), dim3(grid), dim3(256), 0, st, D, CC, B, h->dTri, h->dInst,
+                                   h->dPreWG, h->K, first, h->dAct);
+                return hipGetLastError();
+            });
         for (const SweepClass& c : h->sweep_cls) {
             e = launch_sweep<PM>(h, c);
             if (e != hipSuccess) return e;
@@ -304,12 +320,8 @@ hipError_t Ops<PM>::enqueue_step(qap_rlt2* h, int step)
 template <int PM>
 hipError_t Ops<PM>::enqueue_sweep_concentrate_overlapped(qap_rlt2* h)
 {
-    using T = StoreT<PM>;
     hipStream_t A = h->stream, Bs = h->stream2;
-    hipLaunchKernelGGL((k_spread_prep<PM>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, A, static_cast<T*>(h->dC),
-                       static_cast<T*>(h->dB), static_cast<T*>(h->dCC), h->dInst, h->dPreC, h->K, h->totalC,
-                       h->dAct);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_spread_prep<PM>(h);
     if (e != hipSuccess) return e;
     if ((e = hipEventRecord(h->ev_fork, A)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(Bs, h->ev_fork, 0)) != hipSuccess) return e;
@@ -334,22 +346,31 @@ hipError_t Ops<PM>::certify(qap_rlt2* h)
 {
     using T = StoreT<PM>;
     hipStream_t st = h->stream;
+    const T *D = static_cast<const T*>(h->dD), *C = static_cast<const T*>(h->dC), *B = static_cast<const T*>(h->dB);
+    hipError_t e = hipSuccess;
     if (h->level == 1)
-        hipLaunchKernelGGL((k_cert_noD<T>), dim3(grid_for(h->totalC, 256)), dim3(256), 0, st,
-                           static_cast<const T*>(h->dC), h->dCt, h->totalC);
+        e = in_launches(groups_of(h->totalC, 256), 256, [&](long long first, unsigned grid) {
+            hipLaunchKernelGGL((k_cert_noD<T>), dim3(grid), dim3(256), 0, st, C, h->dCt, h->totalC, first);
+            return hipGetLastError();
+        });
     else if (h->dmode == kAllBlocks)
-        hipLaunchKernelGGL((k_cert_D<T>), dim3(grid_for(h->totalC, 4)), dim3(256), 0, st,
-                           static_cast<const T*>(h->dD), static_cast<const T*>(h->dC), h->dCt, h->dInst, h->dPreC,
-                           h->K, h->totalC);
+        e = in_launches(groups_of(h->totalC, 4), 256, [&](long long first, unsigned grid) {
+            hipLaunchKernelGGL((k_cert_D<T>), dim3(grid), dim3(256), 0, st, D, C, h->dCt, h->dInst, h->dPreC, h->K,
+                               h->totalC, first);
+            return hipGetLastError();
+        });
     else
-        hipLaunchKernelGGL((k_cert_pairs<T>), dim3((unsigned)h->totalCert), dim3(kCertThreads), 0, st,
-                           static_cast<const T*>(h->dD), static_cast<const T*>(h->dC), h->dCt, h->dInst, h->dPreCert,
-                           h->K);
-    hipError_t e = hipGetLastError();
+        e = in_launches(h->totalCert, kCertThreads, [&](long long first, unsigned grid) {
+            hipLaunchKernelGGL((k_cert_pairs<T>), dim3(grid), dim3(kCertThreads), 0, st, D, C, h->dCt, h->dInst,
+                               h->dPreCert, h->K, first);
+            return hipGetLastError();
+        });
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_cert_C<T>), dim3(grid_for(h->totalB, 4)), dim3(256), 0, st, h->dCt,
-                       static_cast<const T*>(h->dB), h->dBt, h->dInst, h->dPreB, h->K, h->totalB);
-    e = hipGetLastError();
+    e = in_launches(groups_of(h->totalB, 4), 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_cert_C<T>), dim3(grid), dim3(256), 0, st, h->dCt, B, h->dBt, h->dInst, h->dPreB, h->K,
+                           h->totalB, first);
+        return hipGetLastError();
+    });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_cert_final<>, dim3(h->K), dim3(64), 0, st, h->dBt, h->dLB, h->dCert, h->dInst);
     return hipGetLastError();
@@ -362,7 +383,7 @@ hipError_t Ops<PM>::init_instance(qap_rlt2* h, int k, const double* dF, const do
     const Inst& I = h->inst[k];
     const int N = I.N;
     const long long nC = (long long)N * N * (N - 1) * (N - 1);
-    hipLaunchKernelGGL((k_init<PM>), dim3(grid_for(nC, 256)), dim3(256), 0, h->stream, dF, dDm, dB0,
+    hipLaunchKernelGGL((k_init<PM>), dim3((unsigned)groups_of(nC, 256)), dim3(256), 0, h->stream, dF, dDm, dB0,
                        static_cast<T*>(h->dB) + I.offB, static_cast<T*>(h->dC) + I.offC, N);
     return hipGetLastError();
 }
@@ -403,15 +424,19 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     src.fix = dfix;
     const int K = ch->K, M = P.N - 1;
     hipStream_t st = ch->stream;
-    hipLaunchKernelGGL((k_child_B<PM>), dim3(grid_for((long long)K * M * M, 256)), dim3(256), 0, st, src,
-                       static_cast<T*>(ch->dB), ch->dLB, ch->dInst, K);
-    hipError_t e = hipGetLastError();
+    hipError_t e = in_launches(groups_of((long long)K * M * M, 256), 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_child_B<PM>), dim3(grid), dim3(256), 0, st, src, static_cast<T*>(ch->dB), ch->dLB,
+                           ch->dInst, K, first);
+        return hipGetLastError();
+    });
     if (e != hipSuccess) return e;
     const long long perC = (long long)M * M * (M - 1) * (M - 1);
-    const unsigned blocksC = grid_for(perC, 256);
-    hipLaunchKernelGGL((k_child_C<PM>), dim3((unsigned)K * blocksC), dim3(256), 0, st, src, static_cast<T*>(ch->dC),
-                       ch->dInst, blocksC);
-    e = hipGetLastError();
+    const unsigned blocksC = (unsigned)groups_of(perC, 256);
+    e = in_launches((long long)K * blocksC, 256, [&](long long first, unsigned grid) {
+        hipLaunchKernelGGL((k_child_C<PM>), dim3(grid), dim3(256), 0, st, src, static_cast<T*>(ch->dC), ch->dInst,
+                           blocksC, first);
+        return hipGetLastError();
+    });
     if (e != hipSuccess || ch->level == 1) return e;
     const Inst& I0 = ch->inst[0];
     T* D = static_cast<T*>(ch->dD);
@@ -419,8 +444,10 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
     // index each child's entries from its own offD.
     if (ch->dmode == kAllBlocks) {
         const long long perD = perC * I0.ldD;
-        hipLaunchKernelGGL((k_child_D<PM>), dim3(grid_for(K * perD, 256)), dim3(256), 0, st, src, D, ch->dInst, K,
-                           perD);
+        return in_launches(groups_of(K * perD, 256), 256, [&](long long first, unsigned grid) {
+            hipLaunchKernelGGL((k_child_D<PM>), dim3(grid), dim3(256), 0, st, src, D, ch->dInst, K, perD, first);
+            return hipGetLastError();
+        });
     } else {
         const unsigned runs = (unsigned)(M * (M - 1) / 2 * (M - 2));
         const long long perD = (perC / 2) * (M - 2) * (M - 2);
@@ -430,7 +457,6 @@ hipError_t Ops<PM>::inherit(qap_rlt2* ph, int pk, qap_rlt2* ch, const int* dfix)
             return hipGetLastError();
         });
     }
-    return hipGetLastError();
 }
 
 }  // namespace qap

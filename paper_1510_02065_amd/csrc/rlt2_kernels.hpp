@@ -384,20 +384,21 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ F, cons
 }
 
 
-// Steps 1-2 precomputation, one thread per C entry of every instance: the
-// amount each entry of block D_beta receives,
+// Steps 1-2 precomputation, one thread per C entry of every instance (this
+// launch's from `first` on): the amount each entry of block D_beta receives,
 //   CC_beta = (c_beta + b_ij / (N-1)) / (N-2),
 // after which c is cleared (B is cleared by the sweep, which does not read it).
 template <int PM>
 __global__ __launch_bounds__(256) void k_spread_prep(StoreT<PM>* __restrict__ C, const StoreT<PM>* __restrict__ B,
                                                      StoreT<PM>* __restrict__ CC, const Inst* __restrict__ inst,
                                                      const long long* __restrict__ preC, int K,
-                                                     long long totalC, const int* __restrict__ act)
+                                                     long long totalC, long long first,
+                                                     const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long x0 = first + (long long)blockIdx.x * 256, x = x0 + threadIdx.x;
     if (x >= totalC) return;
-    const int kk = find_seg_from(preC, K, (long long)blockIdx.x * 256, x);
+    const int kk = find_seg_from(preC, K, x0, x);
     if (!act[kk]) return;
     const Inst I = inst[kk];
     const int N = I.N, n1 = N - 1;
@@ -429,12 +430,13 @@ __device__ __forceinline__ T spread_b(T c, T b, int N)
 template <int PM>
 __global__ __launch_bounds__(256) void k_spread_B(StoreT<PM>* __restrict__ C, const StoreT<PM>* __restrict__ B,
                                                   const Inst* __restrict__ inst, const long long* __restrict__ preC,
-                                                  int K, long long totalC, const int* __restrict__ act)
+                                                  int K, long long totalC, long long first,
+                                                  const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long x0 = first + (long long)blockIdx.x * 256, x = x0 + threadIdx.x;
     if (x >= totalC) return;
-    const int kk = find_seg_from(preC, K, (long long)blockIdx.x * 256, x);
+    const int kk = find_seg_from(preC, K, x0, x);
     if (!act[kk]) return;
     const Inst I = inst[kk];
     const int N = I.N, n1 = N - 1;
@@ -446,11 +448,12 @@ __global__ __launch_bounds__(256) void k_spread_B(StoreT<PM>* __restrict__ C, co
 // b = 0 over the active instances (after step 1 of the level-1 ascent).
 template <int PM>
 __global__ __launch_bounds__(256) void k_clear_B(StoreT<PM>* __restrict__ B, const long long* __restrict__ preB,
-                                                 int K, long long totalB, const int* __restrict__ act)
+                                                 int K, long long totalB, long long first,
+                                                 const int* __restrict__ act)
 {
-    const long long x = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long x0 = first + (long long)blockIdx.x * 256, x = x0 + threadIdx.x;
     if (x >= totalB) return;
-    if (act[find_seg_from(preB, K, (long long)blockIdx.x * 256, x)]) B[x] = (StoreT<PM>)0;
+    if (act[find_seg_from(preB, K, x0, x)]) B[x] = (StoreT<PM>)0;
 }
 
 // The sweep kernels clear instance I's B (N^2 entries) from the workgroup
@@ -483,14 +486,15 @@ template <int PM>
 __global__ __launch_bounds__(256) void k_sweep(StoreT<PM>* __restrict__ Dd, const StoreT<PM>* __restrict__ CC,
                                                StoreT<PM>* __restrict__ B, const int* __restrict__ tri,
                                                const Inst* __restrict__ inst,
-                                               const long long* __restrict__ preWG, int K,
+                                               const long long* __restrict__ preWG, int K, long long first,
                                                const int* __restrict__ act)
 {
     using T = StoreT<PM>;
-    const int kk = find_seg(preWG, K, (long long)blockIdx.x);
+    const long long wg = first + (long long)blockIdx.x;
+    const int kk = find_seg(preWG, K, wg);
     if (!act[kk]) return;   // whole workgroup
     const Inst I = inst[kk];
-    const int lb = (int)((long long)blockIdx.x - I.wg0);
+    const int lb = (int)(wg - I.wg0);
     if (lb == 0) clear_inst_B(B, I, threadIdx.x, 256);
     const int xcd = lb & 7;
     const int local = lb >> 3;
@@ -1306,9 +1310,10 @@ __global__ __launch_bounds__(256) void k_transfer_C(StoreT<PM>* __restrict__ C, 
 template <typename T>
 __global__ __launch_bounds__(256) void k_cert_D(const T* __restrict__ Dd, const T* __restrict__ C,
                                                 double* __restrict__ ct, const Inst* __restrict__ inst,
-                                                const long long* __restrict__ preC, int K, long long totalC)
+                                                const long long* __restrict__ preC, int K, long long totalC,
+                                                long long first)
 {
-    const long long x = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const long long x = (first + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (x >= totalC) return;
     const Inst I = inst[find_seg(preC, K, x)];
@@ -1336,13 +1341,15 @@ __host__ __device__ inline int cert_stretches(int N) { return (N * (N - 1) + cer
 template <typename T>
 __global__ __launch_bounds__(kCertThreads) void k_cert_pairs(const T* __restrict__ Dd, const T* __restrict__ C,
                                                              double* __restrict__ ct, const Inst* __restrict__ inst,
-                                                             const long long* __restrict__ pre, int K)
+                                                             const long long* __restrict__ pre, int K,
+                                                             long long first_wg)
 {
     __shared__ T low[kCertThreads * kCertRegs];
-    const int kk = find_seg(pre, K, (long long)blockIdx.x);
+    const long long wg = first_wg + blockIdx.x;
+    const int kk = find_seg(pre, K, wg);
     const Inst I = inst[kk];
     const int N = I.N, n2 = N - 2, NL = N * (N - 1);
-    const int w = (int)((long long)blockIdx.x - pre[kk]);
+    const int w = (int)(wg - pre[kk]);
     const int stretches = cert_stretches(N);
     const int P = w / stretches, L0 = (w - P * stretches) * cert_pairs(N);
     const int pairs = min(cert_pairs(N), NL - L0), len = pairs * n2;
@@ -1384,9 +1391,10 @@ __global__ __launch_bounds__(kCertThreads) void k_cert_pairs(const T* __restrict
 template <typename T>
 __global__ __launch_bounds__(256) void k_cert_C(const double* __restrict__ ct, const T* __restrict__ B,
                                                 double* __restrict__ bt, const Inst* __restrict__ inst,
-                                                const long long* __restrict__ preB, int K, long long totalB)
+                                                const long long* __restrict__ preB, int K, long long totalB,
+                                                long long first)
 {
-    const long long x = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const long long x = (first + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (x >= totalB) return;
     const Inst I = inst[find_seg(preB, K, x)];

@@ -70,13 +70,50 @@ def test_level1_batch_of_more_pairs_than_one_launch():
         _same_bounds(g, F, D, 2, precision="fp32n", level=1)
 
 
-def test_level2_batch_of_more_assignments_than_one_launch():
-    # 45000 instances of N = 11: 272 million blocks of D, 16 lanes each.
+def test_level1_batch_of_more_entries_than_one_launch():
+    # 360000 instances of N = 11: 4.4 billion entries of C, a thread each in the
+    # single step 1 and in the certification.
+    F, D = qapgen.small(11, 5)
+    count = 360000
+    print("level 1, 360000 instances", flush=True)
+    with Rlt2.batch([F] * count, [D] * count, precision="fp32", level=1) as g, \
+            Rlt2(F, D, precision="fp32", level=1) as h:
+        for s in (3, 5, 6, 7):
+            g.step(s)
+            h.step(s)
+        for x, y in zip(g.bounds(certified=True), h.bounds(certified=True)):
+            np.testing.assert_array_equal(x, y[0])
+
+
+# 45000 instances of N = 11: 272 million blocks of D, 16 lanes each; 52000 of
+# them: 8.6 million facility triples, 512 threads each.
+@pytest.mark.parametrize("count", [45000, 52000])
+def test_level2_batch_of_more_assignments_than_one_launch(count):
     F, D = qapgen.small(11, 4)
-    count = 45000
-    print("level 2, 45000 instances", flush=True)
+    print(f"level 2, {count} instances", flush=True)
     with Rlt2.batch([F] * count, [D] * count, precision="fp32n") as g:
         _same_bounds(g, F, D, 2, precision="fp32n")
+        lb, cert = g.bounds(certified=True)
+        assert (cert == cert[0]).all() and cert[0] <= lb[0]
+
+
+def test_lap_batch_of_more_problems_than_one_launch():
+    # 67.2 million problems of 33 rows, a wave each, that read one matrix.
+    torch = pytest.importorskip("torch")
+    from paper_1510_02065_amd import lap_solve_device
+    count, n = 67200000, 33
+    dev = torch.device("cuda:0")
+    M = qapgen.random_matrix(n, 1, "int")
+    value = torch.zeros(count, dtype=torch.float64, device=dev)
+    print(f"{count} assignment problems", flush=True)
+    lap_solve_device(torch.full((count,), n, dtype=torch.int32, device=dev),
+                     torch.zeros(count, dtype=torch.int64, device=dev), None,
+                     torch.tensor(M.ravel(), dtype=torch.float32, device=dev), value, fp32=True, nearest=True,
+                     stream=torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    want = oracle.lap_concentrate(M)[0]
+    assert float(value.min()) == float(value.max())
+    assert abs(float(value[0]) - want) <= 1e-5 * want
 
 
 def test_children_of_more_runs_than_one_launch():
