@@ -60,30 +60,32 @@ hipError_t enqueue_iteration(qap_rlt2* h)
     return e;
 }
 
-// Copy the trace entries written since the counters were last reset, add the
-// iteration counts, then reset the counters.  `upto`: the iterations the
-// library has enqueued since then.  `counts_iteration0`: the entries come from
-// iteration 0 (recorded in the trace, not counted).  `lb0` (nullable): LB of
-// instance 0.  One copy: the counters, the bounds and the trace lie behind each
-// other, the trace with all instances' first entries first, and only `upto` of
-// its rows are read (with 16 KB per instance read whenever an entry was new, the
-// 196 level-1 children of an N = 14 node spent 0.2 of 1.0 ms here).  A caller
-// that replays steps from a graph of its own has run more iterations than the
-// library knows of: their rows take a second copy.  Nothing is left on the
-// stream: the caller may go on with the handle's steps on another one.
+// Copy the trace entries written since the last call, add the iteration counts.
+// `upto`: the iterations the library has enqueued since then.
+// `counts_iteration0`: the entries come from iteration 0 (recorded in the
+// trace, not counted).  `lb0` (nullable): LB of instance 0.  One copy: the
+// counters, the bounds and the trace lie behind each other, the trace with all
+// instances' first entries first, and only the rows up to the expected last
+// one are read (with 16 KB per instance read whenever an entry was new, the 196
+// level-1 children of an N = 14 node spent 0.2 of 1.0 ms here).  A caller that
+// replays steps from a graph of its own has run more iterations than the
+// library knows of: their rows take a second copy.
+// The counters run on, so that nothing is left on the stream and the caller may
+// go on with the handle's steps on another one; they are cleared, and the fill
+// waited for, once the rows already read are kTraceSlack or 64 KB (a fill and a
+// wait in every call: N = 10 with ten iterations 307 us, now 315).
 qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = false, double* lb0 = nullptr)
 {
     const size_t K = h->K;
-    const long long cap = h->trace_level >= 1 ? qap::kTraceCap : 0;
-    const long long rows = std::min(upto, cap);
+    const long long cap = h->trace_level >= 1 ? qap::kTraceRows : 0;
+    const long long rows = std::min(*std::max_element(h->seen.begin(), h->seen.end()) + upto, cap);
     std::vector<double> buf(3 * K + 2 * K * (size_t)rows);
     QAP_HIP(hipMemcpyAsync(buf.data(), h->dCounter, buf.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    QAP_HIP(hipMemsetAsync(h->dCounter, 0, K * sizeof(long long), h->stream));
     QAP_HIP(hipStreamSynchronize(h->stream));
     static_assert(sizeof(long long) == sizeof(double), "one slot per counter");
     std::vector<long long> cnt(K);
     std::memcpy(cnt.data(), buf.data(), K * sizeof(long long));
-    const long long all = std::min(*std::max_element(cnt.begin(), cnt.end()), cap);
+    const long long most = *std::max_element(cnt.begin(), cnt.end()), all = std::min(most, cap);
     if (all > rows) {
         const size_t have = buf.size();
         buf.resize(3 * K + 2 * K * (size_t)all);
@@ -93,13 +95,19 @@ qap_status drain_trace(qap_rlt2* h, long long upto, bool counts_iteration0 = fal
     }
     const double* trace = buf.data() + 3 * K;
     for (size_t k = 0; k < K; ++k) {
-        for (long long t = 0; t < std::min(cnt[k], all); ++t) {
+        for (long long t = h->seen[k]; t < std::min(cnt[k], all); ++t) {
             h->tLB[k].push_back(trace[((size_t)t * K + k) * 2]);
             h->tLBp[k].push_back(trace[((size_t)t * K + k) * 2 + 1]);
         }
-        if (!counts_iteration0) h->itk[k] += cnt[k];
+        if (!counts_iteration0) h->itk[k] += cnt[k] - h->seen[k];
     }
+    h->seen = cnt;
     if (lb0) *lb0 = buf[K];
+    if (cap > 0 && (most >= qap::kTraceSlack || most * (long long)K >= 4096)) {
+        QAP_HIP(hipMemsetAsync(h->dCounter, 0, K * sizeof(long long), h->stream));
+        QAP_HIP(hipStreamSynchronize(h->stream));
+        h->seen.assign(K, 0);
+    }
     return QAP_OK;
 }
 
@@ -349,6 +357,7 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     h->tLB.resize(count);
     h->tLBp.resize(count);
     h->itk.assign(count, 0);
+    h->seen.assign(count, 0);
 
     auto bail = [&](qap_status st) {
         release(h);
@@ -549,7 +558,7 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     ar.add(&h->dDm, in.Dm);
     ar.add(&h->dB0, in.B0);
     ar.add(&h->dFix, in.fix);
-    ar.add(&record, (3 + 2 * (size_t)qap::kTraceCap) * count, head.data(), head.size());
+    ar.add(&record, (3 + 2 * (size_t)qap::kTraceRows) * count, head.data(), head.size());
     ar.add(reinterpret_cast<char**>(&h->dB), (size_t)h->totalB * h->elem);
     ar.add(reinterpret_cast<char**>(&h->dC), (size_t)h->totalC * h->elem);
     if (h->level == 2) ar.add(reinterpret_cast<char**>(&h->dCC), (size_t)h->totalC * h->elem);
@@ -1203,6 +1212,7 @@ qap_status qap_rlt2_restore(qap_rlt2* h, const void* buf, uint64_t size)
     }
     QAP_HIP(hipMemsetAsync(h->dCounter, 0, h->K * sizeof(long long), h->stream));
     QAP_HIP(hipStreamSynchronize(h->stream));
+    h->seen.assign(h->K, 0);
     h->itk = itk;
     h->tLB = tl;
     h->tLBp = tp;

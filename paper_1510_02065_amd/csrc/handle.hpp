@@ -54,8 +54,9 @@ hipError_t in_launches(long long groups, int threads, F f)
     return e;
 }
 
-// Per-instance trace entries kept on the device between host reads.
-constexpr long long kTraceCap = 1024;
+// Per-instance trace entries kept on the device between host reads, and the
+// rows of the device's trace: besides those, entries already read.
+constexpr long long kTraceCap = 1024, kTraceSlack = 64, kTraceRows = kTraceCap + kTraceSlack;
 
 // LDS of a one-wave workgroup of the assignment kernels at size nmax.
 template <typename T, int SEG, bool AUC>
@@ -141,8 +142,9 @@ struct qap_rlt2 {
     double* dValC = nullptr;    // per-block values of the last step 6 (packed like B)
     double* dValB = nullptr;    // per-instance value of the last step 7
     // One record, read back in one copy: dCounter (K), dLB (2 K), dTrace.
-    double* dTrace = nullptr;   // kTraceCap x K x (LB, LB')
-    long long* dCounter = nullptr;   // trace entries of each instance since the last readback
+    double* dTrace = nullptr;   // kTraceRows x K x (LB, LB')
+    long long* dCounter = nullptr;   // trace entries of each instance
+    std::vector<long long> seen;     // those of them already read back
     int* dTri = nullptr;
     int* dAct = nullptr;        // per-instance flag: the dual ascent still runs
     double* dStop = nullptr;    // (K, UB) of the stop rule

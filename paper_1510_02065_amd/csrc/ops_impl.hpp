@@ -43,7 +43,7 @@ hipError_t launch_B_seg(qap_rlt2* h, const ClassHost& c)
     return in_launches((c.total + LPW - 1) / LPW, 64, [&](long long first, unsigned grid) {
         hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
                            h->dInst, c.dev(first * LPW), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter,
-                           kTraceCap, h->K, h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
+                           kTraceRows, h->K, h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
         return hipGetLastError();
     });
 }

@@ -344,3 +344,30 @@ def test_trace_holds_every_replayed_step():
         np.testing.assert_array_equal(x, y)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("count", [1, 3, 100])
+def test_trace_over_many_readbacks(count):
+    # The device's trace counters run on over several readbacks and are cleared
+    # now and then: calls of one iteration, of a few, of more than the device
+    # keeps (1024), and single steps, against one call.
+    inst = [qapgen.small(3 + k % 3, k) for k in range(count)]
+    args = ([f for f, _ in inst], [d for _, d in inst])
+    a, b = Rlt2.batch(*args), Rlt2.batch(*args)
+    total = 0
+    for iters in [1] * 70 + [1100, 60, 7, 60, 1024, 1]:
+        b.ascend(iters)
+        total += iters
+    for _ in range(1030):
+        for s in (3, 4, 5, 6, 7):
+            b.step(s)
+    b.ascend(2)
+    total += 1032
+    a.ascend(total)
+    assert a.status()[1].tolist() == b.status()[1].tolist() == [total] * count
+    for k in range(count):
+        assert len(a.trace_k(k)[0]) == total + 1
+        for x, y in zip(a.trace_k(k), b.trace_k(k)):
+            np.testing.assert_array_equal(x, y)
+    a.close()
+    b.close()
