@@ -200,3 +200,82 @@ def test_lap_device_batches_of_every_route(batch, dtype):
         got = a[vo[b]:vo[b] + n]
         assert v[b] == M[r, c].sum(), (b, n)
         assert sorted(got) == list(range(n)) and M[np.arange(n), got].sum() == v[b], (b, n)
+
+
+def _route_problems(batch, seed, npdt):
+    """Sizes (most tiny, some at the edges of every class) and costs of a
+    batch: integers with many ties and reals, problem by problem."""
+    rng = np.random.default_rng(seed)
+    sizes = rng.integers(0, 5, size=batch).astype(np.int32)
+    edges = np.array([1, 64, 7, 8, 9, 15, 16, 17, 31, 32, 33, 48, 49, 56, 57, 63], np.int32)
+    at = rng.choice(batch, size=min(batch, 3 * len(edges)), replace=False)
+    sizes[at] = np.resize(edges, len(at))
+    mo = np.concatenate([[0], np.cumsum(sizes.astype(np.int64) ** 2)[:-1]])
+    vo = np.concatenate([[0], np.cumsum(sizes.astype(np.int64))[:-1]])
+    total = int((sizes.astype(np.int64) ** 2).sum())
+    ties = np.repeat(np.arange(batch) % 2 == 0, sizes.astype(np.int64) ** 2)
+    cost = np.where(ties, rng.integers(0, 6, size=total), rng.uniform(-20.0, 100.0, size=total)).astype(npdt)
+    return sizes, mo, vo, cost
+
+
+def _device_solve(torch, sizes, mo, vo, cost, code, tdt, flags, step=None):
+    """Values, residuals, duals and assignments of a device-pointer solve, in
+    calls of `step` problems each (one call without)."""
+    from paper_1510_02065_amd import _binding as B
+    dev, batch = torch.device("cuda:0"), len(sizes)
+    n, m, v = (torch.tensor(x, device=dev) for x in (sizes, mo, vo))
+    c = torch.tensor(cost, dtype=tdt, device=dev)
+    nv = int(sizes.sum())
+    value = torch.zeros(batch, dtype=torch.float64, device=dev)
+    duals = torch.zeros(4 * nv, dtype=tdt, device=dev)
+    assign = torch.zeros(nv, dtype=torch.int32, device=dev)
+    stream = torch.cuda.current_stream()
+    for b in range(0, batch, step or batch):
+        count = min(step or batch, batch - b)
+        st = B.lib().qap_lap_solve(count, n[b:].data_ptr(), m[b:].data_ptr(), v[b:].data_ptr(), c.data_ptr(), code,
+                                   value[b:].data_ptr(), duals.data_ptr(), assign.data_ptr(),
+                                   B.QAP_LAP_DEVICE | B.QAP_LAP_RESIDUAL | flags, stream.cuda_stream)
+        assert st == 0, B.lib().qap_last_error()
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in (value, c, duals, assign)]
+
+
+# Batches past each change of route: the sort in one workgroup and in several,
+# three and five size classes (FP32: one, three and four).
+@pytest.mark.parametrize("dtype,batch,auction", [
+    ("fp64", 1500, False), ("fp64", 6000, False), ("fp64", 9000, False), ("fp64", 9000, True),
+    ("fp32", 1500, False), ("fp32", 9000, False), ("fp32", 33000, False), ("fp32", 33000, True),
+    ("fp32n", 6000, False), ("fp32n", 9000, False), ("fp32n", 33000, False)])
+def test_lap_results_do_not_depend_on_the_route(dtype, batch, auction):
+    """A problem's value, residual, duals and assignment are the same bits in a
+    small batch (a wave per problem) as in one that is sorted and split into
+    size classes of narrower segments, from device and from host buffers."""
+    torch = pytest.importorskip("torch")
+    from paper_1510_02065_amd import _binding as B
+    npdt = np.float64 if dtype == "fp64" else np.float32
+    tdt = torch.float64 if dtype == "fp64" else torch.float32
+    code = {"fp64": B.QAP_FP64, "fp32": B.QAP_FP32_CERTIFIED, "fp32n": B.QAP_FP32_NEAREST}[dtype]
+    flags = B.QAP_LAP_AUCTION if auction else 0
+    sizes, mo, vo, cost = _route_problems(batch, batch, npdt)
+    print(f"{dtype} batch {batch} auction={auction}", flush=True)
+    few = _device_solve(torch, sizes, mo, vo, cost, code, tdt, flags, step=1000)
+    all_at_once = _device_solve(torch, sizes, mo, vo, cost, code, tdt, flags)
+    nv = int(sizes.sum())
+    host = [np.zeros(batch), cost.copy(), np.zeros(4 * nv, npdt), np.zeros(nv, np.int32)]
+    st = B.lib().qap_lap_solve(batch, sizes.ctypes.data, mo.ctypes.data, vo.ctypes.data, host[1].ctypes.data, code,
+                               host[0].ctypes.data, host[2].ctypes.data, host[3].ctypes.data,
+                               B.QAP_LAP_RESIDUAL | flags, None)
+    assert st == 0
+    for what, x, y, z in zip(("value", "residual", "duals", "assign"), few, all_at_once, host):
+        np.testing.assert_array_equal(y, x, err_msg=f"device {what}")
+        np.testing.assert_array_equal(z, x, err_msg=f"host {what}")
+
+
+# The largest problem sets a host launch's width: 16, 32 and 64 lanes.
+@pytest.mark.parametrize("largest", [1, 8, 15, 16, 17, 32, 33, 64])
+def test_lap_host_batch_of_small_problems(largest):
+    rng = np.random.default_rng(largest)
+    sizes = rng.integers(0, largest + 1, size=70)
+    sizes[11] = largest
+    mats = [qapgen.random_matrix(int(n), i, KINDS[i % 4]) for i, n in enumerate(sizes)]
+    _check(mats, lap_solve(mats, residual=True))
