@@ -173,3 +173,66 @@ def test_level1_iterations_equal_their_steps_bitwise(precision):
             np.testing.assert_array_equal(x, y)
     a.close()
     b.close()
+
+
+# Iterations past the ones launched directly are replays of a graph of eight:
+# batches of several size classes (one schedule after the other), level 1, every
+# block stored, and each kernel of steps 1-3 that a single instance can get
+# (N = 23 in FP64: the persistent one; 27 in FP64, 33 in FP32: boxes).
+@pytest.mark.parametrize("sizes,precision,opts", [
+    ((5, 9, 13, 20), "fp64", dict(overlap=False, trace_level=2)),
+    ((5, 9, 13, 20), "fp32", dict(overlap=False)),
+    ((4, 9, 14), "fp32n", {}),
+    ((4, 11, 18), "fp64", dict(level=1)),
+    ((4, 11, 18), "fp32", dict(level=1)),
+    ((6, 9), "fp64", dict(complementary=False)),
+    ((8,), "fp64", dict(lap_solver="auction")),
+    ((23,), "fp64", {}),
+    ((27,), "fp64", {}),
+    ((33,), "fp32n", {}),
+])
+def test_replayed_iterations_equal_launches_bitwise(sizes, precision, opts):
+    inst = [qapgen.uniform(n, n) for n in sizes]
+    print(f"graph replays, {precision}, N = {sizes}, {opts}", flush=True)
+    runs = []
+    for use_graph in (True, False):
+        g = Rlt2.batch([f for f, _ in inst], [d for _, d in inst], precision=precision, use_graph=use_graph, **opts)
+        for iters in (64, 19, 9):
+            g.ascend(iters)
+        runs.append([(*g.trace_k(k), *g.read_state_k(k, want_D=n < 23)[:3],
+                      *(g.lap_values_k(k) if opts.get("trace_level") == 2 else ()))
+                     for k, n in enumerate(sizes)])
+        g.close()
+    for x, y in zip(*runs):
+        assert len(x[0]) == 1 + 64 + 19 + 9
+        for u, v in zip(x, y):
+            np.testing.assert_array_equal(u, v)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_stop_rule_inside_replayed_graphs(precision):
+    # Instances that stop in the middle of a replayed graph of eight iterations
+    # keep the state of their last one while the others go on.
+    inst = [qapgen.uniform(n, n) for n in (7, 10, 13)]
+    args = ([f for f, _ in inst], [d for _, d in inst])
+    free = Rlt2.batch(*args, precision=precision, overlap=False, use_graph=False)
+    free.ascend(120)
+    UB = 2.0 * max(free.trace_k(k)[0][-1] for k in range(3))
+    lbp = [free.trace_k(k)[1] for k in range(3)]
+    # The progress below which at least one instance first falls after iteration
+    # 69, five into the replays, and the others before it or later.
+    K = max(float(lbp[k][1:70].min()) for k in range(3)) * (1 - 1e-9) / UB
+    stops = [next((t for t in range(1, 121) if lbp[k][t] < K * UB), 120) for k in range(3)]
+    print(f"{precision}: stops after {stops}", flush=True)
+    assert max(stops) > 64
+    runs = []
+    for use_graph in (True, False):
+        g = Rlt2.batch(*args, precision=precision, overlap=False, use_graph=use_graph, K=K, UB=UB)
+        g.ascend(120)
+        assert g.status()[1].tolist() == stops
+        runs.append([(*g.trace_k(k), *g.read_state_k(k)) for k in range(3)])
+        g.close()
+    free.close()
+    for x, y in zip(*runs):
+        for u, v in zip(x, y):
+            np.testing.assert_array_equal(u, v)
