@@ -192,6 +192,38 @@ def test_children_inherit_parent_state(precision, level):
     g.close()
 
 
+# Children whose runs of D (a facility pair's row, for all locations) are
+# shorter than a workgroup (24 entries, of a parent of N = 5), just longer (336,
+# of 9), and take several rounds of it.
+@pytest.mark.parametrize("N,precision", [(5, "fp32"), (9, "fp64"), (9, "fp32"), (10, "fp32n"), (13, "fp64"),
+                                         (16, "fp32")])
+def test_children_copy_their_parents_D(N, precision):
+    F, D = qapgen.small(N, 4)
+    g = Rlt2(F, D, precision=precision)
+    g.ascend(2)
+    n2, M = N - 2, N - 1
+    Dst = g.read_state()[3].reshape(-1, n2, n2)
+    fac, loc = [0, N - 1, 2, 3], [N - 1, 0, 2, 1]
+    print(f"children of N={N} {precision}", flush=True)
+    ch = g.children(0, fac, loc)
+    I, J, K, L = layout.c_index_arrays(N)
+    at = np.full((N, N, N, N), -1)
+    at[I, J, K, L] = np.arange(len(I))
+    Ic, Jc, Kc, Lc = layout.c_index_arrays(M)
+    for c, (a, b) in enumerate(zip(fac, loc)):
+        fr = np.array([i for i in range(N) if i != a])
+        lr = np.array([j for j in range(N) if j != b])
+        got = ch.read_state_k(c)[3].reshape(-1, M - 2, M - 2)
+        for x in range(len(Ic)):
+            i, j, k, n = fr[Ic[x]], lr[Jc[x]], fr[Kc[x]], lr[Lc[x]]
+            rows = [r for r in range(N) if r not in (i, k)].index(a)
+            cols = [q for q in range(N) if q not in (j, n)].index(b)
+            block = np.delete(np.delete(Dst[at[i, j, k, n]], rows, axis=0), cols, axis=1)
+            np.testing.assert_array_equal(got[x], block)
+    ch.close()
+    g.close()
+
+
 def test_children_errors():
     F, D = qapgen.small(8, 0)
     g = Rlt2(F, D)
