@@ -65,6 +65,32 @@ def test_noalloc_matches_allocating_entry_point(dtype):
         assert np.isfinite(got[0]).all()
 
 
+@pytest.mark.parametrize("dtype", ["fp64", "fp32"])
+def test_noalloc_sort_starts_from_what_the_last_call_left(dtype):
+    torch = pytest.importorskip("torch")
+    L = B.lib()
+    npdt = np.float64 if dtype == "fp64" else np.float32
+    tdt = torch.float64 if dtype == "fp64" else torch.float32
+    code = B.QAP_FP64 if dtype == "fp64" else B.QAP_FP32_CERTIFIED
+    stream = torch.cuda.Stream()
+    # Sorted by several workgroups, by one, by several again and not at all:
+    # the shared array keeps each call's list, ranges and counters for the next.
+    for count, seed in ((9000, 1), (1500, 2), (5000, 3), (90, 4)):
+        print(f"noalloc {dtype}: batch {count}, seed {seed}", flush=True)
+        sizes, mo, vo, cost = _problems(count, seed, npdt)
+        got = _solve(L.qap_lap_solve_noalloc, torch, sizes, mo, vo, cost, code, tdt, stream)
+        ref = [[], [], [], []]
+        for b in range(0, count, 1000):   # calls that need no list
+            e = min(b + 1000, count)
+            m0, m1 = mo[b], mo[e - 1] + sizes[e - 1].astype(np.int64) ** 2
+            part = _solve(L.qap_lap_solve, torch, sizes[b:e], mo[b:e] - m0, vo[b:e] - vo[b], cost[m0:m1], code, tdt,
+                          stream)
+            for r, x in zip(ref, part):
+                r.append(x)
+        for r, g, what in zip(ref, got, ("value", "residual", "duals", "assign")):
+            np.testing.assert_array_equal(g, np.concatenate(r), err_msg=what)
+
+
 def test_noalloc_rejects_what_it_cannot_do():
     L = B.lib()
     n = np.array([3], np.int32)
