@@ -98,21 +98,26 @@ def test_level2_batch_of_more_assignments_than_one_launch(count):
 
 
 def test_lap_batch_of_more_problems_than_one_launch():
-    # 67.2 million problems of 33 rows, a wave each, that read one matrix.
+    # 67.2 million problems, 100000 of 33 rows and the others of one: the launch
+    # of the largest size class has a wave per problem of the batch.
     torch = pytest.importorskip("torch")
     from paper_1510_02065_amd import lap_solve_device
-    count, n = 67200000, 33
+    count, large, n = 67200000, 100000, 33
     dev = torch.device("cuda:0")
     M = qapgen.random_matrix(n, 1, "int")
-    value = torch.zeros(count, dtype=torch.float64, device=dev)
+    sizes = torch.ones(count, dtype=torch.int32, device=dev)
+    sizes[:large] = n
+    entries = sizes.long() ** 2
+    at = torch.cumsum(entries, 0) - entries
+    small = torch.arange(count - large, device=dev) % 1000
+    cost = torch.cat([torch.tensor(M.ravel(), device=dev).repeat(large), small.double()]).float()
+    value = torch.full((count,), -1.0, dtype=torch.float64, device=dev)
     print(f"{count} assignment problems", flush=True)
-    lap_solve_device(torch.full((count,), n, dtype=torch.int32, device=dev),
-                     torch.zeros(count, dtype=torch.int64, device=dev), None,
-                     torch.tensor(M.ravel(), dtype=torch.float32, device=dev), value, fp32=True, nearest=True,
-                     stream=torch.cuda.current_stream())
+    lap_solve_device(sizes, at, None, cost, value, fp32=True, nearest=True, stream=torch.cuda.current_stream())
     torch.cuda.synchronize()
+    assert bool((value[large:] == small).all())
     want = oracle.lap_concentrate(M)[0]
-    assert float(value.min()) == float(value.max())
+    assert float(value[:large].min()) == float(value[:large].max())
     assert abs(float(value[0]) - want) <= 1e-5 * want
 
 
