@@ -293,15 +293,16 @@ qap_status qap_subproblem(int N, const double* F, const double* D, int m, const 
  *         assignment (not unique when there are ties).
  * flags   QAP_LAP_DEVICE: every pointer above is device memory (of the
  *         calling thread's current device) and the call is asynchronous on
- *         `stream`; for more than 1024 problems a device pass sorts
- *         them by size into a workspace of 4 bytes per problem taken from the
- *         stream-ordered allocator (hipMallocAsync) and released the same way.  Sizes
- *         outside [0, 64] are not checked on the host: such a problem's
+ *         `stream`; for more than 1024 problems a device pass sorts them by
+ *         size into a workspace of 4 bytes per problem taken from the
+ *         stream-ordered allocator (hipMallocAsync) and released the same way.
+ *         Sizes outside [0, 64] are not checked on the host: such a problem's
  *         value is NaN and nothing else of it is written.  Otherwise all
  *         pointers are host memory, sizes are checked (QAP_EINVAL) and the
  *         call is synchronous.  QAP_LAP_RESIDUAL: write residuals in place.
- *         Problems of size n run in segments of the narrowest of 8, 16, 32
- *         or 64 lanes that holds n, several problems per wave.
+ *         Problems run in segments of 16, 32 or 64 lanes, several problems
+ *         per wave where the segments are narrow; the width follows from the
+ *         batch and the sizes, and the results do not depend on it.
  *         QAP_LAP_AUCTION: solve by the auction algorithm
  *         (QAP_LAP_SOLVER_AUCTION); value is then the dual value of the final
  *         prices (<= the optimum, within n * 2^-38 max|M| of it in FP64,
@@ -363,8 +364,8 @@ qap_status qap_rlt2_load_state(qap_rlt2* h, int k, const double* lb, const doubl
                                const double* D);
 
 /* Snapshot of the whole handle (every instance's LB, B, C, D, stop flags,
- * iteration counts and traces) into host memory, for checkpointing a long run (Section 7).  *size receives the bytes needed;
- * with buf NULL or capacity < *size nothing else is written (and QAP_OK is
+ * iteration counts and traces) into host memory, for checkpointing a long run
+ * (Section 7).  *size receives the bytes needed; with buf NULL or capacity < *size nothing else is written (and QAP_OK is
  * returned when buf is NULL, QAP_EINVAL otherwise). */
 qap_status qap_rlt2_snapshot(qap_rlt2* h, void* buf, uint64_t capacity, uint64_t* size);
 

@@ -484,10 +484,12 @@ qap_status make_handle(int count, const int32_t* Ns, const qap_rlt2_opts& o, con
     // sweep classes' order, a second stream and the events between them.
     // Where every size is small the launches and events per size take longer
     // than what they overlap (ten iterations: 40 nodes of N = 3..6 1.42 ms
-    // overlapped and 0.70 in sequence, 40 of 8..14 5.1 and 4.8; four of 100
-    // nodes of N = 10..14 6.96 and 6.92); with larger ones it is the faster
-    // schedule (14 nodes of N = 10..16 4.02 and 4.07, 48 of 10..18 8.0 and
-    // 8.3, 48 of 10..22 26.4 and 27.9).
+    // overlapped and 0.70 in sequence, 40 of 8..14 5.1 and 4.8); where the
+    // largest is well above, it is the faster schedule (48 nodes of N = 10..18
+    // 8.0 and 8.3 ms, 48 of 10..22 26.4 and 27.9).  Between the two they are
+    // within 1.5 % of each other (100 nodes of N = 10..14 6.96 and 6.92, 14 of
+    // 10..16 4.02 and 4.07), so where in that range the line lies, and whether it
+    // goes by the largest size or by the number of sizes, makes no difference.
     if (o.overlap && h->level == 2 && h->dmode == qap::kHalfStore && h->sweep_cls.size() > 1 &&
         h->Nmax >= kOverlapMinN) {
         for (const qap::SweepClass& sc : h->sweep_cls) {

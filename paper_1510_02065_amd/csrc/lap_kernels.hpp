@@ -1,8 +1,7 @@
 // Cost-concentration kernels (Section 4.1 of arXiv 1510.02065).  Each wave
 // works on 64/SEG assignment problems at once (one per SEG-lane segment), each
-// staged in the wave's own LDS region; a workgroup holds WPB independent
-// waves.  Problems of every instance of a handle are served by one launch per
-// segment-size class.
+// staged in the wave's own LDS region; a workgroup is one wave.  Problems of
+// every instance of a handle are served by one launch per segment-size class.
 #pragma once
 #include "lap_auction.hpp"
 #include "lap_slots.hpp"
@@ -13,7 +12,7 @@ namespace qap {
 // Problems of a family, for the instances of one segment-size class:
 // cls[0..Kc) are the instance ids and pre[] the prefix sums of their problem
 // counts, so problem x belongs to instance cls[find_seg(pre, Kc, x)].  A launch
-// takes the problems from `first` on.
+// of k_lap_family_s takes the problems from `first` on.
 struct FamilyClass {
     const int* cls;
     const long long* pre;
@@ -208,7 +207,7 @@ __global__ __launch_bounds__(64) void k_lap_B_s(StoreT<PM>* __restrict__ B, cons
     constexpr int LPW = 64 / SEG;
     const int seg = threadIdx.x / SEG;
     const int lane = threadIdx.x & (SEG - 1);
-    const long long x = fc.first + (long long)blockIdx.x * LPW + seg;
+    const long long x = (long long)blockIdx.x * LPW + seg;
     const int k = x < fc.total ? fc.cls[x] : 0;
     const bool active = x < fc.total && act[k];
     const Inst I = inst[k];

@@ -39,13 +39,12 @@ hipError_t launch_B_seg(qap_rlt2* h, const ClassHost& c)
     constexpr int LPW = 64 / SEG;
     const size_t lds = slot_lds<T, SEG, AUC>(c.nmax);
     if (lds > h->lds_limit) return hipErrorInvalidConfiguration;
+    const unsigned grid = (unsigned)((c.total + LPW - 1) / LPW);   // a wave per instance at most
     const bool tr = h->trace_level >= 1;
-    return in_launches((c.total + LPW - 1) / LPW, 64, [&](long long first, unsigned grid) {
-        hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
-                           h->dInst, c.dev(first * LPW), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter,
-                           kTraceRows, h->K, h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
-        return hipGetLastError();
-    });
+    hipLaunchKernelGGL((k_lap_B_s<PM, SEG, AUC>), dim3(grid), dim3(64), lds, h->stream, static_cast<T*>(h->dB),
+                       h->dInst, c.dev(0), c.nmax, h->dLB, tr ? h->dTrace : nullptr, h->dCounter, kTraceRows, h->K,
+                       h->trace_level >= 2 ? h->dValB : nullptr, h->dSigma, h->dAct, h->dStop);
+    return hipGetLastError();
 }
 
 // Lanes per problem: the narrowest segment that holds the class's problems
