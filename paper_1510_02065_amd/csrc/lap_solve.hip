@@ -44,17 +44,23 @@ namespace qap {
 // 73 | 80, 254 | 200, 83 | 79, 346 | 234, 840 | 411, 223 | 175, 1063 | 477,
 // 3095 | 1283 and 2064 | 868.)  So: one class while the chip holds all but a
 // few rounds of the problems at once, a wave each (its LDS holds 1024 of 64
-// rows in FP64 and 2304 in FP32), and more the more problems there are.
+// rows in FP64 and 2304 in FP32), and more the more problems there are.  The
+// auction in FP64, whose problems take longer, has its classes from 3073
+// problems on: 4000 of 2..8 rows 110 us (one class 161, classes of 8, 16, 32 and
+// 64 lanes 152 with the bidding loop before), of 8..16 264 (434, 579), of 2..30
+// 750 (633, 1358), of 2..64 2587 (1988, 5594).  With fewer problems one class
+// loses less on narrow ranges than it gains on wide ones (2000 of 8..16 273 and
+// 224 us, of 2..64 1779 and 2476), and it is below the 148 and 496 of before.
 struct Classes {
     int count;
     int limit[5];   // largest size of each class, rising
 };
-inline Classes classes_for(int batch, int dtype)
+inline Classes classes_for(int batch, int dtype, int solver)
 {
     if (dtype == QAP_FP64)
-        return batch <= 4096   ? Classes{1, {64}}
-               : batch <= 8192 ? Classes{3, {16, 32, 64}}
-                               : Classes{5, {16, 32, 48, 56, 64}};
+        return batch <= (solver == QAP_LAP_SOLVER_AUCTION ? 3072 : 4096) ? Classes{1, {64}}
+               : batch <= 8192                                          ? Classes{3, {16, 32, 64}}
+                                                                        : Classes{5, {16, 32, 48, 56, 64}};
     return batch <= 8192    ? Classes{1, {64}}
            : batch <= 32768 ? Classes{3, {16, 32, 64}}
                             : Classes{4, {16, 32, 48, 64}};
@@ -186,7 +192,7 @@ hipError_t solve_device(int batch, const int32_t* n, const int64_t* mat_off, con
                         int dtype, double* value, void* duals, int32_t* assign, int wr, int solver, hipStream_t st,
                         int32_t* ws)
 {
-    const qap::Classes cl = qap::classes_for(batch, dtype);
+    const qap::Classes cl = qap::classes_for(batch, dtype, solver);
     if (!ws)
         return QAP_OPS(dtype, lap_batch(st, cl.limit[0], batch, nullptr, nullptr, n, mat_off, vec_off, cost, value,
                                         duals, assign, wr, solver));
@@ -315,7 +321,7 @@ qap_status qap_lap_solve(int batch, const int32_t* n, const int64_t* mat_off, co
     // 30 rows by the auction took 12.9 ms in all with LDS for 64 rows and a wave
     // each, 11.6 now; the canonical solve, whose time is mostly the copies', 10.5
     // either way.
-    const qap::Classes cl = qap::classes_for(batch, dtype);
+    const qap::Classes cl = qap::classes_for(batch, dtype, solver);
     int first = 0;
     for (int c = cl.count - 1; c >= 0; --c) {
         int end = first;

@@ -243,7 +243,8 @@ def _device_solve(torch, sizes, mo, vo, cost, code, tdt, flags, step=None):
 # Batches past each change of route: the sort in one workgroup and in several,
 # three and five size classes (FP32: one, three and four).
 @pytest.mark.parametrize("dtype,batch,auction", [
-    ("fp64", 1500, False), ("fp64", 6000, False), ("fp64", 9000, False), ("fp64", 9000, True),
+    ("fp64", 1500, False), ("fp64", 6000, False), ("fp64", 9000, False), ("fp64", 3072, True),
+    ("fp64", 3073, True), ("fp64", 9000, True),
     ("fp32", 1500, False), ("fp32", 9000, False), ("fp32", 33000, False), ("fp32", 33000, True),
     ("fp32n", 6000, False), ("fp32n", 9000, False), ("fp32n", 33000, False)])
 def test_lap_results_do_not_depend_on_the_route(dtype, batch, auction):
