@@ -40,16 +40,16 @@ HBM_PEAK_GBS = 8000.0
 # until the counters are taken again.
 TRAFFIC = {
     # (step, N, precision, complementary pairs once): (csrc digest, scaled FETCH bytes, scaled WRITE bytes)
-    (4, 25, "fp64", True): ("830b74868359d9a4", 374148.4 * 1024 * 2.0, 776457.5 * 1024 * 1.0),
-    (3, 25, "fp64", True): ("830b74868359d9a4", 397701.1 * 1024 * 2.0, 743985.9 * 1024 * 1.0),
-    (4, 25, "fp32", True): ("830b74868359d9a4", 187225.0 * 1024 * 2.0, 380895.2 * 1024 * 1.0),
-    (3, 25, "fp32", True): ("830b74868359d9a4", 211186.4 * 1024 * 2.0, 390438.6 * 1024 * 1.0),
-    (4, 25, "fp32n", True): ("830b74868359d9a4", 187192.9 * 1024 * 2.0, 386455.8 * 1024 * 1.0),
-    (3, 25, "fp32n", True): ("830b74868359d9a4", 201855.3 * 1024 * 2.0, 372027.9 * 1024 * 1.0),
-    (4, 40, "fp64", True): ("830b74868359d9a4", 6876860.7 * 1024 * 2.0, 14666254.0 * 1024 * 1.0),
-    (3, 40, "fp64", True): ("830b74868359d9a4", 10694057.1 * 1024 * 2.0, 16854063.1 * 1024 * 1.0),
-    (4, 40, "fp32", True): ("830b74868359d9a4", 3441420.8 * 1024 * 2.0, 7976761.6 * 1024 * 1.0),
-    (3, 40, "fp32", True): ("830b74868359d9a4", 4254256.1 * 1024 * 2.0, 8223786.0 * 1024 * 1.0),
+    (4, 25, "fp64", True): ("613a870d34ee0d22", 374167.1 * 1024 * 2.0, 776919.9 * 1024 * 1.0),
+    (3, 25, "fp64", True): ("613a870d34ee0d22", 397701.2 * 1024 * 2.0, 743987.3 * 1024 * 1.0),
+    (4, 25, "fp32", True): ("613a870d34ee0d22", 187230.9 * 1024 * 2.0, 380841.2 * 1024 * 1.0),
+    (3, 25, "fp32", True): ("613a870d34ee0d22", 211189.4 * 1024 * 2.0, 390443.1 * 1024 * 1.0),
+    (4, 25, "fp32n", True): ("613a870d34ee0d22", 187227.0 * 1024 * 2.0, 386584.9 * 1024 * 1.0),
+    (3, 25, "fp32n", True): ("613a870d34ee0d22", 201860.3 * 1024 * 2.0, 372028.5 * 1024 * 1.0),
+    (4, 40, "fp64", True): ("613a870d34ee0d22", 6876860.8 * 1024 * 2.0, 14662431.0 * 1024 * 1.0),
+    (3, 40, "fp64", True): ("613a870d34ee0d22", 10687909.9 * 1024 * 2.0, 16847705.7 * 1024 * 1.0),
+    (4, 40, "fp32", True): ("613a870d34ee0d22", 3441418.3 * 1024 * 2.0, 7965747.3 * 1024 * 1.0),
+    (3, 40, "fp32", True): ("613a870d34ee0d22", 4254600.8 * 1024 * 2.0, 8224572.9 * 1024 * 1.0),
 }
 
 

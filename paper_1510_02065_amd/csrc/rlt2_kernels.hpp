@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void k_sweep(StoreT<PM>* __restrict__ Dd, cons
 // Bound by HBM: the runs of BS entries start at any 8 (4) byte boundary and
 // the lines they share with the neighbouring boxes leave the L2 before those
 // are read, so a run moves about one 64-byte sector more on reads and half of
-// one more on writes than it holds (N = 40 FP64: 39.2 GB for 28.2 GB of
+// one more on writes than it holds (N = 40 FP64: 39.1 GB for 28.2 GB of
 // entries, at 4.8 TB/s).  Longer edges therefore move less but hold fewer
 // workgroups per CU.  Measured (ms, one sweep): FP64 N = 31 1.55 with edge 16
 // and 1.91 with 11, N = 40 8.1 with 14 and 10.0 with 20 (one workgroup per

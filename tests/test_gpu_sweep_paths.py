@@ -1,6 +1,6 @@
 """The steps 1-3 kernels for one stored block per complementary pair (one
-workgroup per facility triple when the triple fits in LDS, location cubes
-otherwise) against the every-block comparison path, at the sizes where the
+workgroup per facility triple when the triple fits in LDS, boxes of
+locations otherwise) against the every-block comparison path, at the sizes where the
 choice changes: bit for bit after two iterations, on the trace and on every
 concentration's value."""
 import numpy as np

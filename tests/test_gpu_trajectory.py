@@ -181,7 +181,7 @@ def test_clustered25_fp32_certified_hundred_iterations(clustered25_oracle):
     assert cert <= ref_lb[-1]
 
 
-# ---- large N: the cube sweep and the wide assignment classes ----------------------
+# ---- large N: the box sweep and the wide assignment classes -----------------------
 
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("N", [27, 35])
